@@ -153,7 +153,7 @@ Workspace plan_workspace(const eph_ctx *c, int N, int precision, int64_t nkl, in
   if (precision == EPH_BF16X3) t += 4 * bf16_w_elems(c->nre, c->nw, (int)ncol);  // bf16 hi/lo of g
   if (wave) {
     t += NQ * (nw + nm) * EPH_MAX_TEMPS * 8;                        // occupation tables
-    t += NQ * nw * 4;                                               // float energies (prefilter)
+    t += NQ * nw * 4;                                               // sums of the planes of a launch (at most)
   } else {
     t += NQ * nw * 10;                                              // energy-sorted lines
   }
@@ -549,6 +549,13 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
       (void)hipGetLastError();
       max_states = std::max<int64_t>(gmax, (int64_t)(xcap / ws.per_state));
     }
+    // the wave kernel takes states one by one; groups bound the staging of
+    // transition rates and are the workgroup form's unit of work
+    const bool groups = gwave == 0 || gr;
+    int64_t ng = ns;
+    int64_t *gstart = nullptr;
+    std::vector<int64_t> hg;
+    if (groups) {
     EPH_HIP(c, c->grp_tmp.ensure(sizeof(int64_t) * 2 * (ns + 1)));
     int64_t *flag = c->grp_tmp.as<int64_t>(), *pos = flag + ns + 1;
     EPH_HIP(c, c->scan_tmp.ensure(sizeof(int64_t) * std::max(scan_tmp_elems(nkl + 1), scan_tmp_elems(ns))));
@@ -558,13 +565,18 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
     EPH_HIP(c, hipMemcpyAsync(&lastpf[0], pos + ns - 1, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     EPH_HIP(c, hipMemcpyAsync(&lastpf[1], flag + ns - 1, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     EPH_HIP(c, hipStreamSynchronize(st));
-    int64_t ng = lastpf[0] + lastpf[1];
+    ng = lastpf[0] + lastpf[1];
     EPH_HIP(c, c->grp_start.ensure(sizeof(int64_t) * (ng + 1)));
-    int64_t *gstart = c->grp_start.as<int64_t>();
+    gstart = c->grp_start.as<int64_t>();
     EPH_HIP(c, launch_group_starts(ns, flag, pos, gstart, st));
-    std::vector<int64_t> hg(ng + 1);
+    hg.resize(ng + 1);
     EPH_HIP(c, hipMemcpyAsync(hg.data(), gstart, sizeof(int64_t) * (ng + 1), hipMemcpyDeviceToHost, st));
+    }
+    auto gfirst = [&](int64_t g) { return groups ? hg[g] : g; };  // first state of a group
 
+    // temperatures per row of the occupation tables (the k-batch kernels read
+    // full rows)
+    const int occ_row = kbatch_q > 0 ? EPH_MAX_TEMPS : occ_stride(p->n_temps);
     // ---- energy-sorted final-state lines (workgroup form) or occupation
     //      tables (wave form); largest phonon energy ----
     if (gwave == 0) {
@@ -575,10 +587,10 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
     } else {
       double kts[EPH_MAX_TEMPS];
       for (int t = 0; t < p->n_temps; t++) kts[t] = U.kb_evk * p->temps_K[t];
-      EPH_HIP(c, c->occ.ensure(sizeof(double) * NQ * (nw + nm) * EPH_MAX_TEMPS));
+      EPH_HIP(c, c->occ.ensure(sizeof(double) * NQ * (nw + nm) * occ_row));
       EPH_HIP(c, launch_occupations(NQ, nw, nm, c->eps.as<double>(), c->om.as<double>(), p->mu_eV, p->n_temps, kts,
-                                    p->omega_cut_eV, c->occ.as<double>(),
-                                    c->occ.as<double>() + (size_t)NQ * nw * EPH_MAX_TEMPS, st));
+                                    p->omega_cut_eV, occ_row, c->occ.as<double>(),
+                                    c->occ.as<double>() + (size_t)NQ * nw * occ_row, st));
     }
     EPH_HIP(c, launch_max_nonneg(NQ * nm, c->om.as<double>(), ctr + 1, st));
     EPH_HIP(c, tm.mark(&e_prep));
@@ -617,25 +629,42 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
     a.inv_tau = inv_tau_s;
     a.ns_total = ns;
     a.st_counts = c->state_cnt.as<int64_t>();
+    if (gwave > 0 && kbatch_q == 0) {  // over the group lists, which are done with
+      EPH_HIP(c, c->grp_tmp.ensure(sizeof(int64_t) * 2 * (ns + 1)));
+      a.kv_counts = c->grp_tmp.as<int64_t>();
+    }
     a.n_kq = ctr + 2;
     a.n_vertex = ctr + 6;
     a.evec32 = fp32 ? c->evec32.as<float2>() : nullptr;
-    a.eps32 = nullptr;
-    if (gwave > 0) {  // the wave kernel prefilters from a float copy of the energies
-      EPH_HIP(c, c->eps32.ensure(sizeof(float) * NQ * nw));
-      EPH_HIP(c, launch_real_to_f32(NQ * nw, c->eps.as<double>(), c->eps32.as<float>(), st));
-      a.eps32 = c->eps32.as<float>();
-    }
     a.uu32 = fp32 ? c->uu32.as<float2>() : nullptr;
     a.occ_f = c->occ.as<double>();
-    a.occ_n = c->occ.as<double>() + (size_t)NQ * nw * EPH_MAX_TEMPS;
+    a.occ_n = c->occ.as<double>() + (size_t)NQ * nw * occ_row;
     a.occ32_f = a.occ32_n = nullptr;
     if (gwave > 0 && fp32) {  // FP32 copies of the occupation tables
-      const size_t no = (size_t)NQ * (nw + nm) * EPH_MAX_TEMPS;
+      const size_t no = (size_t)NQ * (nw + nm) * occ_row;
       EPH_HIP(c, c->occ32.ensure(sizeof(float) * no));
       EPH_HIP(c, launch_real_to_f32((int64_t)no, c->occ.as<double>(), c->occ32.as<float>(), st));
       a.occ32_f = c->occ32.as<float>();
-      a.occ32_n = c->occ32.as<float>() + (size_t)NQ * nw * EPH_MAX_TEMPS;
+      a.occ32_n = c->occ32.as<float>() + (size_t)NQ * nw * occ_row;
+    }
+    // q3 planes per launch of the wave kernel: one where the states alone fill
+    // the card (the plane's q-side tables then stay in the L2s), else as many
+    // as it takes for kFillBlocks workgroups; the sums of the planes of a
+    // launch are kept apart and added in plane order, so the results do not
+    // depend on the number
+    constexpr int64_t kFillBlocks = 16384;
+    int planes = 1;
+    if (gwave > 0 && ns < kFillBlocks) {
+      const int64_t plane_bytes = ns * (8 * p->n_temps + 32);
+      const int64_t count_bytes = gr ? 8 * ns : 0;  // per plane and once more
+      planes = (int)std::min<int64_t>(N, (kFillBlocks + ns - 1) / ns);
+      if (p->mem_budget_bytes > 0) planes = (int)std::min<int64_t>(planes, (NQ * nw * 4 - count_bytes) / (plane_bytes + count_bytes));
+      planes = std::max(planes, 1);
+      if (planes > 1) {
+        EPH_HIP(c, c->part.ensure(plane_bytes * planes));
+        a.part_tau = c->part.as<double>();
+        a.part_cnt = reinterpret_cast<int64_t *>(a.part_tau + (size_t)planes * p->n_temps * ns);
+      }
     }
     const int ncol = c->box.count() * nm * nw;
     if (kbatch_q > 0) {  // ---- the k-batch order (ablation): q batches, all states each ----
@@ -695,15 +724,18 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
       EPH_HIP(c, launch_zero(c->gcur.p, sizeof(int64_t) * (ns + 1), st));
       a.stidx = c->stidx.as<int32_t>();
       a.g_cursor = c->gcur.as<int64_t>();
-      a.ng = ng;
-      a.gstart = gstart;
-      a.s_base = 0;
+      if (planes > 1) {
+        EPH_HIP(c, c->gslot.ensure(sizeof(int64_t) * (planes + 1) * ns));
+        a.g_slot = c->gslot.as<int64_t>();
+      }
+      a.s_lo = a.s_base = 0;
+      a.ns_launch = ns;
       a.X = nullptr;
-      for (int q3 = 0; q3 < N; q3++) {
+      for (int q3 = 0; q3 < N; q3 += planes) {
         a.q3_lo = q3;
-        a.q3_hi = q3 + 1;
-        a.q3_cur = q3;
+        a.q3_hi = std::min(q3 + planes, N);
         EPH_HIP(c, launch_rates_wave(EPH_FP64, a, st, kCount));
+        if (planes > 1) EPH_HIP(c, launch_plane_counts(a, 1, st));
       }
       gam.reset(new eph_gamma());
       gam->ctx = c;
@@ -773,10 +805,12 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
     int64_t g0 = 0;
     while (g0 < ng) {
       int64_t g1 = g0 + 1;
-      while (g1 < ng && hg[g1 + 1] - hg[g0] <= max_states &&
-             (!spill || hrow[hg[g1 + 1]] - hrow[hg[g0]] <= stage_cap))
-        g1++;
-      const int64_t sa = hg[g0], sb = hg[g1];
+      while (g1 < ng && gfirst(g1 + 1) - gfirst(g0) <= max_states &&
+             (!spill || hrow[gfirst(g1 + 1)] - hrow[gfirst(g0)] <= stage_cap)) {
+        if (!groups) g1 = std::min(ng, g0 + max_states);
+        else g1++;
+      }
+      const int64_t sa = gfirst(g0), sb = gfirst(g1);
       EPH_HIP(c, c->xbuf.ensure(xrow * (size_t)(sb - sa)));
       if (p->precision == EPH_BF16X3) EPH_HIP(c, c->abf.ensure(4 * bf16_a_elems(c->nre, nw) * (size_t)(sb - sa)));
       int eb0, eb1, eb2;
@@ -794,8 +828,9 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
                                   c->wt64.as<double2>(), c->evec.as<double2>(), c->tab.as<double2>(),
                                   c->xbuf.as<double2>(), st));
       a.ng = g1 - g0;
-      a.gstart = gstart + g0;
-      a.s_base = sa;
+      a.gstart = gstart ? gstart + g0 : nullptr;
+      a.s_base = a.s_lo = sa;
+      a.ns_launch = sb - sa;
       a.X = c->xbuf.p;
       EPH_HIP(c, tm.mark(&eb1));
       if (gr) {
@@ -805,13 +840,16 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
         a.g_stride = spill ? stage_cap : gam->nnz;
       }
       if (gwave > 0) {
-        // one launch per q3 plane: every resident wave then works on the same
-        // plane, whose q-side tables stay in the XCD's L2
-        for (int q3 = 0; q3 < N; q3++) {
+        for (int q3 = 0; q3 < N; q3 += planes) {
           a.q3_lo = q3;
-          a.q3_hi = q3 + 1;
-          a.q3_cur = q3;
+          a.q3_hi = std::min(q3 + planes, N);
+          if (gr && planes > 1) {  // where each plane's rows start
+            EPH_HIP(c, launch_rates_wave(EPH_FP64, a, st, kCount));
+            EPH_HIP(c, launch_plane_counts(a, 0, st));
+          }
           EPH_HIP(c, launch_rates_wave(p->precision, a, st, gr ? kEmit : kRates));
+          if (planes > 1) EPH_HIP(c, launch_add_planes(a, st));
+          c->launches[1]++;
         }
       } else
         EPH_HIP(c, launch_rates(p->precision, a, st));
@@ -826,10 +864,10 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
       }
       e_batch.insert(e_batch.end(), {eb0, eb1, eb2});
       c->launches[0]++;
-      c->launches[1] += gwave > 0 ? N : 1;
+      if (gwave == 0) c->launches[1]++;
       g0 = g1;
     }
-    EPH_HIP(c, launch_summarize(ns, c->state_cnt.as<int64_t>(), inv_tau_s, ctr + 3, st));
+    EPH_HIP(c, launch_summarize(ns, c->state_cnt.as<int64_t>(), a.kv_counts, inv_tau_s, ctr + 2, st));
     if (gr) EPH_HIP(c, launch_check_rows(ns, c->gcur.as<int64_t>(), gam->row.as<int64_t>(), ctr + 7, st));
     if (gr) {
       gam->h_row = std::move(hrow);

@@ -87,7 +87,7 @@ struct eph_ctx {
   eph::DevBuf tab;                      // e^{2 pi i m/N}, [N] double2
   eph::DevBuf eps, evec, vel, om, uu;   // grid tables
   eph::DevBuf evec32, uu32;             // FP32 copies for reduced forms
-  eph::DevBuf eps32;                    // float band energies (prefilter of long lines)
+  eph::DevBuf part;                     // per-plane sums of a launch of several planes
   eph::DevBuf cnt, offs, scan_tmp, subset;
   eph::DevBuf grp_start, grp_tmp;
   eph::DevBuf line_e, line_key;         // energy-sorted p-lines
@@ -99,6 +99,7 @@ struct eph_ctx {
   eph::DevBuf state_cnt;                // per-state int64 counts
   eph::DevBuf stidx;                    // [N^3][nw] state index table (transition rates)
   eph::DevBuf gcur;                     // per-state transition-rate counts / cursors
+  eph::DevBuf gslot;                    // the same per plane of a launch
   eph::DevBuf gstage_col, gstage_val;   // staging of spilled transition rates
   eph::DevBuf bte_f;                    // F0, F, F' of the iteration
   eph::DevBuf kb_g;                     // G_q of a q batch (k-batch order)
@@ -212,7 +213,6 @@ struct RatesArgs {
   const double2 *evec;             // [N^3][nw][nw]
   const double2 *uu;               // [N^3][nm][nm]
   const float2 *evec32, *uu32;
-  const float *eps32;              // float copy of eps (prefilter of lines longer than 512 energies)
   const double *line_e;
   const uint16_t *line_key;
   const double2 *tab;
@@ -222,14 +222,21 @@ struct RatesArgs {
   int64_t *st_counts;              // [ns_total][2]: n_q_valid, n_terms
   unsigned long long *n_kq;
   unsigned long long *n_vertex;
-  const double *occ_f;             // [N^3][nw][EPH_MAX_TEMPS] Fermi factors (wave kernel)
-  const double *occ_n;             // [N^3][nm][EPH_MAX_TEMPS] Bose factors, 0 below omega_cut
+  // wave kernel
+  int64_t *kv_counts;              // [ns_total][2]: (k,q) pairs, vertices
+  int64_t s_lo, ns_launch;         // states s_lo .. s_lo + ns_launch - 1 of this launch
+  const double *occ_f;             // [N^3][nw][occ_stride(nt)] Fermi factors
+  const double *occ_n;             // [N^3][nm][occ_stride(nt)] Bose factors, 0 below omega_cut
   const float *occ32_f, *occ32_n;  // FP32 copies of occ_f, occ_n (reduced-precision forms)
-  int q3_lo, q3_hi;                // q3 planes of this launch (wave kernel)
-  int q3_cur;                      // the plane (wave kernel launches one plane at a time)
+  int q3_lo, q3_hi;                // q3 planes of this launch, one row of workgroups each
+  double *part_tau;                // [planes][nt][ns_total] sums of each plane of a launch of several, or
+                                   // nullptr: one plane, added to inv_tau
+  int64_t *part_cnt;               // [planes][ns_total][4], with part_tau
   // transition rates of the iterative BTE (wave kernel, FP64, count and emit modes)
   const int32_t *stidx;            // [N^3][nw] index of state (k, m) in the list, -1 if none
-  int64_t *g_cursor;               // [ns_total] per-state count (count mode) or next position (emit)
+  int64_t *g_cursor;               // [ns_total] next position of each state (emit)
+  int64_t *g_slot;                 // [planes][ns_total] counts (count mode); offsets of the planes of a launch
+                                   // from g_cursor (emit); nullptr for one plane, which advances g_cursor
   int32_t *g_col;                  // emitted final-state indices, position - g_base
   double *g_val;                   // emitted values [t][g_stride], 1/s
   int64_t g_stride;                // temperature stride of g_val
@@ -238,10 +245,20 @@ struct RatesArgs {
 // rate-kernel modes (wave kernel)
 constexpr int kRates = 0, kCount = 1, kEmit = 2;
 hipError_t launch_rates(int precision, const RatesArgs &a, hipStream_t st);
-// Wave-autonomous rate kernel; rates_wave_group gives its states per group
-// (0 when the shape is not served and launch_rates must be used).
+// Occupation rows of the wave kernel: one value for one temperature, else
+// padded for vector loads.
+inline int occ_stride(int nt) { return nt == 1 ? 1 : EPH_MAX_TEMPS; }
+// Wave rate kernel; rates_wave_group gives the states per group that the
+// state batches and the transition-rate staging count with (0 when the shape
+// is not served and launch_rates must be used).
 int rates_wave_group(int nw, int nm, RpBox box, int N, int precision);
 hipError_t launch_rates_wave(int precision, const RatesArgs &a, hipStream_t st, int mode = kRates);
+// Adds the planes of a launch (a.part_tau, a.part_cnt) to a.inv_tau and
+// a.st_counts in plane order, and with a.g_slot moves a.g_cursor past them.
+hipError_t launch_add_planes(const RatesArgs &a, hipStream_t st);
+// Counts of a counting launch (a.g_slot): total 1 adds them to a.g_cursor,
+// 0 turns them into offsets and leaves the sums in row planes.
+hipError_t launch_plane_counts(const RatesArgs &a, int total, hipStream_t st);
 // k-batch order of the vertex (k_kbatch.hip): step 1 forms G_q for a batch
 // of q, step 2 runs one wave per state over that batch.
 struct KBatchArgs {
@@ -259,10 +276,11 @@ struct KBatchArgs {
 hipError_t launch_kbatch_step1(int64_t q0, int nb, int N, RpBox box, int nre, int nm, int nw, int ncol,
                                const double2 *wt, const double2 *uu, const double2 *tab, double2 *Gq, hipStream_t st);
 hipError_t launch_kbatch_step2(const KBatchArgs &a, hipStream_t st);
-// Occupation tables: occ_f[k][n][t] = 1/(exp((eps-mu)/kT_t)+1),
+// Occupation tables with rows of `stride` temperatures (zeros past nt):
+// occ_f[k][n][t] = 1/(exp((eps-mu)/kT_t)+1),
 // occ_n[q][nu][t] = 1/expm1(hbar w/kT_t) (0 when hbar w < wcut).
 hipError_t launch_occupations(int64_t nq, int nw, int nm, const double *eps, const double *om, double mu,
-                              int nt, const double *kts_host, double wcut, double *occ_f, double *occ_n,
+                              int nt, const double *kts_host, double wcut, int stride, double *occ_f, double *occ_n,
                               hipStream_t st);
 
 // sigma partial sums per block, then out[T*9 + ab] = pref * sum of partials
@@ -287,7 +305,9 @@ hipError_t launch_density(int64_t nk, int nw, const double *eps, int blo, int bh
 int rates_group_max(int nw, int nm);
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t st);
 hipError_t launch_max_nonneg(int64_t n, const double *x, unsigned long long *out, hipStream_t st);
-hipError_t launch_summarize(int64_t ns, const int64_t *st_counts, const double *inv_tau0,
+// out[1..3] += sum n_q_valid, sum n_terms, #(inv_tau0 == 0); with kv_counts
+// also out[0] += (k,q) pairs and out[4] += vertices
+hipError_t launch_summarize(int64_t ns, const int64_t *st_counts, const int64_t *kv_counts, const double *inv_tau0,
                             unsigned long long *out, hipStream_t st);
 size_t rates_smem_bytes(int precision, int N, int nw, int nm, RpBox box);
 

@@ -1,5 +1,6 @@
-// SERTA scattering rates, wave-autonomous form: shape selection and dispatch
-// to the per-(precision, modes) instances of the kernel in rates_wave.h.
+// SERTA scattering rates, wave form: shape selection and dispatch to the
+// per-(precision, modes) instances of the kernel in rates_wave.h, and the sums
+// over the planes of a launch.
 #include "internal.h"
 
 namespace eph {
@@ -16,7 +17,59 @@ extern template hipError_t dispatch_nm<double, 3, kEmit>(const RatesArgs &, hipS
 extern template hipError_t dispatch_nm<double, 6, kEmit>(const RatesArgs &, hipStream_t);
 }  // namespace wave
 
-// Shapes served by the wave-autonomous kernel: a cubic Rp box of edge 4 or
+namespace {
+
+__global__ void add_planes_kernel(RatesArgs a) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i >= a.ns_launch) return;
+  const int64_t s = a.s_lo + i;
+  const int np = a.q3_hi - a.q3_lo;
+  for (int t = 0; t < a.nt; t++) {
+    double *dst = a.inv_tau + (int64_t)t * a.ns_total + s;
+    double v = a.q3_lo == 0 ? 0.0 : *dst;
+    for (int j = 0; j < np; j++) v += a.part_tau[((int64_t)j * a.nt + t) * a.ns_total + s];
+    *dst = v;
+  }
+  for (int c = 0; c < 4; c++) {
+    int64_t *dst = (c < 2 ? a.st_counts : a.kv_counts - 2) + 2 * s + c;
+    int64_t v = a.q3_lo == 0 ? 0 : *dst;
+    for (int j = 0; j < np; j++) v += a.part_cnt[((int64_t)j * a.ns_total + s) * 4 + c];
+    *dst = v;
+  }
+  if (a.g_slot) a.g_cursor[s] += a.g_slot[(int64_t)np * a.ns_total + s];
+}
+
+__global__ void plane_counts_kernel(RatesArgs a, int total) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i >= a.ns_launch) return;
+  const int64_t s = a.s_lo + i;
+  const int np = a.q3_hi - a.q3_lo;
+  int64_t run = 0;
+  for (int j = 0; j < np; j++) {
+    int64_t *p = a.g_slot + (int64_t)j * a.ns_total + s;
+    const int64_t c = *p;
+    if (!total) *p = run;
+    run += c;
+  }
+  if (total) a.g_cursor[s] += run;
+  else a.g_slot[(int64_t)np * a.ns_total + s] = run;
+}
+
+}  // namespace
+
+hipError_t launch_add_planes(const RatesArgs &a, hipStream_t st) {
+  if (a.ns_launch <= 0) return hipSuccess;
+  hipLaunchKernelGGL(add_planes_kernel, dim3((unsigned)((a.ns_launch + 255) / 256)), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_plane_counts(const RatesArgs &a, int total, hipStream_t st) {
+  if (a.ns_launch <= 0) return hipSuccess;
+  hipLaunchKernelGGL(plane_counts_kernel, dim3((unsigned)((a.ns_launch + 255) / 256)), dim3(256), 0, st, a, total);
+  return hipGetLastError();
+}
+
+// Shapes served by the wave kernel: a cubic Rp box of edge 4 or
 // 6 and final-state lines of at most 2048 energies (N * n_wann).  Returns
 // the states per group, 0 when the shape is not served.
 int rates_wave_group(int nw, int nm, RpBox box, int N, int precision) {
@@ -32,7 +85,7 @@ int rates_wave_group(int nw, int nm, RpBox box, int N, int precision) {
 
 // mode kCount / kEmit (transition rates) are FP64 only.
 hipError_t launch_rates_wave(int precision, const RatesArgs &a, hipStream_t st, int mode) {
-  if (a.ng <= 0) return hipSuccess;
+  if (a.ns_launch <= 0) return hipSuccess;
   const bool m3 = a.nm == 3;
   if (mode == kCount) {
     if (precision != EPH_FP64) return hipErrorNotSupported;

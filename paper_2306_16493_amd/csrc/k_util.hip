@@ -31,26 +31,30 @@ __global__ void max_nonneg_kernel(int64_t n, const double *__restrict__ x, unsig
   if (threadIdx.x == 0) atomicMax(out, red[0]);
 }
 
-// out[0] += sum n_q_valid, out[1] += sum n_terms, out[2] += #(inv_tau[0][s] == 0)
+// out[1] += sum n_q_valid, out[2] += sum n_terms, out[3] += #(inv_tau[0][s] == 0);
+// with kv_counts out[0] += (k,q) pairs, out[4] += vertices
 __global__ void summarize_kernel(int64_t ns, const int64_t *__restrict__ st_counts,
-                                 const double *__restrict__ inv_tau0, unsigned long long *__restrict__ out) {
-  __shared__ unsigned long long red[3][256];
-  unsigned long long a = 0, b = 0, c = 0;
+                                 const int64_t *__restrict__ kv_counts, const double *__restrict__ inv_tau0,
+                                 unsigned long long *__restrict__ out) {
+  __shared__ unsigned long long red[5][256];
+  unsigned long long v[5] = {0, 0, 0, 0, 0};
   for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < ns; s += (int64_t)gridDim.x * blockDim.x) {
-    a += (unsigned long long)st_counts[2 * s];
-    b += (unsigned long long)st_counts[2 * s + 1];
-    c += inv_tau0[s] == 0.0 ? 1ull : 0ull;
+    v[1] += (unsigned long long)st_counts[2 * s];
+    v[2] += (unsigned long long)st_counts[2 * s + 1];
+    v[3] += inv_tau0[s] == 0.0 ? 1ull : 0ull;
+    if (kv_counts) {
+      v[0] += (unsigned long long)kv_counts[2 * s];
+      v[4] += (unsigned long long)kv_counts[2 * s + 1];
+    }
   }
-  red[0][threadIdx.x] = a;
-  red[1][threadIdx.x] = b;
-  red[2][threadIdx.x] = c;
+  for (int q = 0; q < 5; q++) red[q][threadIdx.x] = v[q];
   __syncthreads();
   for (int s = 128; s > 0; s >>= 1) {
     if (threadIdx.x < s)
-      for (int q = 0; q < 3; q++) red[q][threadIdx.x] += red[q][threadIdx.x + s];
+      for (int q = 0; q < 5; q++) red[q][threadIdx.x] += red[q][threadIdx.x + s];
     __syncthreads();
   }
-  if (threadIdx.x < 3) atomicAdd(out + threadIdx.x, red[threadIdx.x][0]);
+  if (threadIdx.x < 5 && red[threadIdx.x][0]) atomicAdd(out + threadIdx.x, red[threadIdx.x][0]);
 }
 
 struct Kts {
@@ -58,31 +62,32 @@ struct Kts {
 };
 
 __global__ void occupation_kernel(int64_t nq, int nw, int nm, const double *__restrict__ eps,
-                                  const double *__restrict__ om, double mu, int nt, Kts kts, double wcut,
+                                  const double *__restrict__ om, double mu, int nt, Kts kts, double wcut, int stride,
                                   double *__restrict__ occ_f, double *__restrict__ occ_n) {
   int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  // rows padded to EPH_MAX_TEMPS entries (zeros past nt) for vector loads
+  // rows of `stride` entries (zeros past nt)
   if (i < nq * nw) {
     const double e = eps[i];
-    for (int t = 0; t < EPH_MAX_TEMPS; t++)
-      occ_f[i * EPH_MAX_TEMPS + t] = t < nt ? 1.0 / (exp((e - mu) / kts.v[t]) + 1.0) : 0.0;
+    for (int t = 0; t < stride; t++)
+      occ_f[i * stride + t] = t < nt ? 1.0 / (exp((e - mu) / kts.v[t]) + 1.0) : 0.0;
   }
   if (i < nq * nm) {
     const double w = om[i];
-    for (int t = 0; t < EPH_MAX_TEMPS; t++)
-      occ_n[i * EPH_MAX_TEMPS + t] = (t < nt && w >= wcut && w > 0.0) ? 1.0 / expm1(w / kts.v[t]) : 0.0;
+    for (int t = 0; t < stride; t++)
+      occ_n[i * stride + t] = (t < nt && w >= wcut && w > 0.0) ? 1.0 / expm1(w / kts.v[t]) : 0.0;
   }
 }
 
 }  // namespace
 
 hipError_t launch_occupations(int64_t nq, int nw, int nm, const double *eps, const double *om, double mu, int nt,
-                              const double *kts_host, double wcut, double *occ_f, double *occ_n, hipStream_t st) {
+                              const double *kts_host, double wcut, int stride, double *occ_f, double *occ_n,
+                              hipStream_t st) {
   Kts k;
   for (int t = 0; t < EPH_MAX_TEMPS; t++) k.v[t] = t < nt ? kts_host[t] : 1.0;
   const int64_t n = nq * (nw > nm ? nw : nm);
   hipLaunchKernelGGL(occupation_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, nq, nw, nm, eps, om,
-                     mu, nt, k, wcut, occ_f, occ_n);
+                     mu, nt, k, wcut, stride, occ_f, occ_n);
   return hipGetLastError();
 }
 
@@ -102,12 +107,13 @@ hipError_t launch_max_nonneg(int64_t n, const double *x, unsigned long long *out
   return hipGetLastError();
 }
 
-hipError_t launch_summarize(int64_t ns, const int64_t *st_counts, const double *inv_tau0, unsigned long long *out,
-                            hipStream_t st) {
+hipError_t launch_summarize(int64_t ns, const int64_t *st_counts, const int64_t *kv_counts, const double *inv_tau0,
+                            unsigned long long *out, hipStream_t st) {
   if (ns <= 0) return hipSuccess;
   int64_t blocks = (ns + 255) / 256;
   if (blocks > 1024) blocks = 1024;
-  hipLaunchKernelGGL(summarize_kernel, dim3((unsigned)blocks), dim3(256), 0, st, ns, st_counts, inv_tau0, out);
+  hipLaunchKernelGGL(summarize_kernel, dim3((unsigned)blocks), dim3(256), 0, st, ns, st_counts, kv_counts,
+                     inv_tau0, out);
   return hipGetLastError();
 }
 

@@ -1,31 +1,30 @@
 #pragma once
-// SERTA scattering rates, wave-autonomous form (gfx950): the kernel template.
-// Instantiated per (precision, phonon modes) in k_rates_wave_<p><nm>.hip and
-// dispatched by k_rates_wave.hip.
+// SERTA scattering rates (gfx950): the kernel template.  Instantiated per
+// (precision, phonon modes, mode) in k_rates_wave_<p><nm>.hip and dispatched
+// by k_rates_wave.hip.
 //
-// Same arithmetic as the workgroup form (separable Rp box: Y per q3, Z per
+// Same arithmetic as the general form (separable Rp box: Y per q3, Z per
 // q-line, G per q; vertex contracted onto the final band m first, then onto
-// the modes; sieve, occupations, Gaussian delta; Sec. II.B/II.C/III.A/III.C),
-// organised so that no workgroup barrier sits inside the q loops:
-//   * each wave64 owns a group of <= GW initial states on one k-line and
-//     sweeps all q-lines on its own; the four waves of a workgroup take
-//     consecutive groups of the same k-line, so their table reads share L1;
-//   * Y_s(p1,p2; q3) lives in registers, one (state, p1, channel) pair per
-//     lane slot, so Z_s(p1; q2,q3) is a lane-local 1-D transform whose
-//     result goes to a ring of Z slots in the wave's LDS slice;
-//   * the final-state line p = k + q (contiguous in the energy table) is
-//     prefiltered 64 entries at a time against the group's state energies
-//     (window max(hbar w) + sw*eta); passing (k-slot, p1) candidates are
-//     compacted with ballots into a candidate queue;
-//   * full passes of candidates are sieved exactly (FP64, every state and
-//     final band) and the (state, m, p1) pairs with a kept term go to a
-//     vertex queue; full passes of that queue evaluate one vertex per lane,
-//     so no lane idles through state, band or mode loops;
-//   * Fermi and Bose factors come from per-call grid tables, so a vertex
-//     pays one exp per kept term (the delta) and no other transcendental;
-//   * phases use 32-bit indices and, in the vertex, a recurrence.
-// Per-state rates are accumulated per lane and reduced with a fixed
-// butterfly at the end, so results are bit-reproducible.
+// the modes; sieve, occupations, Gaussian delta; Sec. II.B/II.C/III.A/III.C).
+// One workgroup takes one initial state s = (n, k) and one q3 plane:
+//   * Y_s(p1,p2; q3) is formed once per plane, straight into the registers of
+//     a matrix-core operand, its (p1, channel) rows spread over the waves;
+//   * Z_s(p1; q2,q3) of a batch of q-lines is one matrix product per 16 lines
+//     (16x16x4 MFMA, rows (p1, channel), inner index (p2, re/im), columns the
+//     lines) into LDS, where all waves read it;
+//   * the q of the batch are taken 64 at a time in the order of the final
+//     states p = k + q, across line ends, so no lane idles at the end of a
+//     line.  Each is sieved exactly (FP64, every final band near the state's
+//     energy; the compares go into wave masks, which the scalar unit joins
+//     and counts), and the (p, m) with a kept term go to the wave's queue;
+//   * the queues of the waves are then evaluated as one list, one vertex per
+//     lane, whole passes dealt out to the waves.
+// Fermi and Bose factors come from per-call grid tables, so a vertex pays one
+// exp per kept term (the delta) and no other transcendental.  The phase of
+// the box corner, e^{i q.lo}, is common to all terms of a vertex and leaves
+// |g|^2 alone, so the three sums run over p = 0 .. NB-1, the last one by
+// Horner's rule.  The lists, their order and the sums over
+// lanes, waves and planes are fixed, so results are bit-reproducible.
 #include <type_traits>
 
 #include "dev_util.h"
@@ -34,769 +33,557 @@
 namespace eph {
 namespace wave {
 
-// Waves per workgroup: 4 (they share the phase table and, working on
-// consecutive groups of one k-line, their L1), 2 for the FP64 form of 48
-// channels, whose per-wave LDS would otherwise let only one workgroup of 4
-// onto a CU.
-template <class T, int NW, int NM>
-__host__ __device__ constexpr int waves_per_block() {
-  return (NW * NM >= 48 && sizeof(T) == 8) ? 2 : 4;
-}
-
-template <class T, int NW, int NM, int GW, int NB, class LT = double>
-struct WaveLayout {
-  static constexpr int C = NW * NM;
-  static constexpr int SMX = GW + NW;  // member states + shadow states
-  // Z ring slots (q-lines in flight): 4, or 2 for 48 channels (LDS)
-  static constexpr int NZ = C >= 48 ? 2 : 4;
-  static constexpr int WPB = waves_per_block<T, NW, NM>();
-  static constexpr int VCAP = 64 + 64 * GW * NW;  // vertex queue: one pass of candidates + a partial pass
-  // one Z block per (slot, state), padded by 16 bytes so that the blocks a
-  // vertex pass reads at the same offset fall in different LDS banks
-  static constexpr int ZB = NB * C + (int)(16 / sizeof(typename V2<T>::t));
-  __host__ __device__ static size_t z_bytes() { return align16(sizeof(typename V2<T>::t) * NZ * GW * ZB); }
-  __host__ __device__ static int qcap(int) { return 128; }  // drained in whole passes during the scan
-  __host__ __device__ static size_t q_bytes(int N) { return align16(4 * (size_t)qcap(N)); }
-  __host__ __device__ static size_t misc_bytes() { return align16(SMX * 8 + SMX * 4 * 4 + NZ * 8 + 64); }
-  __host__ __device__ static size_t line_bytes(int N) { return align16(sizeof(LT) * (size_t)N * NW); }
-  __host__ __device__ static size_t v_bytes() { return align16(8 * (size_t)VCAP); }
-  __host__ __device__ static size_t per_wave(int N) {
-    return z_bytes() + q_bytes(N) + misc_bytes() + line_bytes(N) + v_bytes();
+// One 16 x 16 x 4 matrix product.  Lane l supplies A[l % 16][l / 16] and
+// B[l / 16][l % 16]; it holds column l % 16 of D and, counting the rows of A
+// by row_of(l % 16), rows 4 (l / 16) .. 4 (l / 16) + 3.
+template <class T>
+struct Mfma;
+template <>
+struct Mfma<float> {
+  typedef float acc __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ int row_of(int i) { return i; }
+  static __device__ __forceinline__ acc mul(float a, float b, acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
-  __host__ __device__ static size_t tab_bytes(int N) { return align16(sizeof(typename V2<T>::t) * N); }
-  __host__ __device__ static size_t total(int N) { return tab_bytes(N) + WPB * per_wave(N); }
+};
+template <>
+struct Mfma<double> {
+  typedef double acc __attribute__((ext_vector_type(4)));
+  // the FP64 product leaves row l / 16 + 4 r in register r
+  static __device__ __forceinline__ int row_of(int i) { return 4 * (i & 3) + (i >> 2); }
+  static __device__ __forceinline__ acc mul(double a, double b, acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
 };
 
-// Waves per SIMD the register allocation targets: 3 for the FP32 form of up
-// to 24 channels (whose LDS then also admits three workgroups per CU), 2
-// otherwise.
+// Load at a 32-bit byte offset from a wave-uniform base (one plane of a table
+// is below 4 GB), which needs no 64-bit address arithmetic per lane.
+template <class U>
+__device__ __forceinline__ U at_offset(const U *base, uint32_t bytes) {
+  return *reinterpret_cast<const U *>(reinterpret_cast<const char *>(base) + bytes);
+}
+// x + d brought into [0, N) for x + d in [-N, 2 N): the unsigned wrap of the
+// other candidate is the larger one
+__device__ __forceinline__ uint32_t wrap_up(uint32_t x, uint32_t N) { return min(x, x + N); }    // x in [-N, N)
+__device__ __forceinline__ uint32_t wrap_down(uint32_t x, uint32_t N) { return min(x, x - N); }  // x in [0, 2 N)
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// (a mod N) for 0 <= a < 2^20, N <= 512: the float quotient is off by one at most
+__device__ __forceinline__ int fmod_small(int a, int N, float inv_n) {
+  int r = a - N * (int)floorf((float)a * inv_n);
+  r += (r < 0) ? N : 0;
+  r -= (r >= N) ? N : 0;
+  return r;
+}
+
+template <class T, int NW, int NM, int NB>
+struct WaveLayout {
+  using C2 = typename V2<T>::t;
+  static constexpr int C = NW * NM;
+  static constexpr int ROWS = NB * C;               // (p1, channel) rows of Y and Z
+  static constexpr int MT = (ROWS + 15) / 16;       // 16-row tiles
+  static constexpr int KS = (2 * NB + 3) / 4;       // 4-deep steps over (p2, re/im)
+  static constexpr int WPB = (C >= 48 && sizeof(T) == 8) ? 8 : 4;  // waves per workgroup
+  static constexpr int TPW = (MT + WPB - 1) / WPB;  // tiles per wave
+  // lines per batch: 32 where two batches' worth of LDS is small, so that the
+  // partial last pass over the queue is rare; 16 for 48 channels
+  static constexpr int NL = C >= 48 ? 16 : 32;
+  // one line's Z, padded by 16 bytes so that neighbouring lines start in
+  // different LDS banks
+  static constexpr int ZB = ROWS + (int)(16 / sizeof(C2));
+  static constexpr int QC = 64 * NW + 512;          // queue entries per wave
+  __host__ __device__ static size_t tab_bytes(int N) { return align16(sizeof(C2) * (size_t)N); }
+  static constexpr size_t z_bytes = sizeof(C2) * (size_t)NL * ZB;
+  static constexpr size_t q_bytes = 4 * (size_t)WPB * QC;
+  static constexpr size_t rank_bytes = 2 * (size_t)WPB * QC;  // emit mode
+  static constexpr size_t misc_bytes = 8 * (size_t)WPB * 8 + 64;
+  __host__ __device__ static size_t total(int N, int mode) {
+    return misc_bytes + q_bytes + (mode == kCount ? 0 : tab_bytes(N) + z_bytes) + (mode == kEmit ? rank_bytes : 0);
+  }
+};
+
+// Waves per SIMD the register allocation targets.
 template <class T, int NW, int NM>
 __host__ __device__ constexpr int waves_per_eu() {
-  return (sizeof(T) == 4 && NW * NM <= 24) ? 3 : 2;
+  return sizeof(T) == 4 ? (NW * NM >= 48 ? 3 : 4) : (NW * NM >= 48 ? 2 : 3);
 }
+
 // MODE: kRates computes 1/tau; kCount only counts, per state, the transition
 // rates to final states in the state list (no transforms, no vertices);
 // kEmit computes 1/tau and also writes those transition rates (the summed
-// terms of each (state, q, m) vertex) at the state's running cursor.
-template <class T, int NW, int NM, int GW, int NB, int LPL, int MODE>
-__global__ __launch_bounds__((waves_per_block<T, NW, NM>() * 64))
+// terms of each (state, q, m) vertex) from the state's cursor on.
+// NT: temperatures per row of the occupation tables (1, or 4 for 2..4).
+template <class T, int NW, int NM, int NB, int NT, int MODE>
+__global__ __launch_bounds__((WaveLayout<T, NW, NM, NB>::WPB * 64))
 __attribute__((amdgpu_waves_per_eu(waves_per_eu<T, NW, NM>())))
 void rates_wave_kernel(RatesArgs a) {
+  using LY = WaveLayout<T, NW, NM, NB>;
   using C2 = typename V2<T>::t;
-  // the prefilter reads a float copy of the final-state energies (half the
-  // LDS and prefetch registers of an FP64 copy); its window is widened to
-  // cover the rounding, and the exact sieve that follows is FP64
-  using LT = float;
-  using LY = WaveLayout<T, NW, NM, GW, NB, LT>;
-  constexpr int C = NW * NM;
-  constexpr int SMX = LY::SMX;
-  constexpr int NZ = LY::NZ;
-  constexpr int NPAIR = (GW * NB * C + 63) / 64;
-  constexpr int WPB = LY::WPB;
-  // lanes per vertex: with 8 orbitals and 6 modes a vertex is split over two
-  // lanes (each contracts half of the orbitals, the halves are added, and
-  // each rotates onto half of the modes), which keeps the kernel within its
-  // registers next to Y
-  constexpr int VL = (NW == 8 && NM == 6) ? 2 : 1;
-  constexpr int NWL = NW / VL;  // orbitals per lane in the W contraction
-  constexpr int NML = NM / VL;  // modes per lane in the rotation
+  using MM = Mfma<T>;
+  using Acc = typename MM::acc;
+  // modes of a vertex in flight: all, but for 6 in FP64, whose mode matrices
+  // would not fit the registers beside the band row
+  constexpr int MU = (sizeof(T) == 8 && NM == 6) ? 2 : NM;
+  constexpr int C = LY::C, WPB = LY::WPB, TPW = LY::TPW, KS = LY::KS, NL = LY::NL, QC = LY::QC;
   extern __shared__ __align__(16) unsigned char smem[];
   const int N = a.N;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int LN = N * NW;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-  C2 *sTab = reinterpret_cast<C2 *>(smem);
-  unsigned char *wb = smem + LY::tab_bytes(N) + (size_t)wave * LY::per_wave(N);
-  C2 *sZ = reinterpret_cast<C2 *>(wb);  // [NZ][GW][ZB]: [NB][C] + pad
-  uint32_t *sQ = reinterpret_cast<uint32_t *>(wb + LY::z_bytes());
-  unsigned char *misc = wb + LY::z_bytes() + LY::q_bytes(N);
-  double *sEps = reinterpret_cast<double *>(misc);  // [SMX] state energies
-  int *sKs = reinterpret_cast<int *>(sEps + SMX);     // [SMX] k-slot of each state
-  int *sKfirst = sKs + SMX;                           // [SMX] first state of each k-slot
-  int *sKcnt = sKfirst + SMX;                         // [SMX] states of each k-slot
-  int *sK1 = sKcnt + SMX;                             // [SMX] k1 of each k-slot
-  int *sSlot = sK1 + SMX;                             // [NZ][2] (q2, line) of each Z slot
-  LT *sLine = reinterpret_cast<LT *>(misc + LY::misc_bytes());  // [N][NW] current line energies
-  uint2 *sV = reinterpret_cast<uint2 *>(misc + LY::misc_bytes() + LY::line_bytes(N));  // vertex queue
-
-  for (int t = threadIdx.x; t < N; t += WPB * 64) sTab[t] = mk<T>((T)a.tab[t].x, (T)a.tab[t].y);
-  __syncthreads();  // the only workgroup barrier
-
-  // XCD-aware block order: consecutive block indices go round-robin to the
-  // 8 XCDs, so give each XCD a contiguous range of groups.
-  const int64_t nblk = (a.ng + WPB - 1) / WPB;
-  const int64_t per_xcd = (nblk + 7) / 8;
+  // XCD-aware order: consecutive block indices go round-robin to the 8 XCDs,
+  // so give each XCD a contiguous range of states (neighbours in k share
+  // their final-state plane).
+  const int64_t per_xcd = (a.ns_launch + 7) / 8;
   const int64_t blk = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  const int64_t g = blk * WPB + wave;
-  if (blk >= nblk || g >= a.ng) return;  // wave-uniform
+  if (blk >= a.ns_launch) return;  // workgroup-uniform
+  const int64_t s = a.s_lo + blk;
+  const int plane = blockIdx.y, q3 = a.q3_lo + plane;
 
-  const int64_t s0 = a.gstart[g];
-  const int S = (int)(a.gstart[g + 1] - s0);
-  const int64_t kfirst = a.sk[s0];
-  int SH = 0;
-  {
-    const int64_t klast = a.sk[s0 + S - 1];
-    while (SH < NW - 1 && s0 + S + SH < a.ns_total && a.sk[s0 + S + SH] == klast) SH++;
-  }
-  const int ST = S + SH;
-  const bool cont = (s0 > 0) && (a.sk[s0 - 1] == kfirst);  // first k point counted by an earlier group
-  const int k2 = (int)((kfirst / N) % N), k3 = (int)(kfirst / ((int64_t)N * N));
-  // prefilter window (a float line copy is within 1e-4 eV of the FP64
-  // values for |eps| < 1000 eV; the exact sieve that follows uses FP64)
-  // (a float copy is within 1e-4 eV of the FP64 values for |eps| < 1000 eV)
-  const double W = a.wmax + a.sw * a.eta + 1e-4;
+  uint32_t *sQ = reinterpret_cast<uint32_t *>(smem);            // [WPB][QC] vertices: p1 | line << 9 | m << 15 | listed << 31
+  double *sRed = reinterpret_cast<double *>(smem + LY::q_bytes);  // [WPB][8] reductions; queue lengths in between
+  int *sCnt = reinterpret_cast<int *>(sRed);                    // [WPB][4]: length, listed entries, more to come
+  unsigned char *rest = smem + LY::q_bytes + LY::misc_bytes;
+  C2 *sTab = reinterpret_cast<C2 *>(rest);                      // e^{2 pi i m/N}
+  C2 *sZ = reinterpret_cast<C2 *>(rest + LY::tab_bytes(N));     // [NL][ZB]: [p1][mu][i] + pad
+  uint16_t *sRank = reinterpret_cast<uint16_t *>(rest + LY::tab_bytes(N) + LY::z_bytes);  // [WPB][QC]
+
+  if constexpr (MODE != kCount)
+    for (int t = threadIdx.x; t < N; t += WPB * 64) sTab[t] = mk<T>((T)a.tab[t].x, (T)a.tab[t].y);
+
+  const int k = a.sk[s], n = a.sn[s];
+  const int k1 = k % N, k2 = (k / N) % N, k3 = k / (N * N);
+  const double es = a.eps[(int64_t)k * NW + n];
+  // the first state of a k point also looks for the other states' terms, so
+  // that every (k, q) pair is counted once
+  int nsh = 0;
+  if (MODE != kCount && (s == 0 || a.sk[s - 1] != k))
+    while (nsh < NW - 1 && s + 1 + nsh < a.ns_total && a.sk[s + 1 + nsh] == k) nsh++;
+  const bool count_kq = s == 0 || a.sk[s - 1] != k;
   const double cut = a.sw * a.eta;
+  // bands further away keep no term (the margin covers the rounding of the
+  // exact test)
+  const double reach = (a.wmax + cut) * (1.0 + 1e-12) + 1e-12 * fabs(es);
   const double inv_eta = 1.0 / a.eta;
   const double dnorm = 1.0 / (1.7724538509055160273 * a.eta);
-  const int nt = a.nt;
-  const int lo1 = a.box.lo[0], lo2 = a.box.lo[1], lo3 = a.box.lo[2];
-
-  // states and k-slots (distinct k points, states of one k are contiguous)
-  int NK = 0;
-  if (lane == 0) {
-    int64_t prev = -1;
-    for (int s = 0; s < ST; s++) {
-      const int64_t k = a.sk[s0 + s];
-      if (k != prev) {
-        sKfirst[NK] = s;
-        sKcnt[NK] = 0;
-        sK1[NK] = (int)(k % N);
-        NK++;
-        prev = k;
-      }
-      sKs[s] = NK - 1;
-      sKcnt[NK - 1]++;
-      sEps[s] = a.eps[k * NW + a.sn[s0 + s]];
-    }
-  }
-  NK = __shfl(NK, 0, 64);
-  __syncwarp();
-  int KMX = 0;  // most states at one k point of the group (wave-uniform)
-  for (int ks = 0; ks < NK; ks++) KMX = max(KMX, sKcnt[ks]);
-  double esm[GW];  // energies of the member states (wave-uniform)
-#pragma unroll
-  for (int ss = 0; ss < GW; ss++) esm[ss] = sEps[min(ss, S - 1)];
-
-  double acc[GW][EPH_MAX_TEMPS];
-  unsigned nq_s[GW], nt_s[GW];
-#pragma unroll
-  for (int s = 0; s < GW; s++) {
-    nq_s[s] = nt_s[s] = 0u;
-#pragma unroll
-    for (int t = 0; t < EPH_MAX_TEMPS; t++) acc[s][t] = 0.0;
-  }
-  unsigned long long my_nkq = 0, my_nv = 0;
-  // transition rates: per-state counts (kCount, per lane) or running write
-  // positions (kEmit, wave-uniform)
-  int64_t gcur[GW];
-#pragma unroll
-  for (int ss = 0; ss < GW; ss++) gcur[ss] = (MODE == kEmit && ss < S) ? a.g_cursor[s0 + ss] : 0;
-
-  // pair slots of this lane: P = lane + 64 j -> (s, p1, c) = (P / (NB C), (P / C) % NB, P % C)
-  T yr[NPAIR][NB], yi[NPAIR][NB];
-  const C2 *Xg = reinterpret_cast<const C2 *>(a.X);
-  const int64_t xrow = (int64_t)NB * NB * NB * C;
-
-  // final-state line energies: the next q-line's are loaded into registers
-  // while the current one (in LDS, [m][p1]) is scanned
-  // in FP64, lines of up to 512 energies are prefetched into registers while
-  // a line is worked on; longer lines, and every line in FP32, are copied at
-  // the staging point instead (measured faster: the FP32 instances spill
-  // with the prefetch registers, and at three waves per SIMD hide the
-  // staging loads)
-  constexpr bool PF = sizeof(T) == 8 && LPL <= 8;
-  constexpr int LPR = PF ? LPL : 1;
-  LT nxt[LPR];
-  const LT *eline = a.eps32;  // float copy of the band energies, the prefilter's input
-  // a line is kept in LDS as in the table, [p1][m], and copied with 16-byte
-  // accesses when a row is a whole number of float4
-  auto copy_line = [&](const LT *src) __attribute__((always_inline)) {
-    if constexpr (NW % 4 == 0) {
-      const float4 *s4 = reinterpret_cast<const float4 *>(src);
-      float4 *d4 = reinterpret_cast<float4 *>(sLine);
-      for (int e = lane; e < LN / 4; e += 64) d4[e] = s4[e];
-    } else {
-      for (int e = lane; e < LN; e += 64) sLine[e] = src[e];
-    }
-  };
-  {
-    const int l3 = (k3 + a.q3_lo >= N) ? k3 + a.q3_lo - N : k3 + a.q3_lo;
-    copy_line(eline + (size_t)(k2 + N * l3) * LN);
+  const float inv_n = 1.0f / (float)N;
+  const int p3 = (k3 + q3 >= N) ? k3 + q3 - N : k3 + q3;
+  // the planes of the tables that this workgroup reads
+  const int64_t p_plane = (int64_t)N * N * p3, q_plane = (int64_t)N * N * q3;
+  const double *eps_p = a.eps + p_plane * NW, *om_q = a.om + q_plane * NM;
+  const int32_t *stidx_p = MODE == kRates ? nullptr : a.stidx + p_plane * NW;
+  const C2 *evec_p, *uu_q;
+  const T *occ_p, *occ_q;
+  if constexpr (sizeof(T) == 8) {
+    evec_p = a.evec + p_plane * (NW * NW);
+    uu_q = a.uu + q_plane * (NM * NM);
+    occ_p = a.occ_f + p_plane * (NW * NT);
+    occ_q = a.occ_n + q_plane * (NM * NT);
+  } else {
+    evec_p = a.evec32 + p_plane * (NW * NW);
+    uu_q = a.uu32 + q_plane * (NM * NM);
+    occ_p = a.occ32_f + p_plane * (NW * NT);
+    occ_q = a.occ32_n + q_plane * (NM * NT);
   }
 
-  // One candidate = (k-slot, p1, Z slot): every state of that k point against
-  // every final band m at p = k + q.  Queue item (32 bits): p1 | ks << 10 |
-  // zslot << 15 | (mask of the bands inside the prefilter window) << 17.
-  static_assert(NZ <= 4 && NW <= 8 && SMX <= 32, "candidate item fields");
-  int qn = 0;
-  // Two-level form: stage1(n) sieves the first n queued candidates against
-  // every (state, final band) pair and appends the pairs with a kept term to
-  // the vertex queue (drained in whole passes after each candidate pass, so
-  // it holds < 64 + 64*GW*NW entries); vdrain(n) evaluates the first n
-  // vertices, one per lane.
-  // Vertex item (64 bits): x = p1 | q1 << 10 | i1 << 20 | zslot << 30 with
-  // i1 = q1*lo1 mod N the first phase index; y = s | m << 3 | vp << 6 |
-  // vm << 12 | q2 << 18.
-  int vn = 0;
-  auto vdrain = [&](int count) __attribute__((always_inline)) {
-    if constexpr (MODE == kCount) {
-      // only which final states the kept vertices reach
-      for (int base = 0; base < count; base += 64) {
-        const int i = base + lane;
-        if (i < count) {
-          const uint2 it = sV[i];
-          const int p1 = (int)(it.x & 1023u), s = (int)(it.y & 7u), m = (int)((it.y >> 3) & 7u);
-          const int q2 = (int)((it.y >> 18) & 1023u);
-          const int p2l = (k2 + q2 >= N) ? k2 + q2 - N : k2 + q2;
-          const int p3l = (k3 + a.q3_cur >= N) ? k3 + a.q3_cur - N : k3 + a.q3_cur;
-          const int64_t pidx = p1 + (int64_t)N * (p2l + (int64_t)N * p3l);
-          const bool in_list = a.stidx[pidx * NW + m] >= 0;
+  double acc[NT];
 #pragma unroll
-          for (int ss = 0; ss < GW; ss++) gcur[ss] += (in_list && ss == s) ? 1 : 0;
-        }
+  for (int t = 0; t < NT; t++) acc[t] = 0.0;
+  int n_q = 0, n_t = 0, n_kq = 0, n_v = 0;  // wave-uniform counts
+  int64_t gpos = 0;                         // next transition rate of the state
+  if constexpr (MODE == kEmit) gpos = a.g_cursor[s] + (a.g_slot ? a.g_slot[plane * a.ns_total + s] : 0) - a.g_base;
+
+  // ---- Y_s(p1, p2; q3) as the A operand: lane (i, g) of tile t and step ks
+  //      holds row 16 t + row_of(i) = (p1, channel), inner index 4 ks + g =
+  //      (p2, re/im) ----
+  const int li = lane & 15, lg = lane >> 4;
+  T ya[TPW][KS];
+  if constexpr (MODE != kCount) {
+    __syncthreads();  // phase table
+    const C2 *X = reinterpret_cast<const C2 *>(a.X) + (s - a.s_base) * (int64_t)(NB * NB * NB * C);
+    C2 ph3[NB];
+    {
+      int i3 = 0;
+#pragma unroll
+      for (int p = 0; p < NB; p++) {
+        ph3[p] = sTab[i3];
+        i3 += q3;
+        i3 -= (i3 >= N) ? N : 0;
       }
-      return;
     }
-    const int h = (VL == 1) ? 0 : (lane & (VL - 1));  // this lane's half of a vertex
-    for (int base = 0; base < count; base += 64 / VL) {
-      const int i = base + lane / VL;
-      int e_state = -1, e_col = -1;  // transition rate of this lane's vertex (kEmit)
-      double e_val[EPH_MAX_TEMPS];
-      if (i < count) {
-      // everything the vertex needs is in its queue item (no table lookups)
-      const uint2 it = sV[i];
-      const int p1 = (int)(it.x & 1023u), q1 = (int)((it.x >> 10) & 1023u), i1 = (int)((it.x >> 20) & 1023u);
-      const int zs_slot = (int)(it.x >> 30);
-      const int s = (int)(it.y & 7u), m = (int)((it.y >> 3) & 7u);
-      const unsigned vp = (it.y >> 6) & 63u, vm = (it.y >> 12) & 63u;
-      const int q2 = (int)((it.y >> 18) & 1023u);
-      const int p2l = (k2 + q2 >= N) ? k2 + q2 - N : k2 + q2;
-      const int p3l = (k3 + a.q3_cur >= N) ? k3 + a.q3_cur - N : k3 + a.q3_cur;
-      const int64_t qidx = q1 + (int64_t)N * (q2 + (int64_t)N * a.q3_cur);
-      const int64_t pidx = p1 + (int64_t)N * (p2l + (int64_t)N * p3l);
-      double es = esm[0];
 #pragma unroll
-      for (int ss = 1; ss < GW; ss++) es = (s == ss) ? esm[ss] : es;
-      const double epm = a.eps[pidx * NW + m];
-      double omq[NML];  // phonon energies of this lane's modes
+    for (int i = 0; i < TPW; i++) {
+      const int row = 16 * (wave + WPB * i) + MM::row_of(li);
+      const int p1 = row / C, c = row - p1 * C;
 #pragma unroll
-      for (int nl = 0; nl < NML; nl++) omq[nl] = a.om[qidx * NM + h * NML + nl];
-      my_nv += (h == 0) ? 1 : 0;
-      C2 vrow[NWL];
+      for (int ks = 0; ks < KS; ks++) {
+        const int p2 = (4 * ks + lg) >> 1;
+        const bool im = lg & 1;
+        T y = 0;
+        if (row < LY::ROWS && p2 < NB) {
+          const C2 *x = X + ((p1 * NB + p2) * NB) * C + c;
 #pragma unroll
-      for (int j = 0; j < NWL; j++) {
-        if constexpr (sizeof(T) == 8) vrow[j] = a.evec[(pidx * NW + m) * NW + h * NWL + j];
-        else vrow[j] = a.evec32[(pidx * NW + m) * NW + h * NWL + j];
-      }
-      T wr[NM], wi[NM];
-#pragma unroll
-      for (int mu = 0; mu < NM; mu++) wr[mu] = wi[mu] = 0;
-      // phases e^{i 2pi q1 p1'/N}, p1' = lo1 .. lo1 + NB - 1, by recurrence from
-      // two table entries (per-lane table lookups would conflict in LDS banks)
-      C2 ph = sTab[i1];
-      const C2 rq = sTab[q1];
-      const C2 *zs = sZ + ((size_t)zs_slot * GW + s) * LY::ZB + h * NWL;
-#pragma unroll 1
-      for (int pp = 0; pp < NB; pp++) {
-#pragma unroll
-        for (int mu = 0; mu < NM; mu++) {
-          T tr = 0, ti = 0;
-#pragma unroll
-          for (int j = 0; j < NWL; j++) {
-            const C2 z = zs[pp * C + mu * NW + j];
-            cmac_conj<T>(tr, ti, vrow[j].x, vrow[j].y, z.x, z.y);
+          for (int p = 0; p < NB; p++) {
+            const C2 v = x[p * C];
+            y = fma(ph3[p].x, im ? v.y : v.x, y);
+            y = fma(ph3[p].y, im ? v.x : -v.y, y);
           }
-          cmac<T>(wr[mu], wi[mu], ph.x, ph.y, tr, ti);
         }
-        ph = mk<T>(fma(ph.x, rq.x, -ph.y * rq.y), fma(ph.x, rq.y, ph.y * rq.x));
+        ya[i][ks] = y;
       }
-      if constexpr (VL == 2) {  // the two halves of the orbital sum (both lanes share i)
+    }
+  }
+
+  const int nbatch = (N + NL - 1) / NL;
+  const int nlb = (N + nbatch - 1) / nbatch;  // lines per batch, evened out
+  for (int q2_0 = 0; q2_0 < N; q2_0 += nlb) {
+    const int nl = min(nlb, N - q2_0);
+    // ---- Z_s(p1; q2, q3) of the batch -> LDS ----
+    if constexpr (MODE != kCount) {
+      for (int lt = 0; lt < nl; lt += 16) {
+        T br[KS], bi[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) {
+          const C2 ph = sTab[fmod_small(__umul24(q2_0 + lt + li, (4 * ks + lg) >> 1), N, inv_n)];
+          br[ks] = (lg & 1) ? -ph.y : ph.x;
+          bi[ks] = (lg & 1) ? ph.x : ph.y;
+        }
+#pragma unroll
+        for (int i = 0; i < TPW; i++) {
+          const int tile = wave + WPB * i;
+          if (tile < LY::MT) {  // wave-uniform
+            Acc zr = Acc{0, 0, 0, 0}, zi = Acc{0, 0, 0, 0};
+#pragma unroll
+            for (int ks = 0; ks < KS; ks++) {
+              zr = MM::mul(ya[i][ks], br[ks], zr);
+              zi = MM::mul(ya[i][ks], bi[ks], zi);
+            }
+            const int row = 16 * tile + 4 * lg;
+            C2 *z = sZ + (size_t)(lt + li) * LY::ZB + row;
+            if constexpr (LY::ROWS % 4 == 0) {
+              if (LY::ROWS % 16 == 0 || row < LY::ROWS)
+#pragma unroll
+                for (int r = 0; r < 4; r++) z[r] = mk<T>(zr[r], zi[r]);
+            } else {
+#pragma unroll
+              for (int r = 0; r < 4; r++)
+                if (row + r < LY::ROWS) z[r] = mk<T>(zr[r], zi[r]);
+            }
+          }
+        }
+      }
+    }
+
+    // ---- sieve of the batch's q, in the order of p; 64 per chunk, chunk c
+    //      to wave (c + rotation) % WPB ----
+    const int ne = nl * N;
+    const int rot = (int)((s + q2_0) & (WPB - 1));
+    int base = 64 * ((wave - rot) & (WPB - 1));  // first entry of the wave's next chunk
+    const uint32_t step_l = (uint32_t)(64 * WPB) / (uint32_t)N, step_p = 64 * WPB - step_l * N;
+    uint32_t pl = (uint32_t)(base + lane) / (uint32_t)N, p1 = base + lane - pl * N;  // line in the batch, p1
+    // table entries of the next chunk, loaded a chunk ahead; lanes past the
+    // end read in bounds and are masked
+    double ep[NW], om[NM];
+    uint32_t item = 0, poff = 0;
+    auto fetch = [&]() __attribute__((always_inline)) {
+      const uint32_t l = min(pl, (uint32_t)(nl - 1)), q2 = q2_0 + l;
+      const uint32_t p2 = wrap_down(k2 + q2, N), q1 = wrap_up(p1 - k1, N);
+      item = p1 | (l << 9);
+      poff = __umul24(p2, N) + p1;
+      const uint32_t qoff = __umul24(q2, N) + q1;
+#pragma unroll
+      for (int m = 0; m < NW; m++) ep[m] = at_offset(eps_p + m, poff * (uint32_t)(8 * NW));
+#pragma unroll
+      for (int nu = 0; nu < NM; nu++) om[nu] = at_offset(om_q + nu, __umul24(qoff, 8 * NM));
+      p1 += step_p;
+      pl += step_l;
+      pl += (p1 >= (uint32_t)N) ? 1u : 0u;
+      p1 = wrap_down(p1, N);
+    };
+    if (base < ne) fetch();
+    bool more;
+    do {
+      int cnt = 0, listed = 0;
+      while (base < ne && cnt <= QC - 64 * NW) {
+        const int nlane = ne - base;  // lanes in range
+        const unsigned long long valid = nlane >= 64 ? ~0ull : (1ull << nlane) - 1ull;
+        double e_[NW], w_[NM];
+        unsigned long long okw[NM];  // modes above the frequency cut, lanes in range
+#pragma unroll
+        for (int m = 0; m < NW; m++) e_[m] = ep[m];
+#pragma unroll
+        for (int nu = 0; nu < NM; nu++) {
+          w_[nu] = om[nu];
+          okw[nu] = __ballot(om[nu] >= a.wcut) & valid;
+        }
+        const uint32_t item_ = item, poff_ = poff;
+        base += 64 * WPB;
+        if (base < ne) fetch();
+        // a term (nu, +-) is kept when |d +- w| <= cut with d = es - ep: the
+        // nearer of the two has |  |d| - w  |
+        unsigned long long hit = 0;
+#pragma unroll
+        for (int m = 0; m < NW; m++) {
+          const double d = es - e_[m];
+          if (!(__ballot(fabs(d) <= reach) & valid)) continue;  // wave-uniform
+          unsigned long long any = 0;
+#pragma unroll
+          for (int nu = 0; nu < NM; nu++) any |= __ballot(fabs(fabs(d) - w_[nu]) <= cut) & okw[nu];
+          if (any) {
+            hit |= any;
+            const bool mine = __builtin_amdgcn_inverse_ballot_w64(any);
+            if constexpr (MODE == kRates) {
+              if (mine) sQ[wave * QC + cnt + lanes_below(any)] = item_ | ((uint32_t)m << 15);
+            } else {
+              const bool in_list = mine && at_offset(stidx_p + m, poff_ * (uint32_t)(4 * NW)) >= 0;
+              const unsigned long long lm = __ballot(in_list);
+              if constexpr (MODE == kEmit) {
+                if (mine) {
+                  const int at = wave * QC + cnt + lanes_below(any);
+                  sQ[at] = item_ | ((uint32_t)m << 15) | (in_list ? 0x80000000u : 0u);
+                  sRank[at] = (uint16_t)(listed + lanes_below(lm));
+                }
+              }
+              listed += __popcll(lm);
+            }
+            cnt += (MODE == kCount) ? 0 : __popcll(any);
+          }
+        }
+        n_q += __popcll(hit);
+        for (int j = 0; j < nsh; j++) {  // the other states at this k point
+          const double e2 = a.eps[(int64_t)k * NW + a.sn[s + 1 + j]];
+#pragma unroll
+          for (int m = 0; m < NW; m++) {
+            const double d = fabs(e2 - e_[m]);
+#pragma unroll
+            for (int nu = 0; nu < NM; nu++) hit |= __ballot(fabs(d - w_[nu]) <= cut) & okw[nu];
+          }
+        }
+        if (count_kq) n_kq += __popcll(hit);
+      }
+      if constexpr (MODE == kCount) {
+        n_v += listed;
+        more = false;
+        continue;
+      }
+      n_v += cnt;
+      if (lane == 0) {
+        sCnt[wave * 4] = cnt;
+        sCnt[wave * 4 + 1] = listed;
+        sCnt[wave * 4 + 2] = base < ne ? 1 : 0;
+      }
+      __syncthreads();
+      // ---- vertices of all queues, one per lane ----
+      int pre[WPB + 1], lpre[WPB + 1];
+      pre[0] = lpre[0] = 0;
+      int left = 0;
+#pragma unroll
+      for (int w = 0; w < WPB; w++) {
+        pre[w + 1] = pre[w] + __builtin_amdgcn_readfirstlane(sCnt[w * 4]);
+        if constexpr (MODE == kEmit) lpre[w + 1] = lpre[w] + __builtin_amdgcn_readfirstlane(sCnt[w * 4 + 1]);
+        left |= __builtin_amdgcn_readfirstlane(sCnt[w * 4 + 2]);
+      }
+      more = left != 0;
+      const int total = pre[WPB];
+      for (int v0 = 64 * ((wave - rot) & (WPB - 1)); v0 < total; v0 += 64 * WPB) {
+        const bool live = v0 + lane < total;
+        const int i = min(v0 + lane, total - 1);  // lanes past the end repeat the last vertex and drop it
+        int at = i, lbase = 0;
+#pragma unroll
+        for (int w = 1; w < WPB; w++) {
+          at = (i >= pre[w]) ? i - pre[w] + w * QC : at;
+          if constexpr (MODE == kEmit) lbase = (i >= pre[w]) ? lpre[w] : lbase;
+        }
+        const uint32_t it = sQ[at];
+        const uint32_t vp1 = it & 511u, vl = (it >> 9) & 63u, m = (it >> 15) & 7u;
+        const uint32_t q2 = q2_0 + vl, p2 = wrap_down(k2 + q2, N), q1 = wrap_up(vp1 - k1, N);
+        const uint32_t qoff = __umul24(q2, N) + q1;              // q in its plane
+        const uint32_t pm = (__umul24(p2, N) + vp1) * NW + m;    // (p, m) in its plane
+        const double d = es - at_offset(eps_p, pm * 8u);
+        C2 vrow[NW];
+#pragma unroll
+        for (int j = 0; j < NW; j++) vrow[j] = at_offset(evec_p + j, pm * (uint32_t)(sizeof(C2) * NW));
+        // W_mu = sum_p e^{i 2 pi q1 p/N} sum_i conj(V_im(k+q)) Z(p; mu, i)
+        T wr[NM], wi[NM];
+        const C2 rq = sTab[q1];
+        const C2 *zs = sZ + (size_t)__umul24(vl, LY::ZB);
 #pragma unroll
         for (int mu = 0; mu < NM; mu++) {
-          wr[mu] += __shfl_xor(wr[mu], 1, 64);
-          wi[mu] += __shfl_xor(wi[mu], 1, 64);
+          wr[mu] = wi[mu] = 0;
+#pragma unroll
+          for (int j = 0; j < NW; j++) {
+            const C2 z = zs[(NB - 1) * C + mu * NW + j];
+            cmac_conj<T>(wr[mu], wi[mu], vrow[j].x, vrow[j].y, z.x, z.y);
+          }
         }
-      }
-      double contrib[EPH_MAX_TEMPS];
-      if constexpr (sizeof(T) == 8) {
-        // FP64: the q-side data is loaded mode by mode (a single batch does not
-        // fit the registers next to Y); occupation rows are padded to
-        // EPH_MAX_TEMPS and padding is never accumulated into a written rate
-        double fo[EPH_MAX_TEMPS];
+#pragma unroll 1
+        for (int pp = NB - 2; pp >= 0; pp--) {
 #pragma unroll
-        for (int t = 0; t < EPH_MAX_TEMPS; t++) fo[t] = a.occ_f[(pidx * NW + m) * EPH_MAX_TEMPS + t];
+          for (int mu = 0; mu < NM; mu++) {
+            T tr = 0, ti = 0;
+            cmac<T>(tr, ti, rq.x, rq.y, wr[mu], wi[mu]);
 #pragma unroll
-        for (int t = 0; t < EPH_MAX_TEMPS; t++) contrib[t] = 0.0;
+            for (int j = 0; j < NW; j++) {
+              const C2 z = zs[pp * C + mu * NW + j];
+              cmac_conj<T>(tr, ti, vrow[j].x, vrow[j].y, z.x, z.y);
+            }
+            wr[mu] = tr;
+            wi[mu] = ti;
+          }
+        }
+        // modes: with a = |g|^2 (d+ + d-), b = |g|^2 (d+ - d-), c = |g|^2 d-
+        // (d+- the Gaussians), sum_nu |g|^2 [(N + f) d+ + (1 + N - f) d-] =
+        // sum_nu N a + f sum_nu b + sum_nu c.  Every mode is evaluated and
+        // masked (about 5 of the 6 (nu, +-) terms of a vertex are kept, so
+        // branching would not save work).
+        T sb = 0, sc = 0, ct[NT];
 #pragma unroll
-        for (int nl = 0; nl < NML; nl++) {
-          const int nu = h * NML + nl;
-          const bool okp = (vp >> nu) & 1u, okm = (vm >> nu) & 1u;
-          if (!(okp || okm)) continue;
+        for (int t = 0; t < NT; t++) ct[t] = 0;
+#pragma unroll(MU)
+        for (int nu = 0; nu < NM; nu++) {
+          const double w = at_offset(om_q + nu, __umul24(qoff, 8 * NM)), xpd = d + w, xmd = d - w;
+          const bool on = live && w >= a.wcut;
+          const bool okp = on && fabs(xpd) <= cut, okm = on && fabs(xmd) <= cut;
+          n_t += __popcll(__ballot(okp)) + __popcll(__ballot(okm));
           T gr = 0, gi = 0;
 #pragma unroll
           for (int mu = 0; mu < NM; mu++) {
-            const C2 u = a.uu[(qidx * NM + nu) * NM + mu];
+            const C2 u = at_offset(uu_q + nu * NM + mu, __umul24(qoff, (uint32_t)(sizeof(C2) * NM * NM)));
             cmac<T>(gr, gi, wr[mu], wi[mu], u.x, u.y);
           }
-          const double g2 = fma((double)gr, (double)gr, (double)gi * (double)gi);
-          const double xp = es + omq[nl] - epm, xm = es - omq[nl] - epm;
-          const double dp = okp ? exp(-(xp * inv_eta) * (xp * inv_eta)) * dnorm : 0.0;
-          const double dm = okm ? exp(-(xm * inv_eta) * (xm * inv_eta)) * dnorm : 0.0;
-#pragma unroll
-          for (int t = 0; t < EPH_MAX_TEMPS; t++) {
-            const double nq = a.occ_n[(qidx * NM + nu) * EPH_MAX_TEMPS + t];
-            contrib[t] = fma(g2, fma(nq + fo[t], dp, (1.0 + nq - fo[t]) * dm), contrib[t]);
+          const T g2 = fma(gr, gr, gi * gi);
+          T dp, dm;
+          if constexpr (sizeof(T) == 8) {
+            dp = okp ? exp(-(xpd * inv_eta) * (xpd * inv_eta)) * dnorm : 0.0;
+            dm = okm ? exp(-(xmd * inv_eta) * (xmd * inv_eta)) * dnorm : 0.0;
+          } else {
+            // FP32 form: |g|^2, the Gaussians and the occupation weights in
+            // FP32 (the arguments x are formed in FP64 from the FP64 energies)
+            const float xp = (float)xpd * (float)inv_eta, xm = (float)xmd * (float)inv_eta;
+            dp = okp ? __expf(-xp * xp) * (float)dnorm : 0.f;
+            dm = okm ? __expf(-xm * xm) * (float)dnorm : 0.f;
           }
-        }
-      } else {
-        // FP32 form: the q-side data of this lane's modes and the Fermi
-        // factors in one batch of loads from FP32 copies of the tables, and
-        // |g|^2, the Gaussians and the occupation weights in FP32 (the
-        // arguments x are formed in FP64 from the FP64 energies); the
-        // vertex's contribution is then accumulated in FP64 (occupation rows
-        // are padded to EPH_MAX_TEMPS; padding is never accumulated into a
-        // written rate)
-        static_assert(EPH_MAX_TEMPS == 4, "occupation rows are read as one float4");
-        C2 uq[NML][NM];
-        float4 nqv[NML];
+          const T ga = g2 * (dp + dm);
+          sb = fma(g2, dp - dm, sb);
+          sc = fma(g2, dm, sc);
 #pragma unroll
-        for (int nl = 0; nl < NML; nl++)
-#pragma unroll
-          for (int mu = 0; mu < NM; mu++) uq[nl][mu] = a.uu32[(qidx * NM + h * NML + nl) * NM + mu];
-#pragma unroll
-        for (int nl = 0; nl < NML; nl++)
-          nqv[nl] = reinterpret_cast<const float4 *>(a.occ32_n)[qidx * NM + h * NML + nl];
-        const float4 fo = reinterpret_cast<const float4 *>(a.occ32_f)[pidx * NW + m];
-        const float ie = (float)inv_eta, dn = (float)dnorm;
-        float cf[EPH_MAX_TEMPS] = {0.f, 0.f, 0.f, 0.f};
-        // every mode is evaluated and masked (about 5 of the 6 (nu, +-) terms
-        // of a vertex are kept, so branching would not save work)
-#pragma unroll
-        for (int nl = 0; nl < NML; nl++) {
-          const int nu = h * NML + nl;
-          const bool okp = (vp >> nu) & 1u, okm = (vm >> nu) & 1u;
-          T gr = 0, gi = 0;
-#pragma unroll
-          for (int mu = 0; mu < NM; mu++) cmac<T>(gr, gi, wr[mu], wi[mu], uq[nl][mu].x, uq[nl][mu].y);
-          const float g2 = fmaf(gr, gr, gi * gi);
-          const float xp = (float)(es + omq[nl] - epm) * ie, xm = (float)(es - omq[nl] - epm) * ie;
-          const float dp = okp ? __expf(-xp * xp) * dn : 0.f, dm = okm ? __expf(-xm * xm) * dn : 0.f;
-          const float nq[EPH_MAX_TEMPS] = {nqv[nl].x, nqv[nl].y, nqv[nl].z, nqv[nl].w};
-          const float ff[EPH_MAX_TEMPS] = {fo.x, fo.y, fo.z, fo.w};
-#pragma unroll
-          for (int t = 0; t < EPH_MAX_TEMPS; t++)
-            cf[t] = fmaf(g2, fmaf(nq[t] + ff[t], dp, (1.f + nq[t] - ff[t]) * dm), cf[t]);
+          for (int t = 0; t < NT; t++)
+            ct[t] = fma(at_offset(occ_q + nu * NT + t, __umul24(qoff, (uint32_t)(sizeof(T) * NM * NT))), ga, ct[t]);
         }
 #pragma unroll
-        for (int t = 0; t < EPH_MAX_TEMPS; t++) contrib[t] = (double)cf[t];
-      }
+        for (int t = 0; t < NT; t++) ct[t] += fma(at_offset(occ_p + t, pm * (uint32_t)(sizeof(T) * NT)), sb, sc);
+        if (live) {
 #pragma unroll
-      for (int ss = 0; ss < GW; ss++) {
-        const bool me = ss == s;
+          for (int t = 0; t < NT; t++) acc[t] += (double)ct[t];
+          if constexpr (MODE == kEmit) {
+            if (it >> 31) {  // final state in the list: its transition rate
+              const int64_t e = gpos + lbase + sRank[at];
+              a.g_col[e] = at_offset(stidx_p, pm * 4u);
 #pragma unroll
-        for (int t = 0; t < EPH_MAX_TEMPS; t++) acc[ss][t] += me ? contrib[t] : 0.0;
-      }
-      if constexpr (MODE == kEmit) {
-        // the vertex's transition rate: both halves' modes, emitted by lane half 0
-#pragma unroll
-        for (int t = 0; t < EPH_MAX_TEMPS; t++) {
-          double v = contrib[t];
-          if constexpr (VL == 2) v += __shfl_xor(v, 1, 64);
-          e_val[t] = a.pref * v;
-        }
-        e_col = (h == 0) ? a.stidx[pidx * NW + m] : -1;
-        e_state = s;
-      }
-      }
-      if constexpr (MODE == kEmit) {
-        // entries of one state go to consecutive positions in lane order
-        // (all lanes take part in the ballots)
-        const bool keep = e_col >= 0;
-#pragma unroll
-        for (int ss = 0; ss < GW; ss++) {
-          const unsigned long long bits = __ballot(keep && e_state == ss);
-          if (keep && e_state == ss) {
-            const int64_t e = gcur[ss] + __popcll(bits & ((1ull << lane) - 1ull)) - a.g_base;
-            a.g_col[e] = e_col;
-            for (int t = 0; t < EPH_MAX_TEMPS; t++)
-              if (t < nt) a.g_val[(int64_t)t * a.g_stride + e] = e_val[t];
-          }
-          gcur[ss] += __popcll(bits);
-        }
-      }
-    }
-  };
-  auto vpop = [&](int n) __attribute__((always_inline)) {
-    const int rem = vn - n;
-    for (int b = 0; b < rem; b += 64) {
-      const uint2 v = (b + lane < rem) ? sV[n + b + lane] : make_uint2(0u, 0u);
-      __syncwarp();
-      if (b + lane < rem) sV[b + lane] = v;
-      __syncwarp();
-    }
-    vn = rem;
-  };
-  auto stage1 = [&](int count) __attribute__((always_inline)) {
-    for (int base = 0; base < count; base += 64) {
-      const int i = base + lane;
-      const bool act = i < count;
-      const uint32_t it = act ? sQ[i] : 0u;
-      const int p1 = (int)(it & 1023u), ks = (int)((it >> 10) & 31u), zs_slot = (int)((it >> 15) & 3u);
-      const unsigned bmask = it >> 17;  // final bands that passed the prefilter (0 for idle lanes)
-      const int line = sSlot[2 * zs_slot + 1], q2 = sSlot[2 * zs_slot];
-      int q1 = p1 - sK1[ks];
-      q1 += (q1 < 0) ? N : 0;
-      const int i1 = imod(q1 * lo1, N);
-      const int64_t qidx = q1 + (int64_t)N * (q2 + (int64_t)N * a.q3_cur);
-      const int64_t pidx = p1 + (int64_t)N * line;
-      double om[NM], ep[NW];
-#pragma unroll
-      for (int nu = 0; nu < NM; nu++) om[nu] = act ? a.om[qidx * NM + nu] : 0.0;
-#pragma unroll
-      for (int m = 0; m < NW; m++) ep[m] = act ? a.eps[pidx * NW + m] : 0.0;
-      // modes above the frequency cut (branch-free bit mask)
-      unsigned okw = 0u;
-#pragma unroll
-      for (int nu = 0; nu < NM; nu++) okw |= (om[nu] >= a.wcut) ? (1u << nu) : 0u;
-      // bands some lane needs: a band outside the prefilter window of every
-      // lane's k-slot keeps no term, so it is skipped by the whole wave
-      unsigned long long band_any[NW];
-#pragma unroll
-      for (int m = 0; m < NW; m++) band_any[m] = __ballot((bmask >> m) & 1u);
-      const int sf = sKfirst[ks], sc = act ? sKcnt[ks] : 0;
-      double esr[NW];
-#pragma unroll
-      for (int j = 0; j < NW; j++) esr[j] = (j < sc) ? sEps[sf + j] : 0.0;
-      bool hit = false;
-#pragma unroll
-      for (int j = 0; j < NW; j++) {
-        if (j >= KMX) break;  // wave-uniform
-        const int s = sf + j;
-        const bool sv = j < sc;
-        const unsigned okj = sv ? okw : 0u;
-        const double es = esr[j];
-        // (es + w) and (es - w) once per state, in the oracle's order
-        double wp[NM], wm[NM];
-#pragma unroll
-        for (int nu = 0; nu < NM; nu++) {
-          wp[nu] = es + om[nu];
-          wm[nu] = es - om[nu];
-        }
-        bool hit_s = false;
-        unsigned nterm = 0;
-#pragma unroll
-        for (int m = 0; m < NW; m++) {
-          if (!band_any[m]) continue;  // wave-uniform
-          unsigned vp = 0u, vm = 0u;
-#pragma unroll
-          for (int nu = 0; nu < NM; nu++) {
-            vp |= (fabs(wp[nu] - ep[m]) <= cut) ? (1u << nu) : 0u;
-            vm |= (fabs(wm[nu] - ep[m]) <= cut) ? (1u << nu) : 0u;
-          }
-          vp &= okj;
-          vm &= okj;
-          const bool any = (vp | vm) != 0u;
-          hit_s |= any;
-          nterm += (unsigned)(__popc(vp) + __popc(vm));
-          const bool push = any && s < S;
-          const unsigned long long bits = __ballot(push);
-          if (push)
-            sV[vn + __popcll(bits & ((1ull << lane) - 1ull))] =
-                make_uint2((uint32_t)p1 | ((uint32_t)q1 << 10) | ((uint32_t)i1 << 20) | ((uint32_t)zs_slot << 30),
-                           (uint32_t)s | ((uint32_t)m << 3) | (vp << 6) | (vm << 12) | ((uint32_t)q2 << 18));
-          vn += __popcll(bits);
-        }
-        hit = hit || hit_s;
-        // branch-free per-slot updates (a select on s would become a
-        // dynamically indexed private array)
-#pragma unroll
-        for (int ss = 0; ss < GW; ss++) {
-          const bool me = (ss == s) && sv;
-          nq_s[ss] += (me && hit_s) ? 1u : 0u;
-          nt_s[ss] += me ? nterm : 0u;
-        }
-      }
-      if (act && hit && !(cont && ks == 0)) my_nkq++;
-      __syncwarp();
-      if (vn >= 64) {  // keep the vertex queue below one pass before the next candidates
-        const int vf = vn & ~63;
-        vdrain(vf);
-        __syncwarp();
-        vpop(vf);
-      }
-    }
-  };
-  // drop the first n entries of the queue (after they were evaluated)
-  auto pop = [&](int n) __attribute__((always_inline)) {
-    const int rem = qn - n;
-    for (int b = 0; b < rem; b += 64) {
-      const uint32_t v = (b + lane < rem) ? sQ[n + b + lane] : 0u;
-      __syncwarp();
-      if (b + lane < rem) sQ[b + lane] = v;
-      __syncwarp();
-    }
-    qn = rem;
-  };
-
-  int ql = 0;  // q-lines started in this launch
-  const LT *nline = eline;  // energies of the next q-line
-  for (int q3 = a.q3_lo; q3 < a.q3_hi; q3++) {
-    // ---- Y_s(p1, p2; q3) into registers (p3 loop rolled) ----
-#pragma unroll
-    for (int j = 0; j < NPAIR; j++)
-#pragma unroll
-      for (int p2 = 0; p2 < NB; p2++) yr[j][p2] = yi[j][p2] = 0;
-    if constexpr (MODE != kCount) {
-      // one pair slot at a time, p3 rolled: at most NB loads of X in flight,
-      // so the loads do not compete with Y for registers
-#pragma unroll
-      for (int j = 0; j < NPAIR; j++) {
-        const int P = lane + 64 * j;
-        const int s = P / (NB * C), p1 = (P / C) % NB, c = P % C;
-        if (s < S) {
-          const C2 *xs = Xg + (s0 + s - a.s_base) * xrow + (int64_t)p1 * NB * NB * C + c;
-          int i3 = imod(q3 * lo3, N);
-#pragma unroll 1
-          for (int p3 = 0; p3 < NB; p3++) {
-            const C2 ph = sTab[i3];
-            i3 += q3;
-            i3 -= (i3 >= N) ? N : 0;
-#pragma unroll
-            for (int p2 = 0; p2 < NB; p2++) {
-              const C2 x = xs[p2 * NB * C + p3 * C];
-              cmac<T>(yr[j][p2], yi[j][p2], ph.x, ph.y, x.x, x.y);
+              for (int t = 0; t < NT; t++)
+                if (t < a.nt) a.g_val[(int64_t)t * a.g_stride + e] = a.pref * (double)ct[t];
             }
           }
         }
       }
-    }
-    const int p3line = (k3 + q3 >= N) ? k3 + q3 - N : k3 + q3;
-    for (int q2 = 0; q2 < N; q2++, ql++) {
-      const int zslot = ql & (NZ - 1);
-      {  // the Z slot is reused: evaluate queued work that still points at it
-        bool stale = false;
-        for (int b = 0; b < qn; b += 64)
-          stale |= (b + lane < qn) && (int)((sQ[b + lane] >> 15) & 3u) == zslot;
-        for (int b = 0; b < vn; b += 64)
-          stale |= (b + lane < vn) && (int)(sV[b + lane].x >> 30) == zslot;
-        if (__any(stale)) {
-          stage1(qn);
-          __syncwarp();
-          qn = 0;
-          vdrain(vn);
-          __syncwarp();
-          vn = 0;
-        }
-      }
-      {  // issue the loads of the next q-line's energies
-        int nq2 = q2 + 1, nq3 = q3;
-        if (nq2 == N) {
-          nq2 = 0;
-          nq3 = (q3 + 1 == N) ? 0 : q3 + 1;
-        }
-        const int n2l = (k2 + nq2 >= N) ? k2 + nq2 - N : k2 + nq2;
-        const int n3l = (k3 + nq3 >= N) ? k3 + nq3 - N : k3 + nq3;
-        nline = eline + (size_t)(n2l + N * n3l) * LN;
-        if constexpr (PF) {
-#pragma unroll
-          for (int i = 0; i < LPL; i++) {
-            const int e = lane + 64 * i;
-            nxt[i] = (e < LN) ? nline[e] : (LT)0;
-          }
-        }
-      }
-      // ---- Z_s(p1; q2, q3) -> LDS slot ----
-      C2 ph2[NB];
-      {
-        int i2 = imod(q2 * lo2, N);
-#pragma unroll
-        for (int p = 0; p < NB; p++) {
-          ph2[p] = sTab[i2];
-          i2 += q2;
-          i2 -= (i2 >= N) ? N : 0;
-        }
-      }
-      C2 *zslot_base = sZ + (size_t)zslot * GW * LY::ZB;
-#pragma unroll
-      for (int j = 0; j < NPAIR; j++) {
-        const int P = lane + 64 * j;
-        if (MODE != kCount && P < GW * NB * C) {
-          T r = 0, i = 0;
-#pragma unroll
-          for (int p2 = 0; p2 < NB; p2++) cmac<T>(r, i, ph2[p2].x, ph2[p2].y, yr[j][p2], yi[j][p2]);
-          zslot_base[(P / (NB * C)) * LY::ZB + P % (NB * C)] = mk<T>(r, i);
-        }
-      }
-      const int p2line = (k2 + q2 >= N) ? k2 + q2 - N : k2 + q2;
-      const int line = p2line + N * p3line;
-      if (lane == 0) {
-        sSlot[2 * zslot] = q2;
-        sSlot[2 * zslot + 1] = line;
-      }
-      __syncwarp();
-      // ---- candidates of this q-line: (k-slot, p1) with some band in the window ----
-      // The states of one k point come in band order, so their energies
-      // ascend; a final band within W of any of them lies in [e_first - W,
-      // e_last + W], which is tested in float (a superset of the exact
-      // test, which the FP64 sieve then makes).
-      for (int ks = 0; ks < NK; ks++) {
-        const int sf = sKfirst[ks], sc = sKcnt[ks];
-        const float lo_w = (float)(sEps[sf] - W), hi_w = (float)(sEps[sf + sc - 1] + W);
-        for (int c0 = 0; c0 < N; c0 += 64) {
-          const int p1 = c0 + lane;
-          unsigned bm = 0u;  // bands of this p1 inside the window
-          if (p1 < N) {
-            float ev[NW];
-            if constexpr (NW % 4 == 0) {
-#pragma unroll
-              for (int v = 0; v < NW / 4; v++) {
-                const float4 f = reinterpret_cast<const float4 *>(sLine + (size_t)p1 * NW)[v];
-                ev[4 * v] = f.x;
-                ev[4 * v + 1] = f.y;
-                ev[4 * v + 2] = f.z;
-                ev[4 * v + 3] = f.w;
-              }
-            } else {
-#pragma unroll
-              for (int m = 0; m < NW; m++) ev[m] = sLine[p1 * NW + m];
-            }
-#pragma unroll
-            for (int m = 0; m < NW; m++) bm |= ((ev[m] >= lo_w) & (ev[m] <= hi_w)) ? (1u << m) : 0u;
-          }
-          const bool any = bm != 0u;
-          const unsigned long long bits = __ballot(any);
-          if (any) sQ[qn + __popcll(bits & ((1ull << lane) - 1ull))] =
-              (uint32_t)p1 | ((uint32_t)ks << 10) | ((uint32_t)zslot << 15) | (bm << 17);
-          qn += __popcll(bits);
-          __syncwarp();
-          if (qn >= 64) {  // whole passes only, so the queue stays below 128
-            const int full = qn & ~63;
-            stage1(full);
-            __syncwarp();
-            pop(full);
-          }
-        }
-      }
-      __syncwarp();
-      // stage the next line's energies; the scan of this line is done, and
-      // the drains read energies from global memory
-      if constexpr (PF) {
-#pragma unroll
-        for (int i = 0; i < LPL; i++) {
-          const int e = lane + 64 * i;
-          if (e < LN) sLine[e] = nxt[i];
-        }
-      } else {
-        copy_line(nline);
-      }
-      __syncwarp();
-    }
+      if constexpr (MODE == kEmit) gpos += lpre[WPB];
+      __syncthreads();  // queues and Z are rewritten
+    } while (more);
   }
-  stage1(qn);
-  __syncwarp();
-  vdrain(vn);
 
-  if constexpr (MODE == kCount) {
-    // per-state counts of transition rates, added up over the plane launches
-#pragma unroll
-    for (int s = 0; s < GW; s++) {
-      int64_t c = gcur[s];
-#pragma unroll
-      for (int m = 32; m >= 1; m >>= 1) c += __shfl_xor(c, m, 64);
-      if (lane == 0 && s < S) a.g_cursor[s0 + s] += c;
+  if constexpr (MODE == kCount) {  // this plane's transition rates of the state
+    if (lane == 0) sCnt[wave] = n_v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int64_t c = 0;
+      for (int w = 0; w < WPB; w++) c += sCnt[w];
+      if (a.g_slot) a.g_slot[plane * a.ns_total + s] = c;
+      else a.g_cursor[s] += c;
     }
     return;
   }
-  if constexpr (MODE == kEmit) {
-#pragma unroll
-    for (int s = 0; s < GW; s++)
-      if (lane == 0 && s < S) a.g_cursor[s0 + s] = gcur[s];
-  }
+  if constexpr (MODE == kEmit)
+    if (threadIdx.x == 0 && !a.g_slot) a.g_cursor[s] = gpos + a.g_base;
 
-  // ---- fixed-order reductions; q3 slabs add up in launch order ----
+  // ---- fixed-order reductions; planes add up in order ----
 #pragma unroll
-  for (int s = 0; s < GW; s++) {
+  for (int t = 0; t < NT; t++) {
+    double v = acc[t];
 #pragma unroll
-    for (int t = 0; t < EPH_MAX_TEMPS; t++) {
-      double v = acc[s][t];
-#pragma unroll
-      for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-      if (lane == 0 && s < S && t < nt) {
-        double *dst = a.inv_tau + (int64_t)t * a.ns_total + s0 + s;
-        *dst = (a.q3_lo == 0 ? 0.0 : *dst) + a.pref * v;
-      }
-    }
-    unsigned long long c1 = nq_s[s], c2 = nt_s[s];
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-      c1 += __shfl_xor(c1, m, 64);
-      c2 += __shfl_xor(c2, m, 64);
-    }
-    if (lane == 0 && s < S) {
-      int64_t *dst = a.st_counts + (s0 + s) * 2;
-      dst[0] = (a.q3_lo == 0 ? 0 : dst[0]) + (int64_t)c1;
-      dst[1] = (a.q3_lo == 0 ? 0 : dst[1]) + (int64_t)c2;
-    }
-  }
-  unsigned long long v1 = my_nkq, v2 = my_nv;
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    v1 += __shfl_xor(v1, m, 64);
-    v2 += __shfl_xor(v2, m, 64);
+    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+    if (lane == 0) sRed[wave * 8 + t] = v;
   }
   if (lane == 0) {
-    atomicAdd(a.n_kq, v1);
-    atomicAdd(a.n_vertex, v2);
+    int *c = reinterpret_cast<int *>(sRed + wave * 8 + 4);
+    c[0] = n_q;
+    c[1] = n_t;
+    c[2] = n_kq;
+    c[3] = n_v;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < NT && (int)threadIdx.x < a.nt) {
+    const int t = threadIdx.x;
+    double v = 0.0;
+    for (int w = 0; w < WPB; w++) v += sRed[w * 8 + t];
+    v *= a.pref;
+    if (a.part_tau) {
+      a.part_tau[((int64_t)plane * a.nt + t) * a.ns_total + s] = v;
+    } else {
+      double *dst = a.inv_tau + (int64_t)t * a.ns_total + s;
+      *dst = (q3 == 0 ? 0.0 : *dst) + v;
+    }
+  } else if (threadIdx.x >= 8 && threadIdx.x < 12) {
+    const int j = threadIdx.x - 8;
+    int64_t v = 0;
+    for (int w = 0; w < WPB; w++) v += reinterpret_cast<const int *>(sRed + w * 8 + 4)[j];
+    if (a.part_tau) {
+      a.part_cnt[((int64_t)plane * a.ns_total + s) * 4 + j] = v;
+    } else {
+      int64_t *dst = (j < 2 ? a.st_counts : a.kv_counts - 2) + s * 2 + j;
+      *dst = (q3 == 0 ? 0 : *dst) + v;
+    }
   }
 }
 
-template <class T, int NW, int NM, int GW, int NB, int LPL, int MODE>
-hipError_t launch_wave_l(const RatesArgs &a, hipStream_t st) {
-  using LY = WaveLayout<T, NW, NM, GW, NB, float>;
-  const size_t sh = LY::total(a.N);
+template <class T, int NW, int NM, int NB, int NT, int MODE>
+hipError_t launch_wave(const RatesArgs &a, hipStream_t st) {
+  using LY = WaveLayout<T, NW, NM, NB>;
+  const size_t sh = LY::total(a.N, MODE);
   if (sh > 160 * 1024) return hipErrorInvalidValue;
-  auto kern = rates_wave_kernel<T, NW, NM, GW, NB, LPL, MODE>;
+  auto kern = rates_wave_kernel<T, NW, NM, NB, NT, MODE>;
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
   if (e != hipSuccess) return e;
-  const int64_t nblk = (a.ng + LY::WPB - 1) / LY::WPB;
-  const int64_t grid = ((nblk + 7) / 8) * 8;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(LY::WPB * 64), sh, st, a);
+  const int64_t grid = ((a.ns_launch + 7) / 8) * 8;
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid, (unsigned)(a.q3_hi - a.q3_lo)), dim3(LY::WPB * 64), sh, st, a);
   return hipGetLastError();
 }
 
-template <class T, int NW, int NM, int GW, int NB, int MODE>
-hipError_t launch_wave(const RatesArgs &a, hipStream_t st) {
-  const int ln = a.N * NW;
-  if (ln <= 512) return launch_wave_l<T, NW, NM, GW, NB, 8, MODE>(a, st);
-  if (ln <= 1024) return launch_wave_l<T, NW, NM, GW, NB, 16, MODE>(a, st);
-  if (ln <= 2048) return launch_wave_l<T, NW, NM, GW, NB, 32, MODE>(a, st);
-  return hipErrorNotSupported;
+template <class T, int NW, int NM, int NB, int MODE>
+hipError_t launch_wave_t(const RatesArgs &a, hipStream_t st) {
+  if constexpr (MODE == kCount) {
+    return launch_wave<T, NW, NM, NB, 1, MODE>(a, st);
+  } else {
+    if (a.nt == 1) return launch_wave<T, NW, NM, NB, 1, MODE>(a, st);
+    return launch_wave<T, NW, NM, NB, EPH_MAX_TEMPS, MODE>(a, st);
+  }
 }
 
-
 // Launch for one (precision, modes, mode) triple: dispatch on the orbital
-// count and the Rp box edge.  GW (states per group) must match
-// rates_wave_group.
+// count, the Rp box edge and the temperatures.
 template <class T, int NM, int MODE>
 hipError_t dispatch_nm(const RatesArgs &a, hipStream_t st) {
   const int nb = a.box.n[0];
-#define EPH_W(NW_, GW_)                                               \
-  if (a.nw == NW_) {                                                  \
-    if (nb == 4) return launch_wave<T, NW_, NM, GW_, 4, MODE>(a, st); \
-    if (nb == 6) return launch_wave<T, NW_, NM, GW_, 6, MODE>(a, st); \
-    return hipErrorNotSupported;                                      \
+#define EPH_W(NW_)                                                 \
+  if (a.nw == NW_) {                                               \
+    if (nb == 4) return launch_wave_t<T, NW_, NM, 4, MODE>(a, st); \
+    if (nb == 6) return launch_wave_t<T, NW_, NM, 6, MODE>(a, st); \
+    return hipErrorNotSupported;                                   \
   }
-  if constexpr (NM == 3) {
-    EPH_W(1, 2)
-    EPH_W(2, 2)
-    EPH_W(4, 2)
-    EPH_W(8, 1)
-  } else {
-    EPH_W(1, 2)
-    EPH_W(2, 2)
-    EPH_W(4, 1)
-    EPH_W(8, 1)
-  }
+  EPH_W(1)
+  EPH_W(2)
+  EPH_W(4)
+  EPH_W(8)
 #undef EPH_W
   return hipErrorNotSupported;
 }

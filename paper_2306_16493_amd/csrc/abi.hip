@@ -153,7 +153,7 @@ Workspace plan_workspace(const eph_ctx *c, int N, int precision, int64_t nkl, in
   if (precision == EPH_BF16X3) t += 4 * bf16_w_elems(c->nre, c->nw, (int)ncol);  // bf16 hi/lo of g
   if (wave) {
     t += NQ * (nw + nm) * EPH_MAX_TEMPS * 8;                        // occupation tables
-    t += NQ * nw * 4;                                               // sums of the planes of a launch (at most)
+    t += NQ * nw * 4;                                               // band ranges, sums of the slabs of a launch
   } else {
     t += NQ * nw * 10;                                              // energy-sorted lines
   }
@@ -472,22 +472,6 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
   EPH_HIP(c, electron_tables(c, N, U, st));
   EPH_HIP(c, phonon_tables(c, N, U, p->omega_cut_eV, ctr + 0, st));
   const bool fp32 = p->precision != EPH_FP64;
-  if (fp32) {  // FP32 copies of the rotation tables for the reduced-precision forms
-    EPH_HIP(c, c->evec32.ensure(sizeof(float2) * NQ * nw * nw));
-    EPH_HIP(c, c->uu32.ensure(sizeof(float2) * NQ * nm * nm));
-    EPH_HIP(c, launch_to_f32(NQ * nw * nw, c->evec.as<double2>(), c->evec32.as<float2>(), st));
-    EPH_HIP(c, launch_to_f32(NQ * nm * nm, c->uu.as<double2>(), c->uu32.as<float2>(), st));
-    const size_t nwt = (size_t)c->nre * nw * c->box.count() * nm * nw;
-    if (p->precision == EPH_FP32 && c->wt32.bytes < sizeof(float2) * nwt) {
-      EPH_HIP(c, c->wt32.ensure(sizeof(float2) * nwt));
-      EPH_HIP(c, launch_to_f32((int64_t)nwt, c->wt64.as<double2>(), c->wt32.as<float2>(), st));
-    }
-    const size_t nbf = 2 * bf16_w_elems(c->nre, nw, c->box.count() * nm * nw) * 2;  // hi + lo, 2 bytes each
-    if (p->precision == EPH_BF16X3 && c->wtbf.bytes < nbf) {
-      EPH_HIP(c, c->wtbf.ensure(nbf));
-      EPH_HIP(c, launch_split_bf16(c->nre, nw, c->box.count() * nm * nw, c->wt64.as<double2>(), c->wtbf.p, st));
-    }
-  }
   EPH_HIP(c, tm.mark(&e_tables));
 
   // ---- states in the window ----
@@ -501,7 +485,7 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
   EPH_HIP(c, c->offs.ensure(sizeof(int64_t) * (nkl + 1)));
   EPH_HIP(c, c->scan_tmp.ensure(sizeof(int64_t) * scan_tmp_elems(nkl + 1)));
   EPH_HIP(c, launch_zero(c->cnt.as<int64_t>() + nkl, sizeof(int64_t), st));
-  EPH_HIP(c, launch_count_states(nkl, d_klist, nw, c->eps.as<double>(), blo, bhi, p->win_lo_eV, p->win_hi_eV,
+  EPH_HIP(c, launch_count_states(nkl, d_klist, N, nw, c->eps.as<double>(), blo, bhi, p->win_lo_eV, p->win_hi_eV,
                                  c->cnt.as<int64_t>(), st));
   EPH_HIP(c, launch_scan(nkl + 1, c->cnt.as<int64_t>(), c->offs.as<int64_t>(), c->scan_tmp.as<int64_t>(), st));
   int64_t ns = 0;
@@ -514,7 +498,7 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
     if (counts) *counts = cn;
     return fail(c, EPH_E_TRUNCATED, "capacity below the number of states");
   }
-  EPH_HIP(c, launch_write_states(nkl, d_klist, nw, c->eps.as<double>(), c->vel.as<double>(), blo, bhi, p->win_lo_eV,
+  EPH_HIP(c, launch_write_states(nkl, d_klist, N, nw, c->eps.as<double>(), c->vel.as<double>(), blo, bhi, p->win_lo_eV,
                                  p->win_hi_eV, c->offs.as<int64_t>(), state_k, state_n, energy_eV, vel_ms, st));
   if (states_only && !gr) {
     EPH_HIP(c, hipStreamSynchronize(st));
@@ -556,43 +540,73 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
     int64_t *gstart = nullptr;
     std::vector<int64_t> hg;
     if (groups) {
-    EPH_HIP(c, c->grp_tmp.ensure(sizeof(int64_t) * 2 * (ns + 1)));
-    int64_t *flag = c->grp_tmp.as<int64_t>(), *pos = flag + ns + 1;
-    EPH_HIP(c, c->scan_tmp.ensure(sizeof(int64_t) * std::max(scan_tmp_elems(nkl + 1), scan_tmp_elems(ns))));
-    EPH_HIP(c, launch_group_heads(ns, state_k, N, gmax, flag, st));
-    EPH_HIP(c, launch_scan(ns, flag, pos, c->scan_tmp.as<int64_t>(), st));
-    int64_t lastpf[2];
-    EPH_HIP(c, hipMemcpyAsync(&lastpf[0], pos + ns - 1, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    EPH_HIP(c, hipMemcpyAsync(&lastpf[1], flag + ns - 1, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    EPH_HIP(c, hipStreamSynchronize(st));
-    ng = lastpf[0] + lastpf[1];
-    EPH_HIP(c, c->grp_start.ensure(sizeof(int64_t) * (ng + 1)));
-    gstart = c->grp_start.as<int64_t>();
-    EPH_HIP(c, launch_group_starts(ns, flag, pos, gstart, st));
-    hg.resize(ng + 1);
-    EPH_HIP(c, hipMemcpyAsync(hg.data(), gstart, sizeof(int64_t) * (ng + 1), hipMemcpyDeviceToHost, st));
+      EPH_HIP(c, c->grp_tmp.ensure(sizeof(int64_t) * 2 * (ns + 1)));
+      int64_t *flag = c->grp_tmp.as<int64_t>(), *pos = flag + ns + 1;
+      EPH_HIP(c, c->scan_tmp.ensure(sizeof(int64_t) * std::max(scan_tmp_elems(nkl + 1), scan_tmp_elems(ns))));
+      EPH_HIP(c, launch_group_heads(ns, state_k, N, gmax, flag, st));
+      EPH_HIP(c, launch_scan(ns, flag, pos, c->scan_tmp.as<int64_t>(), st));
+      int64_t lastpf[2];
+      EPH_HIP(c, hipMemcpyAsync(&lastpf[0], pos + ns - 1, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+      EPH_HIP(c, hipMemcpyAsync(&lastpf[1], flag + ns - 1, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+      EPH_HIP(c, hipStreamSynchronize(st));
+      ng = lastpf[0] + lastpf[1];
+      EPH_HIP(c, c->grp_start.ensure(sizeof(int64_t) * (ng + 1)));
+      gstart = c->grp_start.as<int64_t>();
+      EPH_HIP(c, launch_group_starts(ns, flag, pos, gstart, st));
+      hg.resize(ng + 1);
+      EPH_HIP(c, hipMemcpyAsync(hg.data(), gstart, sizeof(int64_t) * (ng + 1), hipMemcpyDeviceToHost, st));
     }
     auto gfirst = [&](int64_t g) { return groups ? hg[g] : g; };  // first state of a group
 
+    if (fp32) {  // reduced-precision copies of g, made once
+      const size_t nwt = (size_t)c->nre * nw * c->box.count() * nm * nw;
+      if (p->precision == EPH_FP32 && c->wt32.bytes < sizeof(float2) * nwt) {
+        EPH_HIP(c, c->wt32.ensure(sizeof(float2) * nwt));
+        EPH_HIP(c, launch_to_f32((int64_t)nwt, c->wt64.as<double2>(), c->wt32.as<float2>(), st));
+      }
+      const size_t nbf = 2 * bf16_w_elems(c->nre, nw, c->box.count() * nm * nw) * 2;  // hi + lo, 2 bytes each
+      if (p->precision == EPH_BF16X3 && c->wtbf.bytes < nbf) {
+        EPH_HIP(c, c->wtbf.ensure(nbf));
+        EPH_HIP(c, launch_split_bf16(c->nre, nw, c->box.count() * nm * nw, c->wt64.as<double2>(), c->wtbf.p, st));
+      }
+    }
     // temperatures per row of the occupation tables (the k-batch kernels read
     // full rows)
     const int occ_row = kbatch_q > 0 ? EPH_MAX_TEMPS : occ_stride(p->n_temps);
-    // ---- energy-sorted final-state lines (workgroup form) or occupation
-    //      tables (wave form); largest phonon energy ----
+    // ---- tables of the rate kernel: the workgroup form's energy-sorted lines
+    //      and FP32 rotation tables; the wave form's band ranges, and its
+    //      occupations or FP32 records ----
+    size_t rec_q = 0;
     if (gwave == 0) {
       EPH_HIP(c, c->line_e.ensure(sizeof(double) * NQ * nw));
       EPH_HIP(c, c->line_key.ensure(sizeof(uint16_t) * NQ * nw));
       EPH_HIP(c, launch_line_sort(N, nw, c->eps.as<double>(), c->line_e.as<double>(), c->line_key.as<uint16_t>(),
                                   st));
+      if (fp32) {
+        EPH_HIP(c, c->evec32.ensure(sizeof(float2) * NQ * nw * nw));
+        EPH_HIP(c, c->uu32.ensure(sizeof(float2) * NQ * nm * nm));
+        EPH_HIP(c, launch_to_f32(NQ * nw * nw, c->evec.as<double2>(), c->evec32.as<float2>(), st));
+        EPH_HIP(c, launch_to_f32(NQ * nm * nm, c->uu.as<double2>(), c->uu32.as<float2>(), st));
+      }
     } else {
       double kts[EPH_MAX_TEMPS];
       for (int t = 0; t < p->n_temps; t++) kts[t] = U.kb_evk * p->temps_K[t];
-      EPH_HIP(c, c->occ.ensure(sizeof(double) * NQ * (nw + nm) * occ_row));
-      EPH_HIP(c, launch_occupations(NQ, nw, nm, c->eps.as<double>(), c->om.as<double>(), p->mu_eV, p->n_temps, kts,
-                                    p->omega_cut_eV, occ_row, c->occ.as<double>(),
-                                    c->occ.as<double>() + (size_t)NQ * nw * occ_row, st));
+      if (kbatch_q == 0) {
+        EPH_HIP(c, c->ranges.ensure(sizeof(float2) * nw * N * wave_plane_groups(N)));
+        EPH_HIP(c, launch_band_ranges(N, nw, c->eps.as<double>(), c->ranges.as<float2>(), st));
+      }
+      if (fp32) {
+        EPH_HIP(c, c->rec.ensure(wave_rec_bytes(nw, nm, p->n_temps, NQ, &rec_q)));
+        EPH_HIP(c, launch_wave_records(N, nw, nm, c->eps.as<double>(), c->om.as<double>(), c->evec.as<double2>(),
+                                       c->uu.as<double2>(), p->mu_eV, p->n_temps, kts, p->omega_cut_eV, c->rec.p, st));
+      } else {
+        EPH_HIP(c, c->occ.ensure(sizeof(double) * NQ * (nw + nm) * occ_row));
+        EPH_HIP(c, launch_occupations(N, nw, nm, c->eps.as<double>(), c->om.as<double>(), p->mu_eV, p->n_temps, kts,
+                                      p->omega_cut_eV, kbatch_q > 0, c->occ.as<double>(),
+                                      c->occ.as<double>() + (size_t)NQ * nw * occ_row, st));
+      }
     }
-    EPH_HIP(c, launch_max_nonneg(NQ * nm, c->om.as<double>(), ctr + 1, st));
+    EPH_HIP(c, launch_max_nonneg(NQ * nm, c->om.as<double>(), gwave > 0 && kbatch_q == 0 ? p->omega_cut_eV : 0.0, ctr + 1, st));
     EPH_HIP(c, tm.mark(&e_prep));
     unsigned long long wbits = 0;
     EPH_HIP(c, hipMemcpyAsync(&wbits, ctr + 1, sizeof(wbits), hipMemcpyDeviceToHost, st));
@@ -635,35 +649,43 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
     }
     a.n_kq = ctr + 2;
     a.n_vertex = ctr + 6;
-    a.evec32 = fp32 ? c->evec32.as<float2>() : nullptr;
-    a.uu32 = fp32 ? c->uu32.as<float2>() : nullptr;
-    a.occ_f = c->occ.as<double>();
-    a.occ_n = c->occ.as<double>() + (size_t)NQ * nw * occ_row;
-    a.occ32_f = a.occ32_n = nullptr;
-    if (gwave > 0 && fp32) {  // FP32 copies of the occupation tables
-      const size_t no = (size_t)NQ * (nw + nm) * occ_row;
-      EPH_HIP(c, c->occ32.ensure(sizeof(float) * no));
-      EPH_HIP(c, launch_real_to_f32((int64_t)no, c->occ.as<double>(), c->occ32.as<float>(), st));
-      a.occ32_f = c->occ32.as<float>();
-      a.occ32_n = c->occ32.as<float>() + (size_t)NQ * nw * occ_row;
+    a.evec32 = fp32 && gwave == 0 ? c->evec32.as<float2>() : nullptr;
+    a.uu32 = fp32 && gwave == 0 ? c->uu32.as<float2>() : nullptr;
+    if (gwave > 0 && fp32) {
+      a.rec_p = c->rec.as<float4>();
+      a.rec_q = a.rec_p + rec_q / 16;
+    } else if (gwave > 0) {
+      a.occ_f = c->occ.as<double>();
+      a.occ_n = c->occ.as<double>() + (size_t)NQ * nw * occ_row;
     }
-    // q3 planes per launch of the wave kernel: one where the states alone fill
-    // the card (the plane's q-side tables then stay in the L2s), else as many
-    // as it takes for kFillBlocks workgroups; the sums of the planes of a
-    // launch are kept apart and added in plane order, so the results do not
-    // depend on the number
+    if (gwave > 0) {
+      a.band_range = c->ranges.as<float2>();
+      a.batch_lines = wave_batch_lines(N);
+      a.plane_groups = wave_plane_groups(N);
+    }
+    // Slabs of q3 planes per launch of the wave kernel: one where the states
+    // alone fill the card (the slab's q-side tables then stay in the L2s),
+    // else as many as it takes for kFillBlocks workgroups; the sums of the
+    // slabs of a launch are kept apart and added in order, so the results do
+    // not depend on the number
     constexpr int64_t kFillBlocks = 16384;
-    int planes = 1;
-    if (gwave > 0 && ns < kFillBlocks) {
-      const int64_t plane_bytes = ns * (8 * p->n_temps + 32);
-      const int64_t count_bytes = gr ? 8 * ns : 0;  // per plane and once more
-      planes = (int)std::min<int64_t>(N, (kFillBlocks + ns - 1) / ns);
-      if (p->mem_budget_bytes > 0) planes = (int)std::min<int64_t>(planes, (NQ * nw * 4 - count_bytes) / (plane_bytes + count_bytes));
-      planes = std::max(planes, 1);
-      if (planes > 1) {
-        EPH_HIP(c, c->part.ensure(plane_bytes * planes));
+    int slabs = 1, nslab = 0;
+    if (gwave > 0) {
+      a.slab_planes = wave_slab_planes(N, ns);
+      nslab = (N + a.slab_planes - 1) / a.slab_planes;
+    }
+    if (nslab > 1 && ns < kFillBlocks) {
+      const int64_t slab_bytes = ns * (8 * p->n_temps + 32);
+      const int64_t count_bytes = gr ? 8 * ns : 0;  // per slab and once more
+      slabs = (int)std::min<int64_t>(nslab, (kFillBlocks + ns - 1) / ns);
+      if (p->mem_budget_bytes > 0)  // what the plan has for band ranges and slab sums
+        slabs = (int)std::min<int64_t>(slabs, (NQ * nw * 4 - 8 * (int64_t)nw * N * a.plane_groups - count_bytes) /
+                                                  (slab_bytes + count_bytes));
+      slabs = std::max(slabs, 1);
+      if (slabs > 1) {
+        EPH_HIP(c, c->part.ensure(slab_bytes * slabs));
         a.part_tau = c->part.as<double>();
-        a.part_cnt = reinterpret_cast<int64_t *>(a.part_tau + (size_t)planes * p->n_temps * ns);
+        a.part_cnt = reinterpret_cast<int64_t *>(a.part_tau + (size_t)slabs * p->n_temps * ns);
       }
     }
     const int ncol = c->box.count() * nm * nw;
@@ -724,18 +746,18 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
       EPH_HIP(c, launch_zero(c->gcur.p, sizeof(int64_t) * (ns + 1), st));
       a.stidx = c->stidx.as<int32_t>();
       a.g_cursor = c->gcur.as<int64_t>();
-      if (planes > 1) {
-        EPH_HIP(c, c->gslot.ensure(sizeof(int64_t) * (planes + 1) * ns));
+      if (slabs > 1) {
+        EPH_HIP(c, c->gslot.ensure(sizeof(int64_t) * (slabs + 1) * ns));
         a.g_slot = c->gslot.as<int64_t>();
       }
       a.s_lo = a.s_base = 0;
       a.ns_launch = ns;
       a.X = nullptr;
-      for (int q3 = 0; q3 < N; q3 += planes) {
-        a.q3_lo = q3;
-        a.q3_hi = std::min(q3 + planes, N);
+      for (int j = 0; j < nslab; j += slabs) {
+        a.slab_lo = j;
+        a.slab_hi = std::min(j + slabs, nslab);
         EPH_HIP(c, launch_rates_wave(EPH_FP64, a, st, kCount));
-        if (planes > 1) EPH_HIP(c, launch_plane_counts(a, 1, st));
+        if (slabs > 1) EPH_HIP(c, launch_slab_counts(a, 1, st));
       }
       gam.reset(new eph_gamma());
       gam->ctx = c;
@@ -840,15 +862,15 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
         a.g_stride = spill ? stage_cap : gam->nnz;
       }
       if (gwave > 0) {
-        for (int q3 = 0; q3 < N; q3 += planes) {
-          a.q3_lo = q3;
-          a.q3_hi = std::min(q3 + planes, N);
-          if (gr && planes > 1) {  // where each plane's rows start
+        for (int j = 0; j < nslab; j += slabs) {
+          a.slab_lo = j;
+          a.slab_hi = std::min(j + slabs, nslab);
+          if (gr && slabs > 1) {  // where each slab's rows start
             EPH_HIP(c, launch_rates_wave(EPH_FP64, a, st, kCount));
-            EPH_HIP(c, launch_plane_counts(a, 0, st));
+            EPH_HIP(c, launch_slab_counts(a, 0, st));
           }
           EPH_HIP(c, launch_rates_wave(p->precision, a, st, gr ? kEmit : kRates));
-          if (planes > 1) EPH_HIP(c, launch_add_planes(a, st));
+          if (slabs > 1) EPH_HIP(c, launch_add_slabs(a, st));
           c->launches[1]++;
         }
       } else
@@ -1283,7 +1305,7 @@ int32_t eph_carrier_density(eph_ctx *c, int32_t grid, int32_t band_lo, int32_t b
   for (int t = 0; t < n_temps; t++) hk[t] = U.kb_evk * temps_K[t];
   EPH_HIP(c, hipMemcpyAsync(kts, hk, sizeof(hk), hipMemcpyHostToDevice, st));
   const double pref = 2.0 / ((double)NQ * c->volume * 1e-30);
-  EPH_HIP(c, launch_density(NQ, nw, c->eps.as<double>(), band_lo, band_hi, mu_eV, n_temps, kts, pref, part, nblk,
+  EPH_HIP(c, launch_density(N, nw, c->eps.as<double>(), band_lo, band_hi, mu_eV, n_temps, kts, pref, part, nblk,
                             outd, st));
   double ho[EPH_MAX_TEMPS];
   EPH_HIP(c, hipMemcpyAsync(ho, outd, sizeof(ho), hipMemcpyDeviceToHost, st));

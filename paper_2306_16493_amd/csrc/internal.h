@@ -53,6 +53,14 @@ struct DevBuf {
   T *as() const { return static_cast<T *>(p); }
 };
 
+// Grid tables with several components per point (bands, eigenvector elements,
+// modes, mode-matrix elements) are kept by i3 plane, each component of a
+// plane contiguous over its N^2 points, so that neighbouring points are read
+// together: element (k, c) of nc components is at plane_at(k, c, nc, N^2).
+__host__ __device__ inline int64_t plane_at(int64_t k, int c, int nc, int64_t n2) {
+  return ((k / n2) * nc + c) * n2 + k % n2;
+}
+
 struct RpBox {
   int lo[3];
   int n[3];
@@ -87,7 +95,7 @@ struct eph_ctx {
   eph::DevBuf tab;                      // e^{2 pi i m/N}, [N] double2
   eph::DevBuf eps, evec, vel, om, uu;   // grid tables
   eph::DevBuf evec32, uu32;             // FP32 copies for reduced forms
-  eph::DevBuf part;                     // per-plane sums of a launch of several planes
+  eph::DevBuf part;                     // sums of each slab of a launch of several
   eph::DevBuf cnt, offs, scan_tmp, subset;
   eph::DevBuf grp_start, grp_tmp;
   eph::DevBuf line_e, line_key;         // energy-sorted p-lines
@@ -99,12 +107,13 @@ struct eph_ctx {
   eph::DevBuf state_cnt;                // per-state int64 counts
   eph::DevBuf stidx;                    // [N^3][nw] state index table (transition rates)
   eph::DevBuf gcur;                     // per-state transition-rate counts / cursors
-  eph::DevBuf gslot;                    // the same per plane of a launch
+  eph::DevBuf gslot;                    // the same per slab of a launch
   eph::DevBuf gstage_col, gstage_val;   // staging of spilled transition rates
   eph::DevBuf bte_f;                    // F0, F, F' of the iteration
   eph::DevBuf kb_g;                     // G_q of a q batch (k-batch order)
   eph::DevBuf occ;                      // Fermi and Bose factor tables
-  eph::DevBuf occ32;                    // their FP32 copies (reduced-precision forms)
+  eph::DevBuf rec;                      // FP32 records of the wave kernel
+  eph::DevBuf ranges;                   // band energy ranges of its chunks
   // stage timing
   bool profiling = false;
   std::vector<hipEvent_t> ev;  // created on demand, reused across calls
@@ -141,8 +150,8 @@ namespace eph {
 
 // ---- launchers (each returns the launch error) ----
 // Bloch sum + Hermitian eigensolve on grid points [k0, k0+nk).
-//  mode 0 (electrons): eval[k][n], evec[k][m][i] = V_im, vel[k][n][3] (m/s)
-//  mode 1 (phonons):   eval[k][nu] = hbar w (eV), evec[k][nu][mu] = u_{mu nu}
+//  mode 0 (electrons): eval (k, n), evec (k, m n + i) = V_im, vel[k][n][3] (m/s)
+//  mode 1 (phonons):   eval (k, nu) = hbar w (eV), evec (k, nu n + mu) = u_{mu nu}
 //                      (A), zero for hbar w < omega_cut; counts excluded modes
 hipError_t launch_bloch_eig(int mode, int n, int N, int64_t k0, int64_t nk, int nr, const int *R,
                             const double *w, const double *Rcart, const double2 *M, const double2 *tab,
@@ -161,11 +170,11 @@ hipError_t launch_bloch_lines(int mode, int n, int N, const int *lo, const int *
                               unsigned long long *n_excluded, hipStream_t st);
 
 // State selection.  cnt/offs sized nklist+1.
-hipError_t launch_count_states(int64_t nklist, const int64_t *klist, int nw, const double *eps, int blo,
+hipError_t launch_count_states(int64_t nklist, const int64_t *klist, int N, int nw, const double *eps, int blo,
                                int bhi, double wlo, double whi, int64_t *cnt, hipStream_t st);
 hipError_t launch_scan(int64_t n, const int64_t *in, int64_t *out_excl, int64_t *tmp, hipStream_t st);
 size_t scan_tmp_elems(int64_t n);
-hipError_t launch_write_states(int64_t nklist, const int64_t *klist, int nw, const double *eps,
+hipError_t launch_write_states(int64_t nklist, const int64_t *klist, int N, int nw, const double *eps,
                                const double *vel, int blo, int bhi, double wlo, double whi,
                                const int64_t *offs, int32_t *sk, int32_t *sn, double *se, double *sv,
                                hipStream_t st);
@@ -198,6 +207,26 @@ hipError_t launch_xform_bf16x3(int64_t ns, const int32_t *sk, const int32_t *sn,
                                const int *re, int ncol, const void *wbf, void *abf, const double2 *evec,
                                const double2 *tab, float2 *X, hipStream_t st);
 
+// Most final-state lines (p2 of one p3 plane) per batch of the wave kernel:
+// the columns of one matrix product.
+constexpr int kWaveLines = 16;
+// FP32 tables of the wave kernel, one record per gather: of a final state
+// (p, m) the eigenvector row, energy and Fermi factors, of a q the mode
+// matrix [nu][mu], energies and Bose factors [nu][t]; stored by 16-byte
+// chunks (RatesArgs::rec_p, rec_q).
+template <int NW, int NT>
+struct alignas(16) PRec {
+  float2 v[NW];
+  double e;
+  float f[NT];
+};
+template <int NM, int NT>
+struct alignas(16) QRec {
+  float2 u[NM * NM];
+  double w[NM];
+  float n[NM * NT];
+};
+
 struct RatesArgs {
   int N, nw, nm, nt;
   RpBox box;
@@ -208,10 +237,11 @@ struct RatesArgs {
   const int64_t *gstart;           // [ng+1] absolute state indices
   int64_t s_base;                  // state index of X row 0
   const int32_t *sk, *sn;
-  const double *eps;               // [N^3][nw]
-  const double *om;                // [N^3][nm]
-  const double2 *evec;             // [N^3][nw][nw]
-  const double2 *uu;               // [N^3][nm][nm]
+  // grid tables by plane_at: energies (k, m), (q, nu) (inf below omega_cut for
+  // the wave kernel), eigenvectors (k, m nw + i),
+  // mode matrices (q, nu nm + mu)
+  const double *eps, *om;
+  const double2 *evec, *uu;
   const float2 *evec32, *uu32;
   const double *line_e;
   const uint16_t *line_key;
@@ -225,18 +255,22 @@ struct RatesArgs {
   // wave kernel
   int64_t *kv_counts;              // [ns_total][2]: (k,q) pairs, vertices
   int64_t s_lo, ns_launch;         // states s_lo .. s_lo + ns_launch - 1 of this launch
-  const double *occ_f;             // [N^3][nw][occ_stride(nt)] Fermi factors
-  const double *occ_n;             // [N^3][nm][occ_stride(nt)] Bose factors, 0 below omega_cut
-  const float *occ32_f, *occ32_n;  // FP32 copies of occ_f, occ_n (reduced-precision forms)
-  int q3_lo, q3_hi;                // q3 planes of this launch, one row of workgroups each
-  double *part_tau;                // [planes][nt][ns_total] sums of each plane of a launch of several, or
-                                   // nullptr: one plane, added to inv_tau
-  int64_t *part_cnt;               // [planes][ns_total][4], with part_tau
+  const double *occ_f;             // Fermi factors (k, m) and Bose factors (q, nu), 0 below omega_cut: by plane_at
+  const double *occ_n;             // for one temperature, else two components of two temperatures each
+  const float4 *rec_p, *rec_q;     // FP32 records in place of evec .. occ_n: 16-byte chunk c of PRec (k, m) at
+                                   // component m chunks + c, of QRec (q) at component c
+  const float2 *band_range;        // [N][plane_groups][nw] lowest and highest energy of each group of 16 p
+  int batch_lines, plane_groups;   // p-lines per batch; groups of a p3 plane, a batch's from its first p on
+  int slab_planes;                 // q3 planes per workgroup (a slab)
+  int slab_lo, slab_hi;            // slabs of this launch, one row of workgroups each
+  double *part_tau;                // [slabs][nt][ns_total] sums of each slab of a launch of several, or
+                                   // nullptr: one slab, added to inv_tau
+  int64_t *part_cnt;               // [slabs][ns_total][4], with part_tau
   // transition rates of the iterative BTE (wave kernel, FP64, count and emit modes)
   const int32_t *stidx;            // [N^3][nw] index of state (k, m) in the list, -1 if none
   int64_t *g_cursor;               // [ns_total] next position of each state (emit)
-  int64_t *g_slot;                 // [planes][ns_total] counts (count mode); offsets of the planes of a launch
-                                   // from g_cursor (emit); nullptr for one plane, which advances g_cursor
+  int64_t *g_slot;                 // [slabs][ns_total] counts (count mode); offsets of the slabs of a launch
+                                   // from g_cursor (emit); nullptr for one slab, which advances g_cursor
   int32_t *g_col;                  // emitted final-state indices, position - g_base
   double *g_val;                   // emitted values [t][g_stride], 1/s
   int64_t g_stride;                // temperature stride of g_val
@@ -245,20 +279,20 @@ struct RatesArgs {
 // rate-kernel modes (wave kernel)
 constexpr int kRates = 0, kCount = 1, kEmit = 2;
 hipError_t launch_rates(int precision, const RatesArgs &a, hipStream_t st);
-// Occupation rows of the wave kernel: one value for one temperature, else
-// padded for vector loads.
-inline int occ_stride(int nt) { return nt == 1 ? 1 : EPH_MAX_TEMPS; }
+// Temperatures per element of the wave kernel's occupation tables: one, or
+// two pairs for two to four.
+__host__ __device__ inline int occ_stride(int nt) { return nt == 1 ? 1 : EPH_MAX_TEMPS; }
 // Wave rate kernel; rates_wave_group gives the states per group that the
 // state batches and the transition-rate staging count with (0 when the shape
 // is not served and launch_rates must be used).
 int rates_wave_group(int nw, int nm, RpBox box, int N, int precision);
 hipError_t launch_rates_wave(int precision, const RatesArgs &a, hipStream_t st, int mode = kRates);
-// Adds the planes of a launch (a.part_tau, a.part_cnt) to a.inv_tau and
-// a.st_counts in plane order, and with a.g_slot moves a.g_cursor past them.
-hipError_t launch_add_planes(const RatesArgs &a, hipStream_t st);
+// Adds the slabs of a launch (a.part_tau, a.part_cnt) to a.inv_tau and
+// a.st_counts in order, and with a.g_slot moves a.g_cursor past them.
+hipError_t launch_add_slabs(const RatesArgs &a, hipStream_t st);
 // Counts of a counting launch (a.g_slot): total 1 adds them to a.g_cursor,
-// 0 turns them into offsets and leaves the sums in row planes.
-hipError_t launch_plane_counts(const RatesArgs &a, int total, hipStream_t st);
+// 0 turns them into offsets and leaves the sums in the row after the slabs.
+hipError_t launch_slab_counts(const RatesArgs &a, int total, hipStream_t st);
 // k-batch order of the vertex (k_kbatch.hip): step 1 forms G_q for a batch
 // of q, step 2 runs one wave per state over that batch.
 struct KBatchArgs {
@@ -276,11 +310,12 @@ struct KBatchArgs {
 hipError_t launch_kbatch_step1(int64_t q0, int nb, int N, RpBox box, int nre, int nm, int nw, int ncol,
                                const double2 *wt, const double2 *uu, const double2 *tab, double2 *Gq, hipStream_t st);
 hipError_t launch_kbatch_step2(const KBatchArgs &a, hipStream_t st);
-// Occupation tables with rows of `stride` temperatures (zeros past nt):
-// occ_f[k][n][t] = 1/(exp((eps-mu)/kT_t)+1),
-// occ_n[q][nu][t] = 1/expm1(hbar w/kT_t) (0 when hbar w < wcut).
-hipError_t launch_occupations(int64_t nq, int nw, int nm, const double *eps, const double *om, double mu,
-                              int nt, const double *kts_host, double wcut, int stride, double *occ_f, double *occ_n,
+// Occupation tables, for every element of eps and om (zeros past nt):
+// f = 1/(exp((eps-mu)/kT_t)+1), N = 1/expm1(hbar w/kT_t) (0 when hbar w < wcut).
+// rows true: EPH_MAX_TEMPS values per element (k-batch kernels); else as the
+// wave kernel reads them.
+hipError_t launch_occupations(int N, int nw, int nm, const double *eps, const double *om, double mu, int nt,
+                              const double *kts_host, double wcut, bool rows, double *occ_f, double *occ_n,
                               hipStream_t st);
 
 // sigma partial sums per block, then out[T*9 + ab] = pref * sum of partials
@@ -300,11 +335,22 @@ hipError_t launch_bte_step(int64_t r0, int64_t r1, const int64_t *row_start, int
 hipError_t launch_check_rows(int64_t ns, const int64_t *cursor, const int64_t *row_start, unsigned long long *bad,
                              hipStream_t st);
 // out[t] = pref * sum_{k, blo <= n <= bhi} f(eps_nk) (partials: [nblk][EPH_MAX_TEMPS])
-hipError_t launch_density(int64_t nk, int nw, const double *eps, int blo, int bhi, double mu, int nt,
+hipError_t launch_density(int N, int nw, const double *eps, int blo, int bhi, double mu, int nt,
                           const double *kts, double pref, double *partials, int nblk, double *out, hipStream_t st);
+// Wave kernel tables: the energy range of every band in every group of 16 p
+// (rounded outwards), and the FP32 records (factors as launch_occupations).
+int wave_batch_lines(int N);
+int wave_plane_groups(int N);
+int wave_slab_planes(int N, int64_t ns);  // q3 planes per workgroup
+hipError_t launch_band_ranges(int N, int nw, const double *eps, float2 *out, hipStream_t st);
+size_t wave_rec_bytes(int nw, int nm, int nt, int64_t nq, size_t *q_offset);
+hipError_t launch_wave_records(int N, int nw, int nm, const double *eps, const double *om, const double2 *evec,
+                               const double2 *uu, double mu, int nt, const double *kts_host, double wcut, void *out,
+                               hipStream_t st);
 int rates_group_max(int nw, int nm);
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t st);
-hipError_t launch_max_nonneg(int64_t n, const double *x, unsigned long long *out, hipStream_t st);
+// also sets the elements below cut to +inf
+hipError_t launch_max_nonneg(int64_t n, double *x, double cut, unsigned long long *out, hipStream_t st);
 // out[1..3] += sum n_q_valid, sum n_terms, #(inv_tau0 == 0); with kv_counts
 // also out[0] += (k,q) pairs and out[4] += vertices
 hipError_t launch_summarize(int64_t ns, const int64_t *st_counts, const int64_t *kv_counts, const double *inv_tau0,

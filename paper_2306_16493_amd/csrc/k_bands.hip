@@ -49,6 +49,7 @@ struct Rot {
 // Outputs of the eigensolve, shared by both Bloch-sum forms.
 struct EigOut {
   int mode, n;
+  int64_t n2;  // points per plane
   const double *mode_mass;
   double cph, omega_cut, vel_unit;
   double *eval;
@@ -165,12 +166,12 @@ __device__ __forceinline__ void eig_store(const EigOut &o, bool live, int64_t kl
       const int64_t kk = kl;
       double2 v = sV[base + i * NP + j];
       if (mode == 0) {
-        if (i == 0) o.eval[kk * n + rank] = wj;
-        o.evec[(kk * n + rank) * n + i] = v;
+        if (i == 0) o.eval[plane_at(kk, rank, n, o.n2)] = wj;
+        o.evec[plane_at(kk, rank * n + i, n * n, o.n2)] = v;
       } else {
         double hw = sqrt(o.cph * fmax(wj, 0.0));
         if (i == 0) {
-          o.eval[kk * n + rank] = hw;
+          o.eval[plane_at(kk, rank, n, o.n2)] = hw;
           if (hw < o.omega_cut) atomicAdd(o.n_excluded, 1ull);
         }
         double2 u = make_double2(0.0, 0.0);
@@ -178,7 +179,7 @@ __device__ __forceinline__ void eig_store(const EigOut &o, bool live, int64_t kl
           double f = sqrt(o.cph / (2.0 * o.mode_mass[i] * hw));
           u = make_double2(v.x * f, v.y * f);
         }
-        o.evec[(kk * n + rank) * n + i] = u;  // evec[q][nu][mu] = u_{mu nu}
+        o.evec[plane_at(kk, rank * n + i, n * n, o.n2)] = u;  // u_{mu nu} at nu n + mu
       }
     }
     if (mode == 0) {
@@ -403,7 +404,7 @@ hipError_t launch_bloch_eig(int mode, int n, int N, int64_t k0, int64_t nk, int 
                             double *eval, double2 *evec, double *vel, unsigned long long *n_excluded,
                             hipStream_t st) {
   if (nk <= 0) return hipSuccess;
-  const EigOut o{mode, n, mode_mass, cph, omega_cut, vel_unit, eval, evec, vel, n_excluded};
+  const EigOut o{mode, n, (int64_t)N * N, mode_mass, cph, omega_cut, vel_unit, eval, evec, vel, n_excluded};
   int NP = n <= 1 ? 1 : n <= 2 ? 2 : n <= 4 ? 4 : 8;
   int mpw = 64 / (NP * NP);
   int64_t ngroups = (nk + mpw - 1) / mpw;
@@ -424,7 +425,7 @@ hipError_t launch_bloch_lines(int mode, int n, int N, const int *lo, const int *
                               const double2 *Mb, const double2 *tab, const double *mode_mass, double cph,
                               double omega_cut, double vel_unit, double *eval, double2 *evec, double *vel,
                               unsigned long long *n_excluded, hipStream_t st) {
-  const EigOut o{mode, n, mode_mass, cph, omega_cut, vel_unit, eval, evec, vel, n_excluded};
+  const EigOut o{mode, n, (int64_t)N * N, mode_mass, cph, omega_cut, vel_unit, eval, evec, vel, n_excluded};
   if (nb[0] > kBoxMaxR1) return hipErrorInvalidValue;
   BoxArgs bx;
   for (int a = 0; a < 3; a++) {

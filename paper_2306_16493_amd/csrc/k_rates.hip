@@ -80,6 +80,7 @@ __global__ __launch_bounds__(256) void rates_kernel(RatesArgs a) {
   constexpr int C = NW * NM;
   extern __shared__ __align__(16) unsigned char smem[];
   const int N = a.N;
+  const int64_t NN = (int64_t)N * N;
   const int n1 = a.box.n[0], n2 = a.box.n[1], n3 = a.box.n[2];
   const int lo1 = a.box.lo[0], lo2 = a.box.lo[1], lo3 = a.box.lo[2];
   const int nbox = n1 * n2 * n3;
@@ -134,7 +135,7 @@ __global__ __launch_bounds__(256) void rates_kernel(RatesArgs a) {
     if (tid < ST) {
       int64_t k = a.sk[s0 + tid];
       sK1[tid] = (int)(k % N);
-      sEps[tid] = a.eps[k * NW + a.sn[s0 + tid]];
+      sEps[tid] = a.eps[plane_at(k, a.sn[s0 + tid], NW, NN)];
     }
     if (tid < SMAX) {
       sNq[tid] = 0;
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(256) void rates_kernel(RatesArgs a) {
         unsigned vp = 0, vm = 0;
 #pragma unroll
         for (int nu = 0; nu < NM; nu++) {
-          om[nu] = a.om[qidx * NM + nu];
+          om[nu] = a.om[plane_at(qidx, nu, NM, NN)];
           bool ok = om[nu] >= a.wcut;
           vp |= (ok && fabs(es + om[nu] - ep) <= cut) ? (1u << nu) : 0u;
           vm |= (ok && fabs(es - om[nu] - ep) <= cut) ? (1u << nu) : 0u;
@@ -236,9 +237,9 @@ __global__ __launch_bounds__(256) void rates_kernel(RatesArgs a) {
 #pragma unroll
         for (int i = 0; i < NW; i++) {
           if constexpr (sizeof(T) == 8) {
-            vrow[i] = a.evec[(pidx * NW + m) * NW + i];
+            vrow[i] = a.evec[plane_at(pidx, m * NW + i, NW * NW, NN)];
           } else {
-            vrow[i] = a.evec32[(pidx * NW + m) * NW + i];
+            vrow[i] = a.evec32[plane_at(pidx, m * NW + i, NW * NW, NN)];
           }
         }
         T wr[NM], wi[NM];
@@ -274,9 +275,9 @@ __global__ __launch_bounds__(256) void rates_kernel(RatesArgs a) {
           for (int mu = 0; mu < NM; mu++) {
             C2 u;
             if constexpr (sizeof(T) == 8) {
-              u = a.uu[(qidx * NM + nu) * NM + mu];
+              u = a.uu[plane_at(qidx, nu * NM + mu, NM * NM, NN)];
             } else {
-              u = a.uu32[(qidx * NM + nu) * NM + mu];
+              u = a.uu32[plane_at(qidx, nu * NM + mu, NM * NM, NN)];
             }
             gr += wr[mu] * u.x - wi[mu] * u.y;
             gi += wr[mu] * u.y + wi[mu] * u.x;

@@ -1,6 +1,6 @@
 // SERTA scattering rates, wave form: shape selection and dispatch to the
 // per-(precision, modes) instances of the kernel in rates_wave.h, and the sums
-// over the planes of a launch.
+// over the slabs of a launch.
 #include "internal.h"
 
 namespace eph {
@@ -19,31 +19,31 @@ extern template hipError_t dispatch_nm<double, 6, kEmit>(const RatesArgs &, hipS
 
 namespace {
 
-__global__ void add_planes_kernel(RatesArgs a) {
+__global__ void add_slabs_kernel(RatesArgs a) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= a.ns_launch) return;
   const int64_t s = a.s_lo + i;
-  const int np = a.q3_hi - a.q3_lo;
+  const int np = a.slab_hi - a.slab_lo;
   for (int t = 0; t < a.nt; t++) {
     double *dst = a.inv_tau + (int64_t)t * a.ns_total + s;
-    double v = a.q3_lo == 0 ? 0.0 : *dst;
+    double v = a.slab_lo == 0 ? 0.0 : *dst;
     for (int j = 0; j < np; j++) v += a.part_tau[((int64_t)j * a.nt + t) * a.ns_total + s];
     *dst = v;
   }
   for (int c = 0; c < 4; c++) {
     int64_t *dst = (c < 2 ? a.st_counts : a.kv_counts - 2) + 2 * s + c;
-    int64_t v = a.q3_lo == 0 ? 0 : *dst;
+    int64_t v = a.slab_lo == 0 ? 0 : *dst;
     for (int j = 0; j < np; j++) v += a.part_cnt[((int64_t)j * a.ns_total + s) * 4 + c];
     *dst = v;
   }
   if (a.g_slot) a.g_cursor[s] += a.g_slot[(int64_t)np * a.ns_total + s];
 }
 
-__global__ void plane_counts_kernel(RatesArgs a, int total) {
+__global__ void slab_counts_kernel(RatesArgs a, int total) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= a.ns_launch) return;
   const int64_t s = a.s_lo + i;
-  const int np = a.q3_hi - a.q3_lo;
+  const int np = a.slab_hi - a.slab_lo;
   int64_t run = 0;
   for (int j = 0; j < np; j++) {
     int64_t *p = a.g_slot + (int64_t)j * a.ns_total + s;
@@ -57,15 +57,15 @@ __global__ void plane_counts_kernel(RatesArgs a, int total) {
 
 }  // namespace
 
-hipError_t launch_add_planes(const RatesArgs &a, hipStream_t st) {
+hipError_t launch_add_slabs(const RatesArgs &a, hipStream_t st) {
   if (a.ns_launch <= 0) return hipSuccess;
-  hipLaunchKernelGGL(add_planes_kernel, dim3((unsigned)((a.ns_launch + 255) / 256)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(add_slabs_kernel, dim3((unsigned)((a.ns_launch + 255) / 256)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
-hipError_t launch_plane_counts(const RatesArgs &a, int total, hipStream_t st) {
+hipError_t launch_slab_counts(const RatesArgs &a, int total, hipStream_t st) {
   if (a.ns_launch <= 0) return hipSuccess;
-  hipLaunchKernelGGL(plane_counts_kernel, dim3((unsigned)((a.ns_launch + 255) / 256)), dim3(256), 0, st, a, total);
+  hipLaunchKernelGGL(slab_counts_kernel, dim3((unsigned)((a.ns_launch + 255) / 256)), dim3(256), 0, st, a, total);
   return hipGetLastError();
 }
 

@@ -81,7 +81,7 @@ __global__ void sigma_final_kernel(int nblk, const double *__restrict__ partials
 }
 
 // sum over k of f(eps_nk) for band_lo <= n <= band_hi, per temperature
-__global__ __launch_bounds__(kSigThreads) void density_kernel(int64_t nk, int nw, const double *__restrict__ eps,
+__global__ __launch_bounds__(kSigThreads) void density_kernel(int64_t nk, int64_t n2, int nw, const double *__restrict__ eps,
                                                                int blo, int bhi, double mu, int nt,
                                                                const double *__restrict__ kts,
                                                                double *__restrict__ partials, int64_t chunk) {
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kSigThreads) void density_kernel(int64_t nk, int nw
   for (int t = 0; t < EPH_MAX_TEMPS; t++) s[t] = c[t] = 0.0;
   for (int64_t k = b0 + threadIdx.x; k < b1; k += kSigThreads)
     for (int n = blo; n <= bhi; n++) {
-      const double e = eps[k * nw + n];
+      const double e = eps[plane_at(k, n, nw, n2)];
       for (int t = 0; t < EPH_MAX_TEMPS; t++) {
         if (t >= nt) break;
         neumaier(s[t], c[t], 1.0 / (exp((e - mu) / kts[t]) + 1.0));
@@ -143,11 +143,12 @@ hipError_t launch_sigma(int64_t ns, const double *e, const double *v, const doub
   return hipGetLastError();
 }
 
-hipError_t launch_density(int64_t nk, int nw, const double *eps, int blo, int bhi, double mu, int nt,
+hipError_t launch_density(int N, int nw, const double *eps, int blo, int bhi, double mu, int nt,
                           const double *kts, double pref, double *partials, int nblk, double *out, hipStream_t st) {
+  const int64_t nk = (int64_t)N * N * N;
   int64_t chunk = (nk + nblk - 1) / nblk;
   if (chunk < 1) chunk = 1;
-  hipLaunchKernelGGL(density_kernel, dim3(nblk), dim3(kSigThreads), 0, st, nk, nw, eps, blo, bhi, mu, nt, kts,
+  hipLaunchKernelGGL(density_kernel, dim3(nblk), dim3(kSigThreads), 0, st, nk, (int64_t)N * N, nw, eps, blo, bhi, mu, nt, kts,
                      partials, chunk);
   hipLaunchKernelGGL(density_final_kernel, dim3(1), dim3(64), 0, st, nblk, partials, pref, out);
   return hipGetLastError();

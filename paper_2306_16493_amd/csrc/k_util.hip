@@ -1,6 +1,8 @@
 // Small device helpers: fills, a max reduction and the per-call count
 // summary (gfx950).  Fills use a kernel rather than hipMemsetAsync so the
 // library never records memset nodes if a caller captures its stream.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace eph {
@@ -11,12 +13,14 @@ __global__ void zero_kernel(int64_t n64, unsigned long long *__restrict__ p) {
   if (i < n64) p[i] = 0ull;
 }
 
-// max of non-negative doubles through their (monotone) bit patterns
-__global__ void max_nonneg_kernel(int64_t n, const double *__restrict__ x, unsigned long long *__restrict__ out) {
+// max of non-negative doubles through their (monotone) bit patterns; elements
+// below cut are set to +inf
+__global__ void max_nonneg_kernel(int64_t n, double *__restrict__ x, double cut, unsigned long long *__restrict__ out) {
   __shared__ unsigned long long red[256];
   unsigned long long m = 0ull;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    double v = x[i];
+    const double v = x[i];
+    if (v < cut) x[i] = __builtin_huge_val();
     if (v > 0.0) {
       unsigned long long b = (unsigned long long)__double_as_longlong(v);
       m = b > m ? b : m;
@@ -61,33 +65,179 @@ struct Kts {
   double v[EPH_MAX_TEMPS];
 };
 
-__global__ void occupation_kernel(int64_t nq, int nw, int nm, const double *__restrict__ eps,
-                                  const double *__restrict__ om, double mu, int nt, Kts kts, double wcut, int stride,
+// Element i = (plane, component, point) of a table whose planes hold n2 points
+// per component: its two pairs of temperatures in the wave kernel's layout.
+__device__ __forceinline__ int64_t pair_at(int64_t i, int64_t n2, int t) {
+  return (((i / n2) * 2 + t / 2) * n2 + i % n2) * 2 + t % 2;
+}
+
+__global__ void occupation_kernel(int64_t nq, int64_t n2, int nw, int nm, const double *__restrict__ eps,
+                                  const double *__restrict__ om, double mu, int nt, Kts kts, double wcut, int rows,
                                   double *__restrict__ occ_f, double *__restrict__ occ_n) {
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  // rows of `stride` entries (zeros past nt)
-  if (i < nq * nw) {
-    const double e = eps[i];
-    for (int t = 0; t < stride; t++)
-      occ_f[i * stride + t] = t < nt ? 1.0 / (exp((e - mu) / kts.v[t]) + 1.0) : 0.0;
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int nv = rows ? EPH_MAX_TEMPS : occ_stride(nt);
+  for (int t = 0; t < nv; t++) {
+    const int64_t at = rows ? i * EPH_MAX_TEMPS + t : nv == 1 ? i : pair_at(i, n2, t);
+    if (i < nq * nw) occ_f[at] = t < nt ? 1.0 / (exp((eps[i] - mu) / kts.v[t]) + 1.0) : 0.0;
+    if (i < nq * nm) {
+      const double w = om[i];
+      occ_n[at] = (t < nt && w >= wcut && w > 0.0) ? 1.0 / expm1(w / kts.v[t]) : 0.0;
+    }
   }
-  if (i < nq * nm) {
-    const double w = om[i];
-    for (int t = 0; t < stride; t++)
-      occ_n[i * stride + t] = (t < nt && w >= wcut && w > 0.0) ? 1.0 / expm1(w / kts.v[t]) : 0.0;
+}
+
+// 16 lanes per group of 16 p of a p3 plane (groups counted from the first p
+// of each batch of lines): the range of every band's energies.
+__global__ __launch_bounds__(256) void band_range_kernel(int N, int nw, int nlb, int plane_groups,
+                                                         const double *__restrict__ eps, float2 *__restrict__ out) {
+  const int64_t g = (blockIdx.x * (int64_t)256 + threadIdx.x) >> 4;
+  if (g >= (int64_t)N * plane_groups) return;  // whole groups
+  const int lane = threadIdx.x & 15;
+  const int p3 = (int)(g / plane_groups), c = (int)(g - (int64_t)p3 * plane_groups);
+  const int gb = (nlb * N + 15) >> 4, b = c / gb;
+  const int ne = min(nlb, N - b * nlb) * N;
+  const int64_t n2 = (int64_t)N * N, p = (int64_t)b * nlb * N + min(16 * (c - b * gb) + lane, ne - 1);
+  for (int m = 0; m < nw; m++) {
+    const double e = eps[(p3 * nw + m) * n2 + p];
+    double lo = e, hi = e;
+    for (int d = 8; d >= 1; d >>= 1) {
+      lo = fmin(lo, __shfl_xor(lo, d, 16));
+      hi = fmax(hi, __shfl_xor(hi, d, 16));
+    }
+    if (lane == 0) out[g * nw + m] = make_float2(__double2float_rd(lo), __double2float_ru(hi));
   }
+}
+
+// Record r of point x, component c0 on, into the chunk layout.
+template <class R>
+__device__ __forceinline__ void put_chunks(const R &r, float4 *__restrict__ out, int64_t plane_comp, int64_t n2, int64_t x) {
+  const float4 *src = reinterpret_cast<const float4 *>(&r);
+#pragma unroll
+  for (int c = 0; c < (int)(sizeof(R) / 16); c++) out[(plane_comp + c) * n2 + x] = src[c];
+}
+
+template <int NW, int NT>
+__global__ void p_record_kernel(int64_t n, int64_t n2, const double *__restrict__ eps,
+                                const double2 *__restrict__ evec, double mu, int nt, Kts kts, float4 *__restrict__ out) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;  // element of eps
+  if (i >= n) return;
+  const int64_t pm = i / n2, x = i % n2;  // plane and band
+  PRec<NW, NT> r = {};
+#pragma unroll
+  for (int j = 0; j < NW; j++) {
+    const double2 v = evec[(pm * NW + j) * n2 + x];
+    r.v[j] = make_float2((float)v.x, (float)v.y);
+  }
+  r.e = eps[i];
+#pragma unroll
+  for (int t = 0; t < NT; t++) r.f[t] = t < nt ? (float)(1.0 / (exp((r.e - mu) / kts.v[t]) + 1.0)) : 0.f;
+  put_chunks(r, out, pm * (int64_t)(sizeof(r) / 16), n2, x);
+}
+
+template <int NM, int NT>
+__global__ void q_record_kernel(int64_t n, int64_t n2, const double *__restrict__ om, const double2 *__restrict__ uu,
+                                int nt, Kts kts, double wcut, float4 *__restrict__ out) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;  // q
+  if (i >= n) return;
+  const int64_t pl = i / n2, x = i % n2;
+  QRec<NM, NT> r = {};
+#pragma unroll
+  for (int e = 0; e < NM * NM; e++) {
+    const double2 u = uu[(pl * (NM * NM) + e) * n2 + x];
+    r.u[e] = make_float2((float)u.x, (float)u.y);
+  }
+#pragma unroll
+  for (int nu = 0; nu < NM; nu++) {
+    const double w = om[(pl * NM + nu) * n2 + x];
+    r.w[nu] = w >= wcut ? w : __builtin_huge_val();
+#pragma unroll
+    for (int t = 0; t < NT; t++)
+      r.n[nu * NT + t] = (t < nt && w >= wcut && w > 0.0) ? (float)(1.0 / expm1(w / kts.v[t])) : 0.f;
+  }
+  put_chunks(r, out, pl * (int64_t)(sizeof(r) / 16), n2, x);
+}
+
+template <int NM, int NT>
+size_t rec_sizes(int nw, int64_t nq, size_t *q_offset) {
+  const size_t p = nw == 1   ? sizeof(PRec<1, NT>)
+                   : nw == 2 ? sizeof(PRec<2, NT>)
+                   : nw == 4 ? sizeof(PRec<4, NT>)
+                             : sizeof(PRec<8, NT>);
+  *q_offset = p * nw * nq;
+  return *q_offset + sizeof(QRec<NM, NT>) * nq;
+}
+
+template <int NT>
+hipError_t wave_records(int N, int nw, int nm, const double *eps, const double *om, const double2 *evec,
+                        const double2 *uu, double mu, int nt, const Kts &k, double wcut, void *out, hipStream_t st) {
+  const int64_t n2 = (int64_t)N * N, nq = n2 * N;
+  size_t qo;
+  (void)wave_rec_bytes(nw, nm, nt, nq, &qo);
+  const dim3 gp((unsigned)((nq * nw + 255) / 256)), gq((unsigned)((nq + 255) / 256));
+  float4 *p = static_cast<float4 *>(out), *q = p + qo / 16;
+#define EPH_PREC(NW_) \
+  if (nw == NW_) hipLaunchKernelGGL((p_record_kernel<NW_, NT>), gp, dim3(256), 0, st, nq * nw, n2, eps, evec, mu, nt, k, p);
+  EPH_PREC(1)
+  EPH_PREC(2)
+  EPH_PREC(4)
+  EPH_PREC(8)
+#undef EPH_PREC
+  if (nm == 3) hipLaunchKernelGGL((q_record_kernel<3, NT>), gq, dim3(256), 0, st, nq, n2, om, uu, nt, k, wcut, q);
+  else hipLaunchKernelGGL((q_record_kernel<6, NT>), gq, dim3(256), 0, st, nq, n2, om, uu, nt, k, wcut, q);
+  return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_occupations(int64_t nq, int nw, int nm, const double *eps, const double *om, double mu, int nt,
-                              const double *kts_host, double wcut, int stride, double *occ_f, double *occ_n,
+int wave_batch_lines(int N) {
+  const int nb = (N + kWaveLines - 1) / kWaveLines;
+  return (N + nb - 1) / nb;  // evened out over the batches
+}
+
+// Planes per workgroup: enough for about 20000 q, so that what a workgroup
+// does once (tables, reductions) stays small beside them, while the states
+// still make 8192 workgroups.  More q per workgroup cost more than they save,
+// the q-side tables of the planes in flight no longer fit the L2s (Al 71^3,
+// FP32: 449 ms at 20000 q, 459 at one plane, 490 at 80000).
+int wave_slab_planes(int N, int64_t ns) {
+  const int64_t n2 = (int64_t)N * N, p = std::min(((int64_t)20000 + n2 / 2) / n2, ns * N / 8192);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(p, N));
+}
+
+int wave_plane_groups(int N) {
+  const int nlb = wave_batch_lines(N), full = N / nlb, rest = N - full * nlb;
+  return full * ((nlb * N + 15) / 16) + (rest * N + 15) / 16;
+}
+
+hipError_t launch_band_ranges(int N, int nw, const double *eps, float2 *out, hipStream_t st) {
+  const int pc = wave_plane_groups(N);
+  hipLaunchKernelGGL(band_range_kernel, dim3((unsigned)(((int64_t)N * pc + 15) / 16)), dim3(256), 0, st, N, nw,
+                     wave_batch_lines(N), pc, eps, out);
+  return hipGetLastError();
+}
+
+size_t wave_rec_bytes(int nw, int nm, int nt, int64_t nq, size_t *q_offset) {
+  if (occ_stride(nt) == 1) return nm == 3 ? rec_sizes<3, 1>(nw, nq, q_offset) : rec_sizes<6, 1>(nw, nq, q_offset);
+  return nm == 3 ? rec_sizes<3, EPH_MAX_TEMPS>(nw, nq, q_offset) : rec_sizes<6, EPH_MAX_TEMPS>(nw, nq, q_offset);
+}
+
+hipError_t launch_wave_records(int N, int nw, int nm, const double *eps, const double *om, const double2 *evec,
+                               const double2 *uu, double mu, int nt, const double *kts_host, double wcut, void *out,
+                               hipStream_t st) {
+  Kts k;
+  for (int t = 0; t < EPH_MAX_TEMPS; t++) k.v[t] = t < nt ? kts_host[t] : 1.0;
+  if (occ_stride(nt) == 1) return wave_records<1>(N, nw, nm, eps, om, evec, uu, mu, nt, k, wcut, out, st);
+  return wave_records<EPH_MAX_TEMPS>(N, nw, nm, eps, om, evec, uu, mu, nt, k, wcut, out, st);
+}
+
+hipError_t launch_occupations(int N, int nw, int nm, const double *eps, const double *om, double mu, int nt,
+                              const double *kts_host, double wcut, bool rows, double *occ_f, double *occ_n,
                               hipStream_t st) {
   Kts k;
   for (int t = 0; t < EPH_MAX_TEMPS; t++) k.v[t] = t < nt ? kts_host[t] : 1.0;
-  const int64_t n = nq * (nw > nm ? nw : nm);
-  hipLaunchKernelGGL(occupation_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, nq, nw, nm, eps, om,
-                     mu, nt, k, wcut, stride, occ_f, occ_n);
+  const int64_t n2 = (int64_t)N * N, nq = n2 * N, n = nq * (nw > nm ? nw : nm);
+  hipLaunchKernelGGL(occupation_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, nq, n2, nw, nm, eps, om,
+                     mu, nt, k, wcut, rows ? 1 : 0, occ_f, occ_n);
   return hipGetLastError();
 }
 
@@ -99,11 +249,11 @@ hipError_t launch_zero(void *p, size_t bytes, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_max_nonneg(int64_t n, const double *x, unsigned long long *out, hipStream_t st) {
+hipError_t launch_max_nonneg(int64_t n, double *x, double cut, unsigned long long *out, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   int64_t blocks = (n + 255) / 256;
   if (blocks > 4096) blocks = 4096;
-  hipLaunchKernelGGL(max_nonneg_kernel, dim3((unsigned)blocks), dim3(256), 0, st, n, x, out);
+  hipLaunchKernelGGL(max_nonneg_kernel, dim3((unsigned)blocks), dim3(256), 0, st, n, x, cut, out);
   return hipGetLastError();
 }
 

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void xform_kernel(int64_t ns, const int32_t *_
         int64_t k1 = k % N, k2 = (k / N) % N, k3 = k / ((int64_t)N * N);
         int64_t ph = (k1 * re[3 * r] + k2 * re[3 * r + 1] + k3 * re[3 * r + 2]) % N;
         if (ph < 0) ph += N;
-        v = cmul(tab[ph], evec[(k * nw + n) * nw + j]);
+        v = cmul(tab[ph], evec[plane_at(k, n * nw + j, nw * nw, (int64_t)N * N)]);
       }
       sB[sl][kl] = mk<T>((T)v.x, (T)v.y);
     }

@@ -61,7 +61,7 @@ __global__ void state_operand_kernel(int64_t ns, const int32_t *__restrict__ sk,
   // phase index (k.Re mod N) in 32-bit integers: |k_i re_i| < 2^31
   int ph = (k1 * re[3 * ir] % N + k2 * re[3 * ir + 1] % N + k3 * re[3 * ir + 2] % N) % N;
   ph += ph < 0 ? N : 0;
-  const double2 p = tab[ph], e = evec[((int64_t)k * nw + n) * nw + j];
+  const double2 p = tab[ph], e = evec[plane_at(k, n * nw + j, nw * nw, (int64_t)N * N)];
   __bf16 h, l;
   split_bf16((float)(p.x * e.x - p.y * e.y), h, l);
   rh[kk] = h;

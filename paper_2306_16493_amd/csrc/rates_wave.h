@@ -6,25 +6,42 @@
 // Same arithmetic as the general form (separable Rp box: Y per q3, Z per
 // q-line, G per q; vertex contracted onto the final band m first, then onto
 // the modes; sieve, occupations, Gaussian delta; Sec. II.B/II.C/III.A/III.C).
-// One workgroup takes one initial state s = (n, k) and one q3 plane:
+// One workgroup takes one initial state s = (n, k) and one q3 plane
+// (several on small grids), and goes through the final states p = k + q of a
+// plane in batches of p-lines:
 //   * Y_s(p1,p2; q3) is formed once per plane, straight into the registers of
 //     a matrix-core operand, its (p1, channel) rows spread over the waves;
-//   * Z_s(p1; q2,q3) of a batch of q-lines is one matrix product per 16 lines
+//   * Z_s(p1; q2,q3) of a batch of lines is one matrix product per 16 lines
 //     (16x16x4 MFMA, rows (p1, channel), inner index (p2, re/im), columns the
 //     lines) into LDS, where all waves read it;
-//   * the q of the batch are taken 64 at a time in the order of the final
-//     states p = k + q, across line ends, so no lane idles at the end of a
-//     line.  Each is sieved exactly (FP64, every final band near the state's
-//     energy; the compares go into wave masks, which the scalar unit joins
-//     and counts), and the (p, m) with a kept term go to the wave's queue;
+//   * a table of the lowest and highest energy of every band in each group of
+//     16 p says which (group, band) can reach the state's energy (about one in
+//     ten for a metal with well separated bands); those are listed and sieved
+//     exactly in FP64, four to a pass; the compares go into wave masks, which
+//     the scalar unit joins and counts, and the (p, m) with a kept term go to
+//     the wave's queue;
 //   * the queues of the waves are then evaluated as one list, one vertex per
-//     lane, whole passes dealt out to the waves.
+//     lane, whole passes dealt out to the waves, while the waves with fewer
+//     passes take more of the next batch's sieve.
 // Fermi and Bose factors come from per-call grid tables, so a vertex pays one
 // exp per kept term (the delta) and no other transcendental.  The phase of
 // the box corner, e^{i q.lo}, is common to all terms of a vertex and leaves
 // |g|^2 alone, so the three sums run over p = 0 .. NB-1, the last one by
-// Horner's rule.  The lists, their order and the sums over
-// lanes, waves and planes are fixed, so results are bit-reproducible.
+// Horner's rule.  The lists, their order and the sums over lanes, waves and
+// planes are fixed, so results are bit-reproducible.
+//
+// What bounds it.  Al-like model (4 bands, 3 modes, box 6^3), 71^3, 3
+// temperatures, FP32: 421 ms for 1.2e10 vertices, about 165 ms of it the
+// vertices (instruction issue: 700 or so FP32 operations each, at 70 TFLOP/s
+// in non-packed form), 130 the sieve, 25 Z, 100 the start of the planes.  One
+// wave per state and line, each with its own Z by vector operations, took
+// 648 ms; 128 threads per workgroup leave fewer waves waiting at a barrier
+// than 256 (443 ms).  The tables are stored by plane and component so that
+// the lanes' reads, neighbours in p or q, run along lines: an array of
+// records, one per gather, made the L1 the bound (160^3, FP32, 1
+// temperature: 173 ms against 101).  FP64, 100^3, 4 % of the states: 244 ms
+// (480 per line, 281 with records).
+#include <cstddef>
 #include <type_traits>
 
 #include "dev_util.h"
@@ -70,12 +87,41 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// (a mod N) for 0 <= a < 2^20, N <= 512: the float quotient is off by one at most
-__device__ __forceinline__ int fmod_small(int a, int N, float inv_n) {
-  int r = a - N * (int)floorf((float)a * inv_n);
-  r += (r < 0) ? N : 0;
-  r -= (r >= N) ? N : 0;
-  return r;
+// exp(x) for x <= 0: x = n ln 2 + r, Taylor series of e^r to r^13 (|r| <=
+// 0.347: remainder below 5e-18), scaled by 2^n.  No special values to tell
+// apart, so 19 instructions.
+__device__ __forceinline__ double exp_neg(double x) {
+  x = fmax(x, -800.0);
+  const double n = rint(x * 1.4426950408889634074);
+  double r = fma(n, -6.93147180369123816490e-01, x);  // ln 2 in two parts
+  r = fma(n, -1.90821492927058770002e-10, r);
+  double p = 1.0 / 6227020800.0;
+  p = fma(p, r, 1.0 / 479001600.0);
+  p = fma(p, r, 1.0 / 39916800.0);
+  p = fma(p, r, 1.0 / 3628800.0);
+  p = fma(p, r, 1.0 / 362880.0);
+  p = fma(p, r, 1.0 / 40320.0);
+  p = fma(p, r, 1.0 / 5040.0);
+  p = fma(p, r, 1.0 / 720.0);
+  p = fma(p, r, 1.0 / 120.0);
+  p = fma(p, r, 1.0 / 24.0);
+  p = fma(p, r, 1.0 / 6.0);
+  p = fma(p, r, 0.5);
+  p = fma(p, r, 1.0);
+  p = fma(p, r, 1.0);
+  return ldexp(p, (int)n);
+}
+
+// (a mod N) for 0 <= a < 2^14, N <= 512, inv_n the float nearest 1/N: the
+// quotient of a + 1/2 is at least 1/(2 N) from a whole number, the float
+// product within 2^-9 / N of it, so the truncation is exact
+__device__ __forceinline__ uint32_t mod_small(uint32_t a, uint32_t N, float inv_n) {
+  return a - __umul24((uint32_t)(((float)a + 0.5f) * inv_n), N);
+}
+// the value of x in one lane, as a wave-uniform value
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(x), lane), hi = __builtin_amdgcn_readlane(__double2hiint(x), lane);
+  return __hiloint2double(hi, lo);
 }
 
 template <class T, int NW, int NM, int NB>
@@ -85,29 +131,34 @@ struct WaveLayout {
   static constexpr int ROWS = NB * C;               // (p1, channel) rows of Y and Z
   static constexpr int MT = (ROWS + 15) / 16;       // 16-row tiles
   static constexpr int KS = (2 * NB + 3) / 4;       // 4-deep steps over (p2, re/im)
-  static constexpr int WPB = (C >= 48 && sizeof(T) == 8) ? 8 : 4;  // waves per workgroup
+  static constexpr int WPB = (C >= 48 && sizeof(T) == 8) ? 8 : C >= 48 ? 4 : 2;  // waves per workgroup
   static constexpr int TPW = (MT + WPB - 1) / WPB;  // tiles per wave
-  // lines per batch: 32 where two batches' worth of LDS is small, so that the
-  // partial last pass over the queue is rare; 16 for 48 channels
-  static constexpr int NL = C >= 48 ? 16 : 32;
+  // most lines per batch: the matrix product's columns (32 lines with 4 waves
+  // to a workgroup took 443 ms for 421 at Al-like 71^3, FP32)
+  static constexpr int NL = kWaveLines;
   // one line's Z, padded by 16 bytes so that neighbouring lines start in
   // different LDS banks
   static constexpr int ZB = ROWS + (int)(16 / sizeof(C2));
-  static constexpr int QC = 64 * NW + 512;          // queue entries per wave
-  __host__ __device__ static size_t tab_bytes(int N) { return align16(sizeof(C2) * (size_t)N); }
+  // sieve passes (four entries each) whose table entries are loaded together
+  static constexpr int SG = NM == 3 ? (sizeof(T) == 8 ? 3 : 4) : 2;
+  static constexpr int QC = 512;                     // queue entries per wave and round (a sieve pass adds 64 at most)
+  __host__ __device__ static size_t tab_bytes(int N) { return sizeof(C2) * 2 * (size_t)((N + 1) & ~1); }
   static constexpr size_t z_bytes = sizeof(C2) * (size_t)NL * ZB;
-  static constexpr size_t q_bytes = 4 * (size_t)WPB * QC;
-  static constexpr size_t rank_bytes = 2 * (size_t)WPB * QC;  // emit mode
-  static constexpr size_t misc_bytes = 8 * (size_t)WPB * 8 + 64;
+  static constexpr size_t q_bytes = 2 * 2 * (size_t)WPB * QC;                      // two rounds of 16-bit entries
+  static constexpr size_t rank_bytes = q_bytes;                                     // emit mode
+  static constexpr int LC = 128;                    // (group, band) list entries per wave
+  static constexpr size_t misc_bytes = 8 * (size_t)WPB * 8 + 2 * 4 * (size_t)WPB * 4 + 2 * (size_t)WPB * LC;
   __host__ __device__ static size_t total(int N, int mode) {
-    return misc_bytes + q_bytes + (mode == kCount ? 0 : tab_bytes(N) + z_bytes) + (mode == kEmit ? rank_bytes : 0);
+    return misc_bytes + (mode == kCount ? 0 : q_bytes + tab_bytes(N) + z_bytes) + (mode == kEmit ? rank_bytes : 0);
   }
 };
 
-// Waves per SIMD the register allocation targets.
+// Waves per SIMD the register allocation targets: as many as leave (almost)
+// no spills.  FP64 with 3 modes: 244 ms with 3, 269 with 2 (Al-like, 100^3);
+// FP32 with 6: 63 ms with 3, 94 with 4, 77 with 2 (Si-like, 130^3).
 template <class T, int NW, int NM>
 __host__ __device__ constexpr int waves_per_eu() {
-  return sizeof(T) == 4 ? (NW * NM >= 48 ? 3 : 4) : (NW * NM >= 48 ? 2 : 3);
+  return sizeof(T) == 4 ? (NM == 6 ? 3 : 4) : (NW * NM >= 48 ? 2 : 3);
 }
 
 // MODE: kRates computes 1/tau; kCount only counts, per state, the transition
@@ -126,7 +177,12 @@ void rates_wave_kernel(RatesArgs a) {
   // modes of a vertex in flight: all, but for 6 in FP64, whose mode matrices
   // would not fit the registers beside the band row
   constexpr int MU = (sizeof(T) == 8 && NM == 6) ? 2 : NM;
-  constexpr int C = LY::C, WPB = LY::WPB, TPW = LY::TPW, KS = LY::KS, NL = LY::NL, QC = LY::QC;
+  using PR = PRec<NW, NT>;
+  using QR = QRec<NM, NT>;
+  constexpr int kPC = sizeof(PR) / 16, kQC = sizeof(QR) / 16;          // chunks of the FP32 records
+  constexpr int kPE = offsetof(PR, e) / 4, kPF = offsetof(PR, f) / 4;  // floats before their members
+  constexpr int kQW = offsetof(QR, w) / 4, kQN = offsetof(QR, n) / 4;
+  constexpr int C = LY::C, WPB = LY::WPB, TPW = LY::TPW, KS = LY::KS, QC = LY::QC;
   extern __shared__ __align__(16) unsigned char smem[];
   const int N = a.N;
   const int lane = threadIdx.x & 63;
@@ -139,254 +195,333 @@ void rates_wave_kernel(RatesArgs a) {
   const int64_t blk = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
   if (blk >= a.ns_launch) return;  // workgroup-uniform
   const int64_t s = a.s_lo + blk;
-  const int plane = blockIdx.y, q3 = a.q3_lo + plane;
+  const int slot = blockIdx.y, slab = a.slab_lo + slot;  // planes slab_planes * slab ..
 
-  uint32_t *sQ = reinterpret_cast<uint32_t *>(smem);            // [WPB][QC] vertices: p1 | line << 9 | m << 15 | listed << 31
-  double *sRed = reinterpret_cast<double *>(smem + LY::q_bytes);  // [WPB][8] reductions; queue lengths in between
-  int *sCnt = reinterpret_cast<int *>(sRed);                    // [WPB][4]: length, listed entries, more to come
-  unsigned char *rest = smem + LY::q_bytes + LY::misc_bytes;
-  C2 *sTab = reinterpret_cast<C2 *>(rest);                      // e^{2 pi i m/N}
-  C2 *sZ = reinterpret_cast<C2 *>(rest + LY::tab_bytes(N));     // [NL][ZB]: [p1][mu][i] + pad
-  uint16_t *sRank = reinterpret_cast<uint16_t *>(rest + LY::tab_bytes(N) + LY::z_bytes);  // [WPB][QC]
+  double *sRed = reinterpret_cast<double *>(smem);                // [WPB][8] reductions
+  int *sCnt = reinterpret_cast<int *>(smem + 8 * WPB * 8);        // [2][WPB][4]: queue length, listed entries, more to come
+  uint16_t *sL = reinterpret_cast<uint16_t *>(smem + 8 * WPB * 8 + 2 * 4 * WPB * 4) + wave * LY::LC;  // the wave's list
+  unsigned char *rest = smem + LY::misc_bytes;
+  uint16_t *sQ = reinterpret_cast<uint16_t *>(rest);              // [2][WPB][QC] vertices: NW (p in the batch) + m
+  C2 *sTab = reinterpret_cast<C2 *>(rest + LY::q_bytes);          // [2][N]: f = e^{2 pi i m/N}, then i f
+  C2 *sZ = reinterpret_cast<C2 *>(rest + LY::q_bytes + LY::tab_bytes(N));  // [NL][ZB]: [p1][mu][i] + pad
+  uint16_t *sRank = reinterpret_cast<uint16_t *>(rest + LY::q_bytes + LY::tab_bytes(N) + LY::z_bytes);  // as sQ
 
-  if constexpr (MODE != kCount)
-    for (int t = threadIdx.x; t < N; t += WPB * 64) sTab[t] = mk<T>((T)a.tab[t].x, (T)a.tab[t].y);
+  if constexpr (MODE != kCount) {
+    for (int t = threadIdx.x; t < N; t += WPB * 64) {
+      const T c = (T)a.tab[t].x, sn = (T)a.tab[t].y;
+      sTab[t] = mk<T>(c, sn);
+      sTab[N + t] = mk<T>(-sn, c);
+    }
+    __syncthreads();
+  }
 
   const int k = a.sk[s], n = a.sn[s];
   const int k1 = k % N, k2 = (k / N) % N, k3 = k / (N * N);
-  const double es = a.eps[(int64_t)k * NW + n];
+  const int64_t n2 = (int64_t)N * N;
+  const double e_k = a.eps[plane_at(k, lane % NW, NW, n2)];  // band energies at k
+  const double es = lane_value(e_k, n);
   // the first state of a k point also looks for the other states' terms, so
-  // that every (k, q) pair is counted once
-  int nsh = 0;
-  if (MODE != kCount && (s == 0 || a.sk[s - 1] != k))
-    while (nsh < NW - 1 && s + 1 + nsh < a.ns_total && a.sk[s + 1 + nsh] == k) nsh++;
+  // that every (k, q) pair is counted once; the states of a k point are
+  // consecutive bands
   const bool count_kq = s == 0 || a.sk[s - 1] != k;
+  int nsh = 0;
+  if (MODE != kCount && count_kq)
+    while (nsh < NW - 1 && s + 1 + nsh < a.ns_total && a.sk[s + 1 + nsh] == k) nsh++;
   const double cut = a.sw * a.eta;
-  // bands further away keep no term (the margin covers the rounding of the
-  // exact test)
-  const double reach = (a.wmax + cut) * (1.0 + 1e-12) + 1e-12 * fabs(es);
+  // a band beyond the reach of these states' energies keeps no term (the
+  // margin covers the rounding here and of the exact test)
+  const double reach = (a.wmax + cut) * (1.0 + 1e-12);
+  const double e_top = lane_value(e_k, n + nsh);
+  const float win_lo = __double2float_rd(es - reach - 1e-12 * fabs(es)),
+              win_hi = __double2float_ru(e_top + reach + 1e-12 * fabs(e_top));
   const double inv_eta = 1.0 / a.eta;
-  const double dnorm = 1.0 / (1.7724538509055160273 * a.eta);
+  const float ex2 = (float)(1.2011224087864498 * inv_eta);  // sqrt(log2 e) / eta: exp(-(x/eta)^2) = 2^-(ex2 x)^2
+  const double pref = a.pref / (1.7724538509055160273 * a.eta);
   const float inv_n = 1.0f / (float)N;
-  const int p3 = (k3 + q3 >= N) ? k3 + q3 - N : k3 + q3;
-  // the planes of the tables that this workgroup reads
-  const int64_t p_plane = (int64_t)N * N * p3, q_plane = (int64_t)N * N * q3;
-  const double *eps_p = a.eps + p_plane * NW, *om_q = a.om + q_plane * NM;
-  const int32_t *stidx_p = MODE == kRates ? nullptr : a.stidx + p_plane * NW;
-  const C2 *evec_p, *uu_q;
-  const T *occ_p, *occ_q;
-  if constexpr (sizeof(T) == 8) {
-    evec_p = a.evec + p_plane * (NW * NW);
-    uu_q = a.uu + q_plane * (NM * NM);
-    occ_p = a.occ_f + p_plane * (NW * NT);
-    occ_q = a.occ_n + q_plane * (NM * NT);
-  } else {
-    evec_p = a.evec32 + p_plane * (NW * NW);
-    uu_q = a.uu32 + q_plane * (NM * NM);
-    occ_p = a.occ32_f + p_plane * (NW * NT);
-    occ_q = a.occ32_n + q_plane * (NM * NT);
-  }
 
   double acc[NT];
 #pragma unroll
   for (int t = 0; t < NT; t++) acc[t] = 0.0;
-  int n_q = 0, n_t = 0, n_kq = 0, n_v = 0;  // wave-uniform counts
-  int64_t gpos = 0;                         // next transition rate of the state
-  if constexpr (MODE == kEmit) gpos = a.g_cursor[s] + (a.g_slot ? a.g_slot[plane * a.ns_total + s] : 0) - a.g_base;
+  int n_dup = 0, n_kq = 0, n_v = 0;  // wave-uniform counts; n_dup: vertices at a q already counted
+  int64_t n_t = 0;
+  int64_t gpos = 0;                // next transition rate of the state
+  if constexpr (MODE == kEmit) gpos = a.g_cursor[s] + (a.g_slot ? a.g_slot[slot * a.ns_total + s] : 0) - a.g_base;
 
-  // ---- Y_s(p1, p2; q3) as the A operand: lane (i, g) of tile t and step ks
-  //      holds row 16 t + row_of(i) = (p1, channel), inner index 4 ks + g =
-  //      (p2, re/im) ----
+  const int nlb = a.batch_lines, nbatch = (N + nlb - 1) / nlb;
+  const int gb_full = (nlb * N + 15) >> 4;  // groups of 16 p of a full batch
+  constexpr int CG = 64 / NW;               // groups per look at the band ranges
   const int li = lane & 15, lg = lane >> 4;
-  T ya[TPW][KS];
-  if constexpr (MODE != kCount) {
-    __syncthreads();  // phase table
-    const C2 *X = reinterpret_cast<const C2 *>(a.X) + (s - a.s_base) * (int64_t)(NB * NB * NB * C);
-    C2 ph3[NB];
+  const int q3_end = min(N, (slab + 1) * a.slab_planes);
+  // modes below the frequency cut have w = inf in om, which keeps no term
+#pragma unroll 1
+  for (int q3 = slab * a.slab_planes; q3 < q3_end; q3++) {
+  const int p3 = (k3 + q3 >= N) ? k3 + q3 - N : k3 + q3;
+  // the planes of the tables that this workgroup reads
+  const double *eps_p = a.eps + (int64_t)p3 * NW * n2, *om_q = a.om + (int64_t)q3 * NM * n2;
+  const float2 *mm_p = a.band_range + (int64_t)a.plane_groups * NW * p3;
+
+  // ---- the sieve: this wave's groups of 16 p, sv_c .. sv_end - 1 of a batch ----
+  int sv_p0 = 0, sv_ne = 0;                // first p and number of p of the batch
+  int sv_mm = 0, sv_c = 0, sv_end = 0;     // its first group in the band-range table; the wave's next and last group
+  float2 range = make_float2(0.f, 0.f);    // band ranges of the groups from sv_c on, loaded ahead
+  int l_pos = 0, l_cnt = 0;                // the list's first entry and length
+  uint32_t hit_s = 0, hit_k = 0;           // kept p of the last entry's group, of the state and of its k point
+  auto load_ranges = [&]() __attribute__((always_inline)) {
+    if (sv_c < sv_end) range = mm_p[(sv_mm + min(sv_c + lane / NW, sv_end - 1)) * NW + lane % NW];
+  };
+  auto start_batch = [&](int b, int c0, int c1) __attribute__((always_inline)) {
+    sv_p0 = b * nlb;
+    sv_ne = min(nlb, N - sv_p0) * N;
+    sv_mm = b * gb_full;
+    sv_c = c0;
+    sv_end = c1;
+    l_cnt = 0;
+    load_ranges();
+  };
+  // sieve until the queue of round parity `par` may be full or the range is done
+  auto sieve = [&](int par) __attribute__((always_inline)) {
+    constexpr int SG = LY::SG;
+    int cnt = 0, listed = 0, more = 0;
+    uint16_t *q = sQ + (par * WPB + wave) * QC;
+    const double *eps_b = eps_p + sv_p0 * N;
+    for (;;) {
+      // list the (group, band) pairs within reach: group << 3 | band, and a
+      // mark on those whose predecessor is the same group
+      while (l_cnt < 4 * SG && sv_c < sv_end) {
+        const bool on = (range.x <= win_hi) & (range.y >= win_lo) & (sv_c + lane / NW < sv_end);
+        const unsigned long long mask = __ballot(on);
+        const uint32_t lower = (uint32_t)(mask >> (lane & ~(NW - 1))) & ((1u << (lane % NW)) - 1u);
+        if (on)
+          sL[(l_pos + l_cnt + lanes_below(mask)) & (LY::LC - 1)] =
+              (uint16_t)((sv_c + lane / NW) << 3 | lane % NW | (lower ? 0x8000 : 0));
+        l_cnt += __popcll(mask);
+        sv_c += CG;
+        load_ranges();
+      }
+      if (l_cnt == 0) break;
+      if (cnt > QC - 64 * SG) {
+        more = 1;
+        break;
+      }
+      __builtin_amdgcn_wave_barrier();
+      // the next passes of four entries, 16 lanes each, their table entries
+      // in one go; lanes of no entry or past the end read in bounds and are
+      // masked
+      uint32_t ee[SG], mm[SG];
+      unsigned long long valid[SG], again[SG];
+      double ep[SG], om[SG][NM];
+#pragma unroll
+      for (int j = 0; j < SG; j++) {
+        const uint32_t i = 4 * j + lg;
+        const uint32_t code = i < (uint32_t)l_cnt ? sL[(l_pos + i) & (LY::LC - 1)] : 0x7fffu;
+        const uint32_t e = (code >> 3 & 0xfffu) * 16u + li;
+        mm[j] = code & (NW - 1);
+        valid[j] = __ballot(e < (uint32_t)sv_ne);
+        again[j] = __ballot(code >> 15);
+        ee[j] = min(e, (uint32_t)(sv_ne - 1));
+        const uint32_t l = (uint32_t)(((float)ee[j] + 0.5f) * inv_n);
+        const uint32_t p1 = ee[j] - __umul24(l, N);
+        const uint32_t q1 = wrap_up(p1 - k1, N), q2 = wrap_up(sv_p0 + l - k2, N);
+        const uint32_t qoff = (__umul24(q2, N) + q1) * 8u;
+        ep[j] = at_offset(eps_b, (__umul24(mm[j], (uint32_t)n2) + ee[j]) * 8u);
+#pragma unroll
+        for (int nu = 0; nu < NM; nu++) om[j][nu] = at_offset(om_q + nu * n2, qoff);
+      }
+#pragma unroll
+      for (int j = 0; j < SG; j++) {
+        if (4 * j >= l_cnt) break;  // wave-uniform
+        // a term (nu, +-) is kept when |d +- w| <= cut with d = es - ep: the
+        // nearer of the two has |  |d| - w  |
+        const double d = fabs(es - ep[j]);
+        unsigned long long any = 0;
+#pragma unroll
+        for (int nu = 0; nu < NM; nu++) any |= __ballot(fabs(d - om[j][nu]) <= cut);
+        any &= valid[j];
+        unsigned long long any_k = any;
+        if (nsh > 0) {  // the other states at this k point
+          for (int i = 0; i < nsh; i++) {
+            const double d2 = fabs(lane_value(e_k, n + 1 + i) - ep[j]);
+#pragma unroll
+            for (int nu = 0; nu < NM; nu++) any_k |= __ballot(fabs(d2 - om[j][nu]) <= cut) & valid[j];
+          }
+          n_kq += __popcll(any_k);
+        }
+        // a p kept for several bands is one q
+        if (again[j]) {
+#pragma unroll
+          for (int g = 0; g < 4; g++) {
+            const uint32_t h = (uint32_t)(any >> 16 * g) & 0xffffu, hk = (uint32_t)(any_k >> 16 * g) & 0xffffu;
+            const bool same = (again[j] >> 16 * g) & 1ull;
+            n_dup += same ? __popc(h & hit_s) : 0;
+            if (nsh > 0) n_kq -= same ? __popc(hk & hit_k) : 0;
+            hit_s = h | (same ? hit_s : 0u);
+            hit_k = hk | (same ? hit_k : 0u);
+          }
+        } else {
+          hit_s = (uint32_t)(any >> 48);
+          hit_k = (uint32_t)(any_k >> 48);
+        }
+        const bool mine = __builtin_amdgcn_inverse_ballot_w64(any);
+        const uint32_t at = cnt + lanes_below(any);
+        if constexpr (MODE == kRates) {
+          if (mine) q[at] = (uint16_t)(ee[j] * NW + mm[j]);
+        } else {
+          const bool in_list = mine && at_offset(a.stidx + (p3 * n2 + sv_p0 * N) * NW, (ee[j] * NW + mm[j]) * 4u) >= 0;
+          const unsigned long long lm = __ballot(in_list);
+          if constexpr (MODE == kEmit) {
+            if (mine) {
+              q[at] = (uint16_t)(ee[j] * NW + mm[j]);
+              // rank among the wave's listed entries of the round, or none
+              sRank[(par * WPB + wave) * QC + at] = in_list ? (uint16_t)(listed + lanes_below(lm)) : (uint16_t)0xffff;
+            }
+          }
+          listed += __popcll(lm);
+        }
+        if constexpr (MODE != kCount) cnt += __popcll(any);
+      }
+      const int done = min(l_cnt, 4 * SG);
+      l_pos += done;
+      l_cnt -= done;
+    }
+    if constexpr (MODE == kCount) {
+      n_v += listed;
+    } else {
+      n_v += cnt;
+      if (lane == 0) {
+        int *o = sCnt + (par * WPB + wave) * 4;
+        o[0] = cnt;
+        o[1] = listed;
+        o[2] = more;
+      }
+    }
+  };
+
+  if constexpr (MODE == kCount) {
+    for (int b = 0; b < nbatch; b++) {
+      const int nc = (min(nlb, N - b * nlb) * N + 15) >> 4;
+      start_batch(b, nc * wave / WPB, nc * (wave + 1) / WPB);
+      sieve(0);
+    }
+  } else {
+    int b = 0, rot = (int)(s & (WPB - 1));
+    const int nc0 = (min(nlb, N) * N + 15) >> 4;
+    start_batch(0, nc0 * wave / WPB, nc0 * (wave + 1) / WPB);
+    // ---- Y_s(p1, p2; q3) as the A operand: lane (i, g) of tile t and step ks
+    //      holds row 16 t + row_of(i) = (p1, channel), inner index 4 ks + g =
+    //      (p2, re/im).  Rows past the last repeat it (their products are not
+    //      kept), so that a tile's loads go out together. ----
+    static_assert(NB % 2 == 0, "whole steps over (p2, re/im)");
+    T ya[TPW][KS];
     {
+      int64_t x0 = (s - a.s_base) * (int64_t)(NB * NB * NB * C);
+      asm volatile("" : "+s"(x0));  // read again for every plane: kept over the loop the row would fill the registers
+      const C2 *X = reinterpret_cast<const C2 *>(a.X) + x0;
+      C2 ph3[NB];  // Re(f x) = (f.x, -f.y) . x, Im(f x) = (f.y, f.x) . x
       int i3 = 0;
 #pragma unroll
       for (int p = 0; p < NB; p++) {
-        ph3[p] = sTab[i3];
+        const C2 f = sTab[((lg & 1) ? N : 0) + i3];
+        ph3[p] = (lg & 1) ? mk<T>(-f.x, f.y) : mk<T>(f.x, -f.y);
         i3 += q3;
         i3 -= (i3 >= N) ? N : 0;
       }
-    }
 #pragma unroll
-    for (int i = 0; i < TPW; i++) {
-      const int row = 16 * (wave + WPB * i) + MM::row_of(li);
-      const int p1 = row / C, c = row - p1 * C;
-#pragma unroll
-      for (int ks = 0; ks < KS; ks++) {
-        const int p2 = (4 * ks + lg) >> 1;
-        const bool im = lg & 1;
-        T y = 0;
-        if (row < LY::ROWS && p2 < NB) {
-          const C2 *x = X + ((p1 * NB + p2) * NB) * C + c;
-#pragma unroll
-          for (int p = 0; p < NB; p++) {
-            const C2 v = x[p * C];
-            y = fma(ph3[p].x, im ? v.y : v.x, y);
-            y = fma(ph3[p].y, im ? v.x : -v.y, y);
-          }
-        }
-        ya[i][ks] = y;
-      }
-    }
-  }
-
-  const int nbatch = (N + NL - 1) / NL;
-  const int nlb = (N + nbatch - 1) / nbatch;  // lines per batch, evened out
-  for (int q2_0 = 0; q2_0 < N; q2_0 += nlb) {
-    const int nl = min(nlb, N - q2_0);
-    // ---- Z_s(p1; q2, q3) of the batch -> LDS ----
-    if constexpr (MODE != kCount) {
-      for (int lt = 0; lt < nl; lt += 16) {
-        T br[KS], bi[KS];
+      for (int i = 0; i < TPW; i++) {
+        int lo = lane;
+        asm volatile("" : "+v"(lo));  // the offsets are not kept over the planes
+        const int row = min(16 * (wave + WPB * i) + MM::row_of(lo & 15), LY::ROWS - 1);
+        const int p1 = row / C, c = row - p1 * C;
+        const uint32_t off0 = (uint32_t)(((p1 * NB + (lo >> 5)) * NB) * C + c) * (uint32_t)sizeof(C2);
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) {
-          const C2 ph = sTab[fmod_small(__umul24(q2_0 + lt + li, (4 * ks + lg) >> 1), N, inv_n)];
-          br[ks] = (lg & 1) ? -ph.y : ph.x;
-          bi[ks] = (lg & 1) ? ph.x : ph.y;
-        }
+          const uint32_t off = off0 + ks * (uint32_t)(2 * NB * C * sizeof(C2));
+          T y = 0;
 #pragma unroll
-        for (int i = 0; i < TPW; i++) {
-          const int tile = wave + WPB * i;
-          if (tile < LY::MT) {  // wave-uniform
-            Acc zr = Acc{0, 0, 0, 0}, zi = Acc{0, 0, 0, 0};
-#pragma unroll
-            for (int ks = 0; ks < KS; ks++) {
-              zr = MM::mul(ya[i][ks], br[ks], zr);
-              zi = MM::mul(ya[i][ks], bi[ks], zi);
-            }
-            const int row = 16 * tile + 4 * lg;
-            C2 *z = sZ + (size_t)(lt + li) * LY::ZB + row;
-            if constexpr (LY::ROWS % 4 == 0) {
-              if (LY::ROWS % 16 == 0 || row < LY::ROWS)
-#pragma unroll
-                for (int r = 0; r < 4; r++) z[r] = mk<T>(zr[r], zi[r]);
-            } else {
-#pragma unroll
-              for (int r = 0; r < 4; r++)
-                if (row + r < LY::ROWS) z[r] = mk<T>(zr[r], zi[r]);
-            }
+          for (int p = 0; p < NB; p++) {
+            const C2 v = at_offset(X + p * C, off);
+            y = fma(ph3[p].x, v.x, y);
+            y = fma(ph3[p].y, v.y, y);
           }
+          if constexpr (sizeof(T) == 8) asm volatile("" : "+v"(y));
+          ya[i][ks] = y;
         }
+        // the loads in flight fit the registers: one tile's, in FP64 one step's
+        if constexpr (sizeof(T) == 4) asm volatile("" : "+v"(ya[i][0]), "+v"(ya[i][KS - 1]));
       }
     }
-
-    // ---- sieve of the batch's q, in the order of p; 64 per chunk, chunk c
-    //      to wave (c + rotation) % WPB ----
-    const int ne = nl * N;
-    const int rot = (int)((s + q2_0) & (WPB - 1));
-    int base = 64 * ((wave - rot) & (WPB - 1));  // first entry of the wave's next chunk
-    const uint32_t step_l = (uint32_t)(64 * WPB) / (uint32_t)N, step_p = 64 * WPB - step_l * N;
-    uint32_t pl = (uint32_t)(base + lane) / (uint32_t)N, p1 = base + lane - pl * N;  // line in the batch, p1
-    // table entries of the next chunk, loaded a chunk ahead; lanes past the
-    // end read in bounds and are masked
-    double ep[NW], om[NM];
-    uint32_t item = 0, poff = 0;
-    auto fetch = [&]() __attribute__((always_inline)) {
-      const uint32_t l = min(pl, (uint32_t)(nl - 1)), q2 = q2_0 + l;
-      const uint32_t p2 = wrap_down(k2 + q2, N), q1 = wrap_up(p1 - k1, N);
-      item = p1 | (l << 9);
-      poff = __umul24(p2, N) + p1;
-      const uint32_t qoff = __umul24(q2, N) + q1;
-#pragma unroll
-      for (int m = 0; m < NW; m++) ep[m] = at_offset(eps_p + m, poff * (uint32_t)(8 * NW));
-#pragma unroll
-      for (int nu = 0; nu < NM; nu++) om[nu] = at_offset(om_q + nu, __umul24(qoff, 8 * NM));
-      p1 += step_p;
-      pl += step_l;
-      pl += (p1 >= (uint32_t)N) ? 1u : 0u;
-      p1 = wrap_down(p1, N);
-    };
-    if (base < ne) fetch();
-    bool more;
-    do {
-      int cnt = 0, listed = 0;
-      while (base < ne && cnt <= QC - 64 * NW) {
-        const int nlane = ne - base;  // lanes in range
-        const unsigned long long valid = nlane >= 64 ? ~0ull : (1ull << nlane) - 1ull;
-        double e_[NW], w_[NM];
-        unsigned long long okw[NM];  // modes above the frequency cut, lanes in range
-#pragma unroll
-        for (int m = 0; m < NW; m++) e_[m] = ep[m];
-#pragma unroll
-        for (int nu = 0; nu < NM; nu++) {
-          w_[nu] = om[nu];
-          okw[nu] = __ballot(om[nu] >= a.wcut) & valid;
-        }
-        const uint32_t item_ = item, poff_ = poff;
-        base += 64 * WPB;
-        if (base < ne) fetch();
-        // a term (nu, +-) is kept when |d +- w| <= cut with d = es - ep: the
-        // nearer of the two has |  |d| - w  |
-        unsigned long long hit = 0;
-#pragma unroll
-        for (int m = 0; m < NW; m++) {
-          const double d = es - e_[m];
-          if (!(__ballot(fabs(d) <= reach) & valid)) continue;  // wave-uniform
-          unsigned long long any = 0;
-#pragma unroll
-          for (int nu = 0; nu < NM; nu++) any |= __ballot(fabs(fabs(d) - w_[nu]) <= cut) & okw[nu];
-          if (any) {
-            hit |= any;
-            const bool mine = __builtin_amdgcn_inverse_ballot_w64(any);
-            if constexpr (MODE == kRates) {
-              if (mine) sQ[wave * QC + cnt + lanes_below(any)] = item_ | ((uint32_t)m << 15);
-            } else {
-              const bool in_list = mine && at_offset(stidx_p + m, poff_ * (uint32_t)(4 * NW)) >= 0;
-              const unsigned long long lm = __ballot(in_list);
-              if constexpr (MODE == kEmit) {
-                if (mine) {
-                  const int at = wave * QC + cnt + lanes_below(any);
-                  sQ[at] = item_ | ((uint32_t)m << 15) | (in_list ? 0x80000000u : 0u);
-                  sRank[at] = (uint16_t)(listed + lanes_below(lm));
-                }
-              }
-              listed += __popcll(lm);
-            }
-            cnt += (MODE == kCount) ? 0 : __popcll(any);
-          }
-        }
-        n_q += __popcll(hit);
-        for (int j = 0; j < nsh; j++) {  // the other states at this k point
-          const double e2 = a.eps[(int64_t)k * NW + a.sn[s + 1 + j]];
-#pragma unroll
-          for (int m = 0; m < NW; m++) {
-            const double d = fabs(e2 - e_[m]);
-#pragma unroll
-            for (int nu = 0; nu < NM; nu++) hit |= __ballot(fabs(d - w_[nu]) <= cut) & okw[nu];
-          }
-        }
-        if (count_kq) n_kq += __popcll(hit);
-      }
-      if constexpr (MODE == kCount) {
-        n_v += listed;
-        more = false;
-        continue;
-      }
-      n_v += cnt;
-      if (lane == 0) {
-        sCnt[wave * 4] = cnt;
-        sCnt[wave * 4 + 1] = listed;
-        sCnt[wave * 4 + 2] = base < ne ? 1 : 0;
-      }
+    sieve(0);
+    bool new_z = true;
+    for (int par = 0;; par ^= 1) {  // rounds: one queue each, of one batch
       __syncthreads();
-      // ---- vertices of all queues, one per lane ----
+      const int p0 = b * nlb, nl = min(nlb, N - p0);
       int pre[WPB + 1], lpre[WPB + 1];
       pre[0] = lpre[0] = 0;
-      int left = 0;
+      int more = 0;
 #pragma unroll
       for (int w = 0; w < WPB; w++) {
-        pre[w + 1] = pre[w] + __builtin_amdgcn_readfirstlane(sCnt[w * 4]);
-        if constexpr (MODE == kEmit) lpre[w + 1] = lpre[w] + __builtin_amdgcn_readfirstlane(sCnt[w * 4 + 1]);
-        left |= __builtin_amdgcn_readfirstlane(sCnt[w * 4 + 2]);
+        const int *o = sCnt + (par * WPB + w) * 4;
+        pre[w + 1] = pre[w] + __builtin_amdgcn_readfirstlane(o[0]);
+        if constexpr (MODE == kEmit) lpre[w + 1] = lpre[w] + __builtin_amdgcn_readfirstlane(o[1]);
+        more |= __builtin_amdgcn_readfirstlane(o[2]);
       }
-      more = left != 0;
       const int total = pre[WPB];
-      for (int v0 = 64 * ((wave - rot) & (WPB - 1)); v0 < total; v0 += 64 * WPB) {
+      if (new_z) {
+        // ---- Z_s(p1; q2, q3) of the batch -> LDS ----
+        const C2 *tab = sTab + ((lg & 1) ? N : 0);
+        for (int lt = 0; lt < nl; lt += 16) {
+          const uint32_t q2 = wrap_up(p0 + lt + li - k2, N);
+          C2 f[KS];
+#pragma unroll
+          for (int ks = 0; ks < KS; ks++) f[ks] = tab[mod_small(__umul24(q2, (4 * ks + lg) >> 1), N, inv_n)];
+#pragma unroll
+          for (int i = 0; i < TPW; i++) {
+            const int tile = wave + WPB * i;
+            if (tile < LY::MT) {  // wave-uniform
+              Acc zr = Acc{0, 0, 0, 0}, zi = Acc{0, 0, 0, 0};
+#pragma unroll
+              for (int ks = 0; ks < KS; ks++) {
+                zr = MM::mul(ya[i][ks], f[ks].x, zr);
+                zi = MM::mul(ya[i][ks], f[ks].y, zi);
+              }
+              const int row = 16 * tile + 4 * lg;
+              C2 *z = sZ + __umul24(lt + li, LY::ZB) + row;
+              if constexpr (LY::ROWS % 4 == 0) {
+                if (LY::ROWS % 16 == 0 || row < LY::ROWS)
+#pragma unroll
+                  for (int r = 0; r < 4; r++) z[r] = mk<T>(zr[r], zi[r]);
+              } else {
+#pragma unroll
+                for (int r = 0; r < 4; r++)
+                  if (row + r < LY::ROWS) z[r] = mk<T>(zr[r], zi[r]);
+              }
+            }
+          }
+        }
+        __syncthreads();
+      }
+      // ---- the next batch's share of the sieve: waves with a pass of
+      //      vertices more take fewer chunks; its band ranges load meanwhile ----
+      const int turn = (wave - rot) & (WPB - 1);  // this wave's turn in the round
+      if (!more && b + 1 < nbatch) {
+        constexpr int kPassChunks = NM == 3 ? 64 : 256;  // groups of sieve that cost a pass
+        const int nc = (min(nlb, N - (b + 1) * nlb) * N + 15) >> 4;
+        const int heavy = ((total + 63) >> 6) % WPB, light = WPB - heavy;
+        const int x = heavy ? max(0, nc - light * kPassChunks) / WPB : 0, rest_c = nc - heavy * x;
+        const int j = turn - heavy;
+        const float r = __builtin_amdgcn_rcpf((float)light);  // (rest_c j + 1/2) / light: exact at j = light
+        const int c0 = j < 0 ? turn * x : heavy * x + (int)(((float)(rest_c * j) + 0.5f) * r);
+        const int c1 = j < 0 ? c0 + x : heavy * x + (int)(((float)(rest_c * (j + 1)) + 0.5f) * r);
+        start_batch(b + 1, __builtin_amdgcn_readfirstlane(c0), __builtin_amdgcn_readfirstlane(c1));
+      }
+      // ---- vertices of all queues, one per lane ----
+      // bases of the batch's first p and of the plane's first q
+      [[maybe_unused]] const double2 *evec_b = a.evec + (int64_t)p3 * (NW * NW) * n2 + p0 * N;
+      [[maybe_unused]] const double2 *uu_q = a.uu + (int64_t)q3 * (NM * NM) * n2;
+      [[maybe_unused]] const double *occ_b =
+          a.occ_f + (NT == 1 ? (int64_t)p3 * NW * n2 + p0 * N : 2 * ((int64_t)p3 * NW * 2 * n2 + p0 * N));
+      [[maybe_unused]] const float4 *rec_b = a.rec_p + (int64_t)p3 * NW * kPC * n2 + p0 * N;
+      [[maybe_unused]] const float4 *rec_qp = a.rec_q + (int64_t)q3 * kQC * n2;
+      for (int v0 = 64 * turn; v0 < total; v0 += 64 * WPB) {
         const bool live = v0 + lane < total;
         const int i = min(v0 + lane, total - 1);  // lanes past the end repeat the last vertex and drop it
         int at = i, lbase = 0;
@@ -395,15 +530,38 @@ void rates_wave_kernel(RatesArgs a) {
           at = (i >= pre[w]) ? i - pre[w] + w * QC : at;
           if constexpr (MODE == kEmit) lbase = (i >= pre[w]) ? lpre[w] : lbase;
         }
-        const uint32_t it = sQ[at];
-        const uint32_t vp1 = it & 511u, vl = (it >> 9) & 63u, m = (it >> 15) & 7u;
-        const uint32_t q2 = q2_0 + vl, p2 = wrap_down(k2 + q2, N), q1 = wrap_up(vp1 - k1, N);
-        const uint32_t qoff = __umul24(q2, N) + q1;              // q in its plane
-        const uint32_t pm = (__umul24(p2, N) + vp1) * NW + m;    // (p, m) in its plane
-        const double d = es - at_offset(eps_p, pm * 8u);
+        at += par * WPB * QC;
+        const uint32_t pm = sQ[at], e = pm / NW, m = pm % NW;  // p from the batch's first on, band
+        const uint32_t vl = (uint32_t)(((float)e + 0.5f) * inv_n), vp1 = e - __umul24(vl, N);
+        const uint32_t q1 = wrap_up(vp1 - k1, N), q2 = wrap_up(p0 + vl - k2, N);
+        const uint32_t qoff = __umul24(q2, N) + q1;  // q in its plane
+        double d;
         C2 vrow[NW];
+        // FP32: the records' chunks, all loads of the vertex issued here, ahead of
+        // the sum below, which hides them
+        [[maybe_unused]] float4 pc[kPC], qc[kQC];
+        [[maybe_unused]] auto p_float = [&](int f) __attribute__((always_inline)) {
+          const float4 c = pc[f / 4];
+          return f % 4 == 0 ? c.x : f % 4 == 1 ? c.y : f % 4 == 2 ? c.z : c.w;
+        };
+        [[maybe_unused]] auto q_float = [&](int f) __attribute__((always_inline)) {
+          const float4 c = qc[f / 4];
+          return f % 4 == 0 ? c.x : f % 4 == 1 ? c.y : f % 4 == 2 ? c.z : c.w;
+        };
+        if constexpr (sizeof(T) == 8) {
+          d = es - at_offset(eps_p + p0 * N, (m * (uint32_t)n2 + e) * 8u);
 #pragma unroll
-        for (int j = 0; j < NW; j++) vrow[j] = at_offset(evec_p + j, pm * (uint32_t)(sizeof(C2) * NW));
+          for (int j = 0; j < NW; j++) vrow[j] = at_offset(evec_b + j * n2, (m * (uint32_t)(NW * n2) + e) * 16u);
+        } else {
+#pragma unroll
+          for (int c = 0; c < kPC; c++) pc[c] = at_offset(rec_b + c * n2, (m * (uint32_t)(kPC * n2) + e) * 16u);
+#pragma unroll
+          for (int c = 0; c < kQC; c++) qc[c] = at_offset(rec_qp + c * n2, qoff * 16u);
+          __builtin_amdgcn_sched_barrier(0);
+          d = es - __hiloint2double(__float_as_int(p_float(kPE + 1)), __float_as_int(p_float(kPE)));
+#pragma unroll
+          for (int j = 0; j < NW; j++) vrow[j] = mk<T>(p_float(2 * j), p_float(2 * j + 1));
+        }
         // W_mu = sum_p e^{i 2 pi q1 p/N} sum_i conj(V_im(k+q)) Z(p; mu, i)
         T wr[NM], wi[NM];
         const C2 rq = sTab[q1];
@@ -440,65 +598,99 @@ void rates_wave_kernel(RatesArgs a) {
         T sb = 0, sc = 0, ct[NT];
 #pragma unroll
         for (int t = 0; t < NT; t++) ct[t] = 0;
-#pragma unroll(MU)
+#pragma unroll MU
         for (int nu = 0; nu < NM; nu++) {
-          const double w = at_offset(om_q + nu, __umul24(qoff, 8 * NM)), xpd = d + w, xmd = d - w;
-          const bool on = live && w >= a.wcut;
-          const bool okp = on && fabs(xpd) <= cut, okm = on && fabs(xmd) <= cut;
+          double w;
+          C2 u[NM];
+          if constexpr (sizeof(T) == 8) {
+            w = at_offset(om_q + nu * n2, qoff * 8u);
+#pragma unroll
+            for (int mu = 0; mu < NM; mu++) u[mu] = at_offset(uu_q + (nu * NM + mu) * n2, qoff * 16u);
+          } else {
+            w = __hiloint2double(__float_as_int(q_float(kQW + 2 * nu + 1)), __float_as_int(q_float(kQW + 2 * nu)));
+#pragma unroll
+            for (int mu = 0; mu < NM; mu++) u[mu] = mk<T>(q_float(2 * (nu * NM + mu)), q_float(2 * (nu * NM + mu) + 1));
+          }
+          const double xpd = d + w, xmd = d - w;
+          const bool okp = live && fabs(xpd) <= cut, okm = live && fabs(xmd) <= cut;
           n_t += __popcll(__ballot(okp)) + __popcll(__ballot(okm));
           T gr = 0, gi = 0;
 #pragma unroll
-          for (int mu = 0; mu < NM; mu++) {
-            const C2 u = at_offset(uu_q + nu * NM + mu, __umul24(qoff, (uint32_t)(sizeof(C2) * NM * NM)));
-            cmac<T>(gr, gi, wr[mu], wi[mu], u.x, u.y);
-          }
+          for (int mu = 0; mu < NM; mu++) cmac<T>(gr, gi, wr[mu], wi[mu], u[mu].x, u[mu].y);
           const T g2 = fma(gr, gr, gi * gi);
           T dp, dm;
           if constexpr (sizeof(T) == 8) {
-            dp = okp ? exp(-(xpd * inv_eta) * (xpd * inv_eta)) * dnorm : 0.0;
-            dm = okm ? exp(-(xmd * inv_eta) * (xmd * inv_eta)) * dnorm : 0.0;
+            dp = okp ? exp_neg(-(xpd * inv_eta) * (xpd * inv_eta)) : 0.0;
+            dm = okm ? exp_neg(-(xmd * inv_eta) * (xmd * inv_eta)) : 0.0;
           } else {
             // FP32 form: |g|^2, the Gaussians and the occupation weights in
             // FP32 (the arguments x are formed in FP64 from the FP64 energies)
-            const float xp = (float)xpd * (float)inv_eta, xm = (float)xmd * (float)inv_eta;
-            dp = okp ? __expf(-xp * xp) * (float)dnorm : 0.f;
-            dm = okm ? __expf(-xm * xm) * (float)dnorm : 0.f;
+            const float xp = (float)xpd * ex2, xm = (float)xmd * ex2;
+            dp = okp ? __builtin_amdgcn_exp2f(-xp * xp) : 0.f;
+            dm = okm ? __builtin_amdgcn_exp2f(-xm * xm) : 0.f;
           }
           const T ga = g2 * (dp + dm);
           sb = fma(g2, dp - dm, sb);
           sc = fma(g2, dm, sc);
 #pragma unroll
-          for (int t = 0; t < NT; t++)
-            ct[t] = fma(at_offset(occ_q + nu * NT + t, __umul24(qoff, (uint32_t)(sizeof(T) * NM * NT))), ga, ct[t]);
+          for (int t = 0; t < NT; t++) {
+            T nq;
+            if constexpr (sizeof(T) == 4) {
+              nq = q_float(kQN + nu * NT + t);
+            } else if constexpr (NT == 1) {
+              nq = at_offset(a.occ_n + (q3 * NM + nu) * n2, qoff * 8u);
+            } else {
+              const double2 f = at_offset(reinterpret_cast<const double2 *>(a.occ_n) + ((q3 * NM + nu) * 2 + t / 2) * n2, qoff * 16u);
+              nq = t % 2 ? f.y : f.x;
+            }
+            ct[t] = fma(nq, ga, ct[t]);
+          }
         }
 #pragma unroll
-        for (int t = 0; t < NT; t++) ct[t] += fma(at_offset(occ_p + t, pm * (uint32_t)(sizeof(T) * NT)), sb, sc);
+        for (int t = 0; t < NT; t++) {
+          T f;
+          if constexpr (sizeof(T) == 4) {
+            f = p_float(kPF + t);
+          } else if constexpr (NT == 1) {
+            f = at_offset(occ_b, (m * (uint32_t)n2 + e) * 8u);
+          } else {
+            const double2 f2 = at_offset(reinterpret_cast<const double2 *>(occ_b) + (t / 2) * n2, (m * (uint32_t)(2 * n2) + e) * 16u);
+            f = t % 2 ? f2.y : f2.x;
+          }
+          ct[t] += fma(f, sb, sc);
+        }
         if (live) {
 #pragma unroll
           for (int t = 0; t < NT; t++) acc[t] += (double)ct[t];
           if constexpr (MODE == kEmit) {
-            if (it >> 31) {  // final state in the list: its transition rate
+            if (sRank[at] != 0xffff) {  // final state in the list: its transition rate
               const int64_t e = gpos + lbase + sRank[at];
-              a.g_col[e] = at_offset(stidx_p, pm * 4u);
+              a.g_col[e] = at_offset(a.stidx + (p3 * n2 + p0 * N) * NW, pm * 4u);
 #pragma unroll
               for (int t = 0; t < NT; t++)
-                if (t < a.nt) a.g_val[(int64_t)t * a.g_stride + e] = a.pref * (double)ct[t];
+                if (t < a.nt) a.g_val[(int64_t)t * a.g_stride + e] = pref * (double)ct[t];
             }
           }
         }
       }
       if constexpr (MODE == kEmit) gpos += lpre[WPB];
-      __syncthreads();  // queues and Z are rewritten
-    } while (more);
+      // ---- the next round's queue ----
+      if (!more && ++b == nbatch) break;  // workgroup-uniform
+      new_z = !more;
+      rot = (rot + 1) & (WPB - 1);
+      sieve(par ^ 1);
+    }
+    __syncthreads();  // the next plane and the reductions reuse the LDS
+  }
   }
 
-  if constexpr (MODE == kCount) {  // this plane's transition rates of the state
+  if constexpr (MODE == kCount) {  // the slab's transition rates of the state
     if (lane == 0) sCnt[wave] = n_v;
     __syncthreads();
     if (threadIdx.x == 0) {
       int64_t c = 0;
       for (int w = 0; w < WPB; w++) c += sCnt[w];
-      if (a.g_slot) a.g_slot[plane * a.ns_total + s] = c;
+      if (a.g_slot) a.g_slot[slot * a.ns_total + s] = c;
       else a.g_cursor[s] += c;
     }
     return;
@@ -506,7 +698,7 @@ void rates_wave_kernel(RatesArgs a) {
   if constexpr (MODE == kEmit)
     if (threadIdx.x == 0 && !a.g_slot) a.g_cursor[s] = gpos + a.g_base;
 
-  // ---- fixed-order reductions; planes add up in order ----
+  // ---- fixed-order reductions; slabs add up in order ----
 #pragma unroll
   for (int t = 0; t < NT; t++) {
     double v = acc[t];
@@ -514,34 +706,37 @@ void rates_wave_kernel(RatesArgs a) {
     for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
     if (lane == 0) sRed[wave * 8 + t] = v;
   }
+  const int n_q = n_v - n_dup;
+  if (nsh == 0) n_kq = count_kq ? n_q : 0;
   if (lane == 0) {
     int *c = reinterpret_cast<int *>(sRed + wave * 8 + 4);
     c[0] = n_q;
-    c[1] = n_t;
-    c[2] = n_kq;
-    c[3] = n_v;
+    c[1] = n_kq;
+    c[2] = n_v;
+    sRed[wave * 8 + 6] = __longlong_as_double(n_t);
   }
   __syncthreads();
   if ((int)threadIdx.x < NT && (int)threadIdx.x < a.nt) {
     const int t = threadIdx.x;
     double v = 0.0;
     for (int w = 0; w < WPB; w++) v += sRed[w * 8 + t];
-    v *= a.pref;
+    v *= pref;
     if (a.part_tau) {
-      a.part_tau[((int64_t)plane * a.nt + t) * a.ns_total + s] = v;
+      a.part_tau[((int64_t)slot * a.nt + t) * a.ns_total + s] = v;
     } else {
       double *dst = a.inv_tau + (int64_t)t * a.ns_total + s;
-      *dst = (q3 == 0 ? 0.0 : *dst) + v;
+      *dst = (slab == 0 ? 0.0 : *dst) + v;
     }
   } else if (threadIdx.x >= 8 && threadIdx.x < 12) {
-    const int j = threadIdx.x - 8;
+    const int j = threadIdx.x - 8;  // n_q, n_terms, (k,q) pairs, vertices
     int64_t v = 0;
-    for (int w = 0; w < WPB; w++) v += reinterpret_cast<const int *>(sRed + w * 8 + 4)[j];
+    for (int w = 0; w < WPB; w++)
+      v += j == 1 ? __double_as_longlong(sRed[w * 8 + 6]) : reinterpret_cast<const int *>(sRed + w * 8 + 4)[j == 0 ? 0 : j - 1];
     if (a.part_tau) {
-      a.part_cnt[((int64_t)plane * a.ns_total + s) * 4 + j] = v;
+      a.part_cnt[((int64_t)slot * a.ns_total + s) * 4 + j] = v;
     } else {
       int64_t *dst = (j < 2 ? a.st_counts : a.kv_counts - 2) + s * 2 + j;
-      *dst = (q3 == 0 ? 0 : *dst) + v;
+      *dst = (slab == 0 ? 0 : *dst) + v;
     }
   }
 }
@@ -555,7 +750,7 @@ hipError_t launch_wave(const RatesArgs &a, hipStream_t st) {
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
   if (e != hipSuccess) return e;
   const int64_t grid = ((a.ns_launch + 7) / 8) * 8;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid, (unsigned)(a.q3_hi - a.q3_lo)), dim3(LY::WPB * 64), sh, st, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid, (unsigned)(a.slab_hi - a.slab_lo)), dim3(LY::WPB * 64), sh, st, a);
   return hipGetLastError();
 }
 

@@ -32,7 +32,7 @@ hipError_t electron_tables(eph_ctx *c, int N, const Units &U, hipStream_t st) {
     return launch_bloch_lines(0, c->nw, N, c->hbox_lo, c->hbox_n, c->lattice, c->hbox.as<double2>(),
                               c->tab.as<double2>(), nullptr, U.cph_ev, 0.0, U.vel_unit, c->eps.as<double>(),
                               c->evec.as<double2>(), c->vel.as<double>(), nullptr, st);
-  return launch_bloch_eig(0, c->nw, N, 0, NQ, c->nrh, c->rh.as<int>(), c->rh_w.as<double>(), c->rh_cart.as<double>(),
+  return launch_bloch_eig(0, c->nw, N, NQ, c->nrh, c->rh.as<int>(), c->rh_w.as<double>(), c->rh_cart.as<double>(),
                           c->ham.as<double2>(), c->tab.as<double2>(), nullptr, U.cph_ev, 0.0, U.vel_unit,
                           c->eps.as<double>(), c->evec.as<double2>(), c->vel.as<double>(), nullptr, st);
 }
@@ -45,7 +45,7 @@ hipError_t phonon_tables(eph_ctx *c, int N, const Units &U, double omega_cut, un
     return launch_bloch_lines(1, c->nm, N, c->dbox_lo, c->dbox_n, c->lattice, c->dbox.as<double2>(),
                               c->tab.as<double2>(), c->mode_mass_d.as<double>(), U.cph_ev, omega_cut, U.vel_unit,
                               c->om.as<double>(), c->uu.as<double2>(), nullptr, n_excluded, st);
-  return launch_bloch_eig(1, c->nm, N, 0, NQ, c->nrd, c->rd.as<int>(), c->rd_w.as<double>(), nullptr,
+  return launch_bloch_eig(1, c->nm, N, NQ, c->nrd, c->rd.as<int>(), c->rd_w.as<double>(), nullptr,
                           c->dyn.as<double2>(), c->tab.as<double2>(), c->mode_mass_d.as<double>(), U.cph_ev,
                           omega_cut, U.vel_unit, c->om.as<double>(), c->uu.as<double2>(), nullptr, n_excluded, st);
 }

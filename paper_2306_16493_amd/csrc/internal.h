@@ -149,11 +149,12 @@ struct eph_gamma {
 namespace eph {
 
 // ---- launchers (each returns the launch error) ----
-// Bloch sum + Hermitian eigensolve on grid points [k0, k0+nk).
+// Bloch sum + Hermitian eigensolve on grid points [0, nk).
 //  mode 0 (electrons): eval (k, n), evec (k, m n + i) = V_im, vel[k][n][3] (m/s)
 //  mode 1 (phonons):   eval (k, nu) = hbar w (eV), evec (k, nu n + mu) = u_{mu nu}
 //                      (A), zero for hbar w < omega_cut; counts excluded modes
-hipError_t launch_bloch_eig(int mode, int n, int N, int64_t k0, int64_t nk, int nr, const int *R,
+//  mode 2:             mode 0's eval alone
+hipError_t launch_bloch_eig(int mode, int n, int N, int64_t nk, int nr, const int *R,
                             const double *w, const double *Rcart, const double2 *M, const double2 *tab,
                             const double *mode_mass, double cph, double omega_cut, double vel_unit,
                             double *eval, double2 *evec, double *vel, unsigned long long *n_excluded,

@@ -7,14 +7,23 @@
 // Phonons: D(q) = sum_R w_R Phi(R)/sqrt(M M') e^{iq.R}, (hbar w)^2 = C lambda,
 // u_{mu nu} = e_{mu nu} sqrt(C/(2 M_mu hbar w_nu)) (Sec. II.B).
 //
-// Layout on the chip: one wave64 per workgroup; a matrix of padded size NP
-// (1, 2, 4 or 8) occupies NP*NP lanes, one element (i,j) per lane, so a wave
-// holds 64/(NP*NP) matrices.  Each lane accumulates its own element of the
-// Bloch sum (and of the three derivatives) in registers; the eigensolve is a
-// parallel cyclic Jacobi with round-robin pairing: every round applies
-// NP/2 disjoint complex rotations at once, each lane updating its element of
-// A and V from the (at most four) elements of the two rows/columns it mixes,
-// staged in LDS.  Everything stays in FP64.
+// Layout on the chip: a matrix takes NP lanes (its size n rounded up to a power
+// of two), one column of A and of V per lane in registers, so a wave holds
+// 64 / NP matrices.  The eigensolve is a parallel cyclic Jacobi with
+// round-robin pairing: every round applies n/2 disjoint complex rotations at
+// once.  A lane rotates its column with its partner's, whose elements come
+// over the cross-lane network, and then the rows of its column, which are all
+// its own.  Everything stays in FP64.
+//
+// What bounds it: vector instructions, some 250 FP64 operations and 100
+// cross-lane moves to a round of eight 8 x 8 matrices, 7 rounds to a sweep.
+// Both tables of a grid, 130^3 with 8 bands and 6 modes: 25 ms; 100^3 with 4
+// and 3: 1.3 ms.  With one element per lane, read from LDS with the rows and
+// columns it mixes, each lane formed the rotation of its row and column anew
+// and the wave waited three times a round: 89 and 4.2 ms.
+#include <algorithm>
+#include <utility>
+
 #include "dev_util.h"
 #include "internal.h"
 
@@ -26,29 +35,158 @@ constexpr int kMaxSweeps = 40;
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
-__device__ __forceinline__ double2 cconj(double2 a) { return make_double2(a.x, -a.y); }
 __device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 
 // Partner of index x in round r of the round-robin (circle) schedule of NP
 // indices; NP-1 rounds cover every pair once.
 template <int NP>
-__device__ __forceinline__ int rr_partner(int x, int r) {
+__host__ __device__ constexpr int rr_partner(int x, int r) {
   if (NP == 1) return x;
-  constexpr int M = NP - 1;
-  int pos = (x == 0) ? 0 : ((x - 1 - r + 2 * M) % M) + 1;
-  int ppos = NP - 1 - pos;
+  constexpr int M = NP > 1 ? NP - 1 : 1;
+  const int pos = (x == 0) ? 0 : ((x - 1 - r + 2 * M) % M) + 1;
+  const int ppos = NP - 1 - pos;
   return (ppos == 0) ? 0 : ((ppos - 1 + r) % M) + 1;
 }
 
-// element (row a, col b) of the block rotation J of this round.
-struct Rot {
-  double c;
-  double2 se;  // s e^{i phi}
+constexpr int pow2_up(int n) { return n <= 1 ? 1 : n <= 2 ? 2 : n <= 4 ? 4 : 8; }
+
+// the value of x in the lane at byte address at (4 times its number)
+__device__ __forceinline__ double lane_get(double x, int at) {
+  const int lo = __builtin_amdgcn_ds_bpermute(at, __double2loint(x));
+  const int hi = __builtin_amdgcn_ds_bpermute(at, __double2hiint(x));
+  return __hiloint2double(hi, lo);
+}
+template <int CTRL>
+__device__ __forceinline__ double quad_get(double x) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+// the value of x in the matrix's lane I
+template <int NP, int I>
+__device__ __forceinline__ double lane_of(double x, int base4) {
+  if constexpr (NP == 4) return quad_get<I * 0x55>(x);
+  else return lane_get(x, base4 + 4 * I);
+}
+// the value of x in the lane of the partner column in round R (at: its address)
+template <int NP, int R>
+__device__ __forceinline__ double partner_get(double x, int at) {
+  if constexpr (NP == 4)
+    return quad_get<rr_partner<4>(0, R) | rr_partner<4>(1, R) << 2 | rr_partner<4>(2, R) << 4 | rr_partner<4>(3, R) << 6>(x);
+  else
+    return lane_get(x, at);
+}
+
+// A matrix's lanes: column j, base4 = 4 * (lane of column 0).
+struct Cols {
+  int j, base4;
 };
+
+// the rotation of rows I and rr_partner(I), if I is the smaller
+template <int NE, int NP, int R, int I>
+__device__ __forceinline__ void rotate_rows(double2 (&A)[NE], const Cols &m, double c, double2 se) {
+  constexpr int Q = rr_partner<NP>(I, R);
+  if constexpr (I < Q && Q < NE) {
+    const double cr = lane_of<NP, I>(c, m.base4);
+    const double2 s = make_double2(lane_of<NP, I>(se.x, m.base4), lane_of<NP, I>(se.y, m.base4));
+    const double2 bp = A[I], bq = A[Q];
+    // rows of J^H: (c, -s e) and (conj(s e), c)
+    A[I] = cadd(make_double2(cr * bp.x, cr * bp.y), cmul(make_double2(-s.x, -s.y), bq));
+    A[Q] = cadd(make_double2(cr * bq.x, cr * bq.y), cmul(make_double2(s.x, -s.y), bp));
+    if (m.j == I) A[Q] = make_double2(0.0, 0.0);  // the annihilated pair
+    if (m.j == Q) A[I] = make_double2(0.0, 0.0);
+  }
+}
+
+template <int NE, int NP, bool VEC, int R, int... I>
+__device__ __forceinline__ void jacobi_round(double2 (&A)[NE], double2 (&V)[NE], const Cols &m,
+                                             std::integer_sequence<int, I...>) {
+  const int j = m.j;
+  int pj = j;
+  double2 apq = make_double2(0.0, 0.0);
+  double dg = 0.0;
+#pragma unroll
+  for (int x = 0; x < NE; x++) {
+    const int px = rr_partner<NP>(x, R);
+    if (j == x) {
+      dg = A[x].x;
+      if (px < NE) {
+        pj = px;
+        apq = A[px];
+      }
+    }
+  }
+  const int at = m.base4 + 4 * pj, up = m.base4 + 4 * max(j, pj);
+  const double dgo = lane_get(dg, at);
+  apq = make_double2(lane_get(apq.x, up), lane_get(apq.y, up));  // A_pq, p < q, from column q
+  double c = 1.0;
+  double2 se = make_double2(0.0, 0.0);  // s e^{i phi}: J_pp = J_qq = c, J_pq = se, J_qp = -conj(se)
+  const double g = sqrt(apq.x * apq.x + apq.y * apq.y);
+  if (pj != j && g != 0.0) {
+    const double app = j < pj ? dg : dgo, aqq = j < pj ? dgo : dg;
+    const double theta = (aqq - app) / (2.0 * g);
+    const double t = (theta >= 0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
+    c = 1.0 / sqrt(t * t + 1.0);
+    const double s = t * c;
+    se = make_double2(s * apq.x / g, s * apq.y / g);
+  }
+  const double2 jp = make_double2(j > pj ? se.x : -se.x, se.y);  // the partner column's factor
+#pragma unroll
+  for (int i = 0; i < NE; i++) {
+    const double2 o = make_double2(partner_get<NP, R>(A[i].x, at), partner_get<NP, R>(A[i].y, at));
+    A[i] = cadd(make_double2(A[i].x * c, A[i].y * c), cmul(o, jp));
+    if constexpr (VEC) {
+      const double2 v = make_double2(partner_get<NP, R>(V[i].x, at), partner_get<NP, R>(V[i].y, at));
+      V[i] = cadd(make_double2(V[i].x * c, V[i].y * c), cmul(v, jp));
+    }
+  }
+  (rotate_rows<NE, NP, R, I>(A, m, c, se), ...);
+#pragma unroll
+  for (int i = 0; i < NE; i++)
+    if (j == i) A[i].y = 0.0;
+}
+
+template <int NE, int NP, bool VEC, int... R>
+__device__ __forceinline__ void jacobi_sweep(double2 (&A)[NE], double2 (&V)[NE], const Cols &m,
+                                             std::integer_sequence<int, R...>) {
+  (jacobi_round<NE, NP, VEC, R>(A, V, m, std::make_integer_sequence<int, NE>()), ...);
+}
+
+// Parallel cyclic Jacobi on the matrices of one wave; lanes of columns past
+// NE hold zeros.  On return the diagonal holds the eigenvalues and, with VEC,
+// V the eigenvectors.
+template <int NE, bool VEC>
+__device__ __forceinline__ void jacobi(double2 (&A)[NE], double2 (&V)[NE], const Cols &m, bool live) {
+  constexpr int NP = pow2_up(NE);
+  if constexpr (VEC)
+#pragma unroll
+    for (int i = 0; i < NE; i++) V[i] = make_double2(i == m.j ? 1.0 : 0.0, 0.0);
+  for (int sweep = 0; sweep < kMaxSweeps; sweep++) {
+    double off = 0.0, tot = 0.0;
+#pragma unroll
+    for (int i = 0; i < NE; i++) {
+      const double a2 = A[i].x * A[i].x + A[i].y * A[i].y;
+      off += (i != m.j) ? a2 : 0.0;
+      tot += a2;
+    }
+#pragma unroll
+    for (int d = 1; d < NP; d <<= 1) {
+      off += __shfl_xor(off, d, 64);
+      tot += __shfl_xor(tot, d, 64);
+    }
+    const bool done = (off == 0.0) || (off <= 1e-33 * tot) || !live;
+    // matrices settle in runs of 64 / NP^2, so that a point's rotations do not
+    // depend on how many matrices share a wave
+    constexpr int G = 64 / NP;
+    const unsigned long long open = __ballot(!done);
+    if (open == 0) break;
+    const unsigned long long mine = (G == 64 ? ~0ull : (1ull << G % 64) - 1) << ((threadIdx.x & 63) / G * G % 64);
+    if (open & mine) jacobi_sweep<NE, NP, VEC>(A, V, m, std::make_integer_sequence<int, NP - 1>());
+  }
+}
 
 // Outputs of the eigensolve, shared by both Bloch-sum forms.
 struct EigOut {
-  int mode, n;
   int64_t n2;  // points per plane
   const double *mode_mass;
   double cph, omega_cut, vel_unit;
@@ -58,327 +196,266 @@ struct EigOut {
   unsigned long long *n_excluded;
 };
 
-// Parallel cyclic Jacobi on the matrices of one wave (element (i, j) of
-// matrix mloc in each lane, acc its value, d0..d2 its k-derivatives), then
-// eigenvalues sorted ascending, eigenvectors (or mode amplitudes) and
-// velocities written for grid point kl.  The wave is the whole workgroup.
-template <int NP>
-__device__ __forceinline__ void eig_store(const EigOut &o, bool live, int64_t kl, double2 acc, double2 d0,
-                                          double2 d1, double2 d2, double2 *sA, double2 *sV, Rot *sR, double *sW) {
-  constexpr int L = NP * NP;
-  const int mode = o.mode, n = o.n;
-  const int lane = threadIdx.x;
-  const int e = lane % L;
-  const int i = e / NP, j = e % NP;
-  const bool valid_ij = (i < n) && (j < n);
-  const int base = (lane / L) * L;
-    sA[lane] = valid_ij ? acc : make_double2(0.0, 0.0);
-    sV[lane] = make_double2(i == j ? 1.0 : 0.0, 0.0);
-    __syncthreads();
+// kElectrons: energies, eigenvectors, velocities; kPhonons: frequencies and
+// mode amplitudes; kEnergies: the electrons' energies alone.
+enum { kElectrons = 0, kPhonons = 1, kEnergies = 2 };
 
-    // ---- parallel cyclic Jacobi ----
-    for (int sweep = 0; sweep < kMaxSweeps; sweep++) {
-      double2 a = sA[lane];
-      double a2 = valid_ij ? (a.x * a.x + a.y * a.y) : 0.0;
-      double off = (i != j) ? a2 : 0.0, tot = a2;
+// One row block of a derivative matrix per wave, staged for its velocities;
+// matrices start 16 bytes apart in the banks.
+constexpr int stage_rows(int ne) { return ne < 4 ? ne : 4; }
+constexpr int stage_stride(int ne) { return stage_rows(ne) * ne + 1; }
+constexpr size_t stage_bytes(int ne) { return sizeof(double2) * (size_t)(64 / pow2_up(ne)) * stage_stride(ne); }
+
+// Eigenvalues sorted ascending, eigenvectors (or mode amplitudes) and
+// velocities of grid point kl from the column A of its matrix.  deriv(b, d)
+// gives the column of the matrix's derivative along b, lat(b, a) Cartesian
+// component a of that direction; stage is the wave's own.
+template <int NE, int MODE, class Deriv, class Lat>
+__device__ __forceinline__ void eig_store(const EigOut &o, bool live, int64_t kl, double2 (&A)[NE], const Cols &m,
+                                          double2 *stage, Deriv deriv, Lat lat) {
+  constexpr int NP = pow2_up(NE);
+  const int j = m.j;
+  double2 V[NE];
+  jacobi<NE, MODE != kEnergies>(A, V, m, live);
+  double wj = 0.0;
 #pragma unroll
-      for (int m = 1; m < L; m <<= 1) {
-        off += __shfl_xor(off, m, 64);
-        tot += __shfl_xor(tot, m, 64);
-      }
-      bool done = (off == 0.0) || (off <= 1e-33 * tot) || !live;
-      if (__all(done)) break;
-      for (int r = 0; r < NP - 1; r++) {
-        // rotation parameters: lane (p,q) with p<q, q = partner(p)
-        if (valid_ij && i < j && rr_partner<NP>(i, r) == j) {
-          double2 apq = sA[base + i * NP + j];
-          double g = sqrt(apq.x * apq.x + apq.y * apq.y);
-          Rot ro;
-          if (g == 0.0) {
-            ro.c = 1.0;
-            ro.se = make_double2(0.0, 0.0);
-          } else {
-            double app = sA[base + i * NP + i].x, aqq = sA[base + j * NP + j].x;
-            double theta = (aqq - app) / (2.0 * g);
-            double t = (theta >= 0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-            double c = 1.0 / sqrt(t * t + 1.0), s = t * c;
-            ro.c = c;
-            ro.se = make_double2(s * apq.x / g, s * apq.y / g);
-          }
-          sR[base + i] = ro;  // indexed by the smaller index of the pair
-        }
-        __syncthreads();
-        // J entries: J_pp = c, J_pq = s e, J_qp = -s conj(e), J_qq = c (p<q)
-        const int pi = rr_partner<NP>(i, r), pj = rr_partner<NP>(j, r);
-        const bool roti = (i < n) && (pi < n) && (pi != i);
-        const bool rotj = (j < n) && (pj < n) && (pj != j);
-        // column factors J_{b j} for b in {j, pj}
-        double2 Jjj = make_double2(1.0, 0.0), Jpj = make_double2(0.0, 0.0);
-        if (rotj) {
-          Rot ro = sR[base + min(j, pj)];
-          Jjj = make_double2(ro.c, 0.0);
-          if (j > pj) Jpj = ro.se;                                  // J_{p q} with p=pj<q=j
-          else Jpj = make_double2(-ro.se.x, ro.se.y);               // J_{q p} = -conj(se)
-        }
-        double2 Jii = make_double2(1.0, 0.0), Jpi = make_double2(0.0, 0.0);
-        if (roti) {
-          Rot ro = sR[base + min(i, pi)];
-          Jii = make_double2(ro.c, 0.0);
-          if (i > pi) Jpi = ro.se;
-          else Jpi = make_double2(-ro.se.x, ro.se.y);
-        }
-        double2 nA = make_double2(0.0, 0.0), nV = make_double2(0.0, 0.0);
-        if (valid_ij) {
-          // (J^H A J)_ij = sum_{a in {i,pi}} sum_{b in {j,pj}} conj(J_ai) A_ab J_bj
-          double2 Aij = sA[base + i * NP + j];
-          double2 col_i = cmul(Aij, Jjj);
-          if (rotj) col_i = cadd(col_i, cmul(sA[base + i * NP + pj], Jpj));
-          nA = cmul(cconj(Jii), col_i);
-          if (roti) {
-            double2 col_p = cmul(sA[base + pi * NP + j], Jjj);
-            if (rotj) col_p = cadd(col_p, cmul(sA[base + pi * NP + pj], Jpj));
-            nA = cadd(nA, cmul(cconj(Jpi), col_p));
-          }
-          nV = cmul(sV[base + i * NP + j], Jjj);
-          if (rotj) nV = cadd(nV, cmul(sV[base + i * NP + pj], Jpj));
-          if (i != j && pi == j && roti) nA = make_double2(0.0, 0.0);  // annihilated pair
-          if (i == j) nA.y = 0.0;
-        } else {
-          nV = sV[lane];
-        }
-        __syncthreads();
-        sA[lane] = nA;
-        sV[lane] = nV;
-        __syncthreads();
-      }
-    }
-
-    // ---- sort eigenvalues ascending; lane (i,j) carries column j ----
-    if (lane < 64 && i == 0) sW[base + j] = (j < n) ? sA[base + j * NP + j].x : 0.0;
-    __syncthreads();
-    int rank = 0;
-    double wj = sW[base + j];
-    for (int jj = 0; jj < n; jj++) {
-      double wo = sW[base + jj];
-      rank += (wo < wj) || (wo == wj && jj < j);
-    }
-    if (live && valid_ij) {
-      const int64_t kk = kl;
-      double2 v = sV[base + i * NP + j];
-      if (mode == 0) {
-        if (i == 0) o.eval[plane_at(kk, rank, n, o.n2)] = wj;
-        o.evec[plane_at(kk, rank * n + i, n * n, o.n2)] = v;
-      } else {
-        double hw = sqrt(o.cph * fmax(wj, 0.0));
-        if (i == 0) {
-          o.eval[plane_at(kk, rank, n, o.n2)] = hw;
-          if (hw < o.omega_cut) atomicAdd(o.n_excluded, 1ull);
-        }
+  for (int i = 0; i < NE; i++) wj = (i == j) ? A[i].x : wj;
+  int rank = 0;
+#pragma unroll
+  for (int i = 0; i < NE; i++) {
+    const double wo = lane_get(wj, m.base4 + 4 * i);
+    rank += (wo < wj) || (wo == wj && i < j);
+  }
+  const bool on = live && j < NE;
+  if constexpr (MODE == kPhonons) {
+    const double hw = sqrt(o.cph * fmax(wj, 0.0));
+    if (on) {
+      o.eval[plane_at(kl, rank, NE, o.n2)] = hw;
+      if (hw < o.omega_cut) atomicAdd(o.n_excluded, 1ull);
+#pragma unroll
+      for (int i = 0; i < NE; i++) {
         double2 u = make_double2(0.0, 0.0);
         if (hw >= o.omega_cut) {
-          double f = sqrt(o.cph / (2.0 * o.mode_mass[i] * hw));
-          u = make_double2(v.x * f, v.y * f);
+          const double f = sqrt(o.cph / (2.0 * o.mode_mass[i] * hw));
+          u = make_double2(V[i].x * f, V[i].y * f);
         }
-        o.evec[plane_at(kk, rank * n + i, n * n, o.n2)] = u;  // u_{mu nu} at nu n + mu
+        o.evec[plane_at(kl, rank * NE + i, NE * NE, o.n2)] = u;  // u_{mu nu} at nu n + mu
       }
     }
-    if (mode == 0) {
-      // velocities: v_col = Re sum_ij conj(V_i,col) dH_ij V_j,col, butterfly over the matrix lanes
-      for (int col = 0; col < n; col++) {
-        double c0 = 0.0, c1 = 0.0, c2 = 0.0;
-        if (valid_ij) {
-          double2 vi = sV[base + i * NP + col], vj = sV[base + j * NP + col];
-          double2 pr = cmul(cconj(vi), vj);  // conj(V_i) V_j
-          c0 = pr.x * d0.x - pr.y * d0.y;
-          c1 = pr.x * d1.x - pr.y * d1.y;
-          c2 = pr.x * d2.x - pr.y * d2.y;
-        }
+  } else {
+    if (on) {
+      o.eval[plane_at(kl, rank, NE, o.n2)] = wj;
+      if constexpr (MODE == kElectrons)
 #pragma unroll
-        for (int m = 1; m < L; m <<= 1) {
-          c0 += __shfl_xor(c0, m, 64);
-          c1 += __shfl_xor(c1, m, 64);
-          c2 += __shfl_xor(c2, m, 64);
-        }
-        int rk = 0;
-        double wc = sW[base + col];
-        for (int jj = 0; jj < n; jj++) {
-          double wo = sW[base + jj];
-          rk += (wo < wc) || (wo == wc && jj < col);
-        }
-        if (live && e == 0) {
-          double *vo = o.vel + (kl * n + rk) * 3;
-          vo[0] = c0 * o.vel_unit;
-          vo[1] = c1 * o.vel_unit;
-          vo[2] = c2 * o.vel_unit;
-        }
-      }
+        for (int i = 0; i < NE; i++) o.evec[plane_at(kl, rank * NE + i, NE * NE, o.n2)] = V[i];
     }
-  __syncthreads();
+  }
+  if constexpr (MODE == kElectrons) {
+    // velocities: Re sum_ij conj(V_i) dH_ij V_j of the lane's own column V,
+    // dH by blocks of rows through LDS
+    constexpr int RB = stage_rows(NE);
+    double v0 = 0.0, v1 = 0.0, v2 = 0.0;
+    double2 *sm = stage + (m.base4 / 4 / NP) * stage_stride(NE);
+#pragma unroll 1
+    for (int b = 0; b < 3; b++) {
+      double2 d[NE];
+      deriv(b, d);
+      double u = 0.0;
+#pragma unroll
+      for (int r = 0; r < NE; r += RB) {
+        if (j < NE)
+#pragma unroll
+          for (int i = 0; i < RB; i++) sm[i * NE + j] = d[r + i];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < RB; i++) {
+          double yr = 0.0, yi = 0.0;
+#pragma unroll
+          for (int c = 0; c < NE; c++) {
+            const double2 h = sm[i * NE + c];
+            cmac<double>(yr, yi, h.x, h.y, V[c].x, V[c].y);
+          }
+          u = fma(V[r + i].x, yr, u);
+          u = fma(V[r + i].y, yi, u);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+      v0 = fma(lat(b, 0), u, v0);
+      v1 = fma(lat(b, 1), u, v1);
+      v2 = fma(lat(b, 2), u, v2);
+    }
+    if (on) {
+      double *vo = o.vel + (kl * NE + rank) * 3;
+      vo[0] = v0 * o.vel_unit;
+      vo[1] = v1 * o.vel_unit;
+      vo[2] = v2 * o.vel_unit;
+    }
+  }
 }
 
-template <int NP>
-__global__ __launch_bounds__(64) void bloch_eig_kernel(EigOut o, int N, int64_t k0, int64_t nk, int nr,
+template <int NE, int MODE>
+__global__ __launch_bounds__(64) void bloch_eig_kernel(EigOut o, int N, int64_t nk, int nr,
                                                        const int *__restrict__ R, const double *__restrict__ w,
                                                        const double *__restrict__ Rcart,
                                                        const double2 *__restrict__ M,
                                                        const double2 *__restrict__ tab) {
-  constexpr int L = NP * NP;
-  constexpr int MPW = 64 / L;
-  __shared__ double2 sA[64];
-  __shared__ double2 sV[64];
-  __shared__ Rot sR[64];
-  __shared__ double sW[64];
-  const int mode = o.mode, n = o.n;
+  constexpr int NP = pow2_up(NE), MPW = 64 / NP;
+  __shared__ double2 stage[MODE == kElectrons ? stage_bytes(NE) / sizeof(double2) : 1];
   const int lane = threadIdx.x;
-  const int mloc = lane / L;
-  const int e = lane % L;
-  const int i = e / NP, j = e % NP;
-  const bool valid_ij = (i < n) && (j < n);
+  const Cols m{lane % NP, 4 * (lane / NP * NP)};
+  const int jc = min(m.j, NE - 1);
 
   const int64_t ngroups = (nk + MPW - 1) / MPW;
   for (int64_t gidx = blockIdx.x; gidx < ngroups; gidx += gridDim.x) {
-    const int64_t kl = gidx * MPW + mloc;
+    const int64_t kl = gidx * MPW + lane / NP;
     const bool live = kl < nk;
-    const int64_t kg = k0 + (live ? kl : 0);
+    const int64_t kg = live ? kl : 0;
     const int64_t k1 = kg % N, k2 = (kg / N) % N, k3 = kg / ((int64_t)N * N);
-
-    // ---- Bloch sum (and derivatives for electrons), direct over the R list ----
-    double2 acc = make_double2(0.0, 0.0);
-    double2 d0 = acc, d1 = acc, d2 = acc;
-    if (valid_ij) {
+    // ---- Bloch sum, direct over the R list ----
+    auto phase = [&](int r) {
+      int64_t s = (k1 * R[3 * r] + k2 * R[3 * r + 1] + k3 * R[3 * r + 2]) % N;
+      if (s < 0) s += N;
+      double2 ph = tab[s];
+      const double wr = w[r];
+      ph.x *= wr;
+      ph.y *= wr;
+      return ph;
+    };
+    double2 A[NE];
+#pragma unroll
+    for (int i = 0; i < NE; i++) A[i] = make_double2(0.0, 0.0);
+    if (m.j < NE)
       for (int r = 0; r < nr; r++) {
-        int64_t s = (k1 * R[3 * r] + k2 * R[3 * r + 1] + k3 * R[3 * r + 2]) % N;
-        if (s < 0) s += N;
-        double2 ph = tab[s];
-        double wr = w[r];
-        ph.x *= wr;
-        ph.y *= wr;
-        double2 t = cmul(ph, M[(size_t)r * n * n + i * n + j]);
-        acc = cadd(acc, t);
-        if (mode == 0) {
-          // i * R_a * t
-          double2 it = make_double2(-t.y, t.x);
-          double r0 = Rcart[3 * r], r1 = Rcart[3 * r + 1], r2 = Rcart[3 * r + 2];
-          d0.x += r0 * it.x; d0.y += r0 * it.y;
-          d1.x += r1 * it.x; d1.y += r1 * it.y;
-          d2.x += r2 * it.x; d2.y += r2 * it.y;
+        const double2 ph = phase(r);
+#pragma unroll
+        for (int i = 0; i < NE; i++) A[i] = cadd(A[i], cmul(ph, M[(size_t)r * NE * NE + i * NE + jc]));
+      }
+    // i R_a times the terms of the sum
+    auto deriv = [&](int a, double2(&d)[NE]) {
+#pragma unroll
+      for (int i = 0; i < NE; i++) d[i] = make_double2(0.0, 0.0);
+      for (int r = 0; r < nr; r++) {
+        const double2 ph = phase(r);
+        const double ra = Rcart[3 * r + a];
+#pragma unroll
+        for (int i = 0; i < NE; i++) {
+          const double2 t = cmul(ph, M[(size_t)r * NE * NE + i * NE + jc]);
+          d[i].x -= ra * t.y;
+          d[i].y += ra * t.x;
         }
       }
-    }
-    eig_store<NP>(o, live, kl, acc, d0, d1, d2, sA, sV, sR, sW);
+    };
+    eig_store<NE, MODE>(o, live, kl, A, m, stage, deriv, [](int b, int a) { return b == a ? 1.0 : 0.0; });
   }
 }
 
 // Separable form of the same Bloch sum for R lists that fill a box
 // [lo, lo + nb) (missing vectors are zero in the dense copy Mb, weights
-// folded in).  One wave per k-line (k2, k3): every lane first sums its
-// element over the (R2, R3) planes for each R1,
+// folded in).  One workgroup per k-line (k2, k3): its threads first sum the
+// elements over the (R2, R3) planes for each R1,
 //   T0(R1) = sum_{R2,R3} e^{i2pi(k2 R2 + k3 R3)/N} M(R),  T2, T3 the same
 //   weighted by R2, R3 (electrons),
-// in registers, then per k1 on the line
+// into LDS, then per k1 on the line
 //   M(k) = sum_R1 e^{i2pi k1 R1/N} T0(R1),  S1 = sum_R1 R1 e^{..} T0(R1),
 //   S2, S3 = sum_R1 e^{..} T2,3(R1),  dM/dk_a = i sum_b L_ba S_b
 // (L the lattice vectors as rows), which is the direct sum associated
-// differently.  NR1 bounds the box length along R1.
+// differently.
 struct BoxArgs {
   int lo[3], nb[3];
   double lat[9];
 };
 
-template <int NP, int NR1, int MODE>
-__global__ __launch_bounds__(64) void bloch_line_kernel(EigOut o, int N, BoxArgs bx, const double2 *__restrict__ Mb,
-                                                        const double2 *__restrict__ tab) {
-  constexpr int NRD = MODE == 0 ? NR1 : 1;  // derivative planes only for electrons
-  constexpr int L = NP * NP;
-  constexpr int MPW = 64 / L;
-  __shared__ double2 sA[64];
-  __shared__ double2 sV[64];
-  __shared__ Rot sR[64];
-  __shared__ double sW[64];
-  constexpr int mode = MODE;
-  const int n = o.n;
-  const int lane = threadIdx.x;
-  const int mloc = lane / L;
-  const int e = lane % L;
-  const int i = e / NP, j = e % NP;
-  const bool valid_ij = (i < n) && (j < n);
+constexpr int kLineWaves = 4;  // most waves per workgroup
+
+template <int NE, int MODE>
+__global__ __launch_bounds__(64 * kLineWaves) void bloch_line_kernel(EigOut o, int N, BoxArgs bx,
+                                                                     const double2 *__restrict__ Mb,
+                                                                     const double2 *__restrict__ tab) {
+  constexpr int NP = pow2_up(NE), MPW = 64 / NP, NN = NE * NE;
+  extern __shared__ __align__(16) double2 sm[];
   const int n1 = bx.nb[0], n2 = bx.nb[1], n3 = bx.nb[2];
-  const size_t nn = (size_t)n * n;
-  const int64_t nlines = (int64_t)N * N;
-  for (int64_t line = blockIdx.x; line < nlines; line += gridDim.x) {
-    const int k2 = (int)(line % N), k3 = (int)(line / N);
-    double2 T0[NR1], T2[NRD], T3[NRD];
-#pragma unroll
-    for (int b = 0; b < NR1; b++) T0[b] = make_double2(0.0, 0.0);
-#pragma unroll
-    for (int b = 0; b < NRD; b++) T2[b] = T3[b] = make_double2(0.0, 0.0);
-    if (valid_ij) {
-      int i2 = imod(k2 * bx.lo[1], N);
-      const int i3s = imod(k3 * bx.lo[2], N);
-      for (int b2 = 0; b2 < n2; b2++) {
-        const double r2 = (double)(bx.lo[1] + b2);
-        int i23 = i2 + i3s;
-        i23 -= (i23 >= N) ? N : 0;
-        for (int b3 = 0; b3 < n3; b3++) {
-          const double2 ph = tab[i23];
+  double2 *sT = sm;                                          // [T0, T2, T3][n1][NN]
+  double2 *stage = sm + (MODE == kElectrons ? 3 : 1) * n1 * NN + threadIdx.x / 64 * (int)(stage_bytes(NE) / sizeof(double2));
+  const int k2 = (int)(blockIdx.x % N), k3 = (int)(blockIdx.x / N);
+  for (int x = threadIdx.x; x < n1 * NN; x += blockDim.x) {
+    const double2 *mx = Mb + (size_t)(x / NN) * n2 * n3 * NN + x % NN;
+    double2 t0 = make_double2(0.0, 0.0), t2 = t0, t3 = t0;
+    int i2 = imod(k2 * bx.lo[1], N);
+    const int i3s = imod(k3 * bx.lo[2], N);
+    for (int b2 = 0; b2 < n2; b2++) {
+      const double r2 = (double)(bx.lo[1] + b2);
+      int i23 = i2 + i3s;
+      i23 -= (i23 >= N) ? N : 0;
+      for (int b3 = 0; b3 < n3; b3++) {
+        const double2 t = cmul(tab[i23], mx[((size_t)b2 * n3 + b3) * NN]);
+        t0 = cadd(t0, t);
+        if constexpr (MODE == kElectrons) {
           const double r3 = (double)(bx.lo[2] + b3);
-          const double2 *m = Mb + ((size_t)b2 * n3 + b3) * nn + i * n + j;
-#pragma unroll
-          for (int b1 = 0; b1 < NR1; b1++) {
-            if (b1 < n1) {
-              const double2 t = cmul(ph, m[(size_t)b1 * n2 * n3 * nn]);
-              T0[b1] = cadd(T0[b1], t);
-              if constexpr (MODE == 0) {
-                T2[b1].x = fma(r2, t.x, T2[b1].x);
-                T2[b1].y = fma(r2, t.y, T2[b1].y);
-                T3[b1].x = fma(r3, t.x, T3[b1].x);
-                T3[b1].y = fma(r3, t.y, T3[b1].y);
-              }
-            }
-          }
-          i23 += k3;
-          i23 -= (i23 >= N) ? N : 0;
+          t2.x = fma(r2, t.x, t2.x);
+          t2.y = fma(r2, t.y, t2.y);
+          t3.x = fma(r3, t.x, t3.x);
+          t3.y = fma(r3, t.y, t3.y);
         }
-        i2 += k2;
-        i2 -= (i2 >= N) ? N : 0;
+        i23 += k3;
+        i23 -= (i23 >= N) ? N : 0;
       }
+      i2 += k2;
+      i2 -= (i2 >= N) ? N : 0;
     }
-    for (int kb = 0; kb < N; kb += MPW) {
-      const int k1r = kb + mloc;
-      const bool live = k1r < N;
-      const int k1 = live ? k1r : 0;
-      double2 acc = make_double2(0.0, 0.0), s1 = acc, s2 = acc, s3 = acc;
-      if (valid_ij) {
-        int i1 = imod(k1 * bx.lo[0], N);
+    sT[x] = t0;
+    if constexpr (MODE == kElectrons) {
+      sT[n1 * NN + x] = t2;
+      sT[2 * n1 * NN + x] = t3;
+    }
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const Cols m{lane % NP, 4 * (lane / NP * NP)};
+  const int jc = min(m.j, NE - 1);
+  // waves take MPW points at a time
+  for (int kb = threadIdx.x / 64 * MPW; kb < N; kb += (int)blockDim.x / 64 * MPW) {
+    const int k1r = kb + lane / NP;
+    const bool live = k1r < N;
+    const int k1 = live ? k1r : 0;
+    const int i1s = imod(k1 * bx.lo[0], N);
+    double2 A[NE];
 #pragma unroll
-        for (int b1 = 0; b1 < NR1; b1++) {
-          if (b1 < n1) {
-            const double2 ph = tab[i1];
-            const double2 t = cmul(ph, T0[b1]);
-            acc = cadd(acc, t);
-            if constexpr (MODE == 0) {
-              const double r1 = (double)(bx.lo[0] + b1);
-              s1.x = fma(r1, t.x, s1.x);
-              s1.y = fma(r1, t.y, s1.y);
-              s2 = cadd(s2, cmul(ph, T2[b1]));
-              s3 = cadd(s3, cmul(ph, T3[b1]));
-            }
-            i1 += k1;
-            i1 -= (i1 >= N) ? N : 0;
-          }
+    for (int i = 0; i < NE; i++) A[i] = make_double2(0.0, 0.0);
+    int i1 = i1s;
+    for (int b1 = 0; b1 < n1; b1++) {
+      const double2 ph = tab[i1];
+#pragma unroll
+      for (int i = 0; i < NE; i++) A[i] = cadd(A[i], cmul(ph, sT[b1 * NN + i * NE + jc]));
+      i1 += k1;
+      i1 -= (i1 >= N) ? N : 0;
+    }
+    if (m.j >= NE)
+#pragma unroll
+      for (int i = 0; i < NE; i++) A[i] = make_double2(0.0, 0.0);
+    auto deriv = [&](int b, double2(&d)[NE]) {  // i S_b
+#pragma unroll
+      for (int i = 0; i < NE; i++) d[i] = make_double2(0.0, 0.0);
+      int i1 = i1s;
+      for (int b1 = 0; b1 < n1; b1++) {
+        double2 ph = tab[i1];
+        if (b == 0) {
+          const double r1 = (double)(bx.lo[0] + b1);
+          ph = make_double2(r1 * ph.x, r1 * ph.y);
         }
-      }
-      double2 d[3];
 #pragma unroll
-      for (int a = 0; a < 3; a++) {
-        // i * sum_b L_ba S_b
-        const double re = bx.lat[a] * s1.x + bx.lat[3 + a] * s2.x + bx.lat[6 + a] * s3.x;
-        const double im = bx.lat[a] * s1.y + bx.lat[3 + a] * s2.y + bx.lat[6 + a] * s3.y;
-        d[a] = make_double2(-im, re);
+        for (int i = 0; i < NE; i++) {
+          const double2 t = cmul(ph, sT[((b == 0 ? 0 : b) * n1 + b1) * NN + i * NE + jc]);
+          d[i].x -= t.y;
+          d[i].y += t.x;
+        }
+        i1 += k1;
+        i1 -= (i1 >= N) ? N : 0;
       }
-      const int64_t kl = (int64_t)k1 + (int64_t)N * line;
-      eig_store<NP>(o, live, kl, acc, d[0], d[1], d[2], sA, sV, sR, sW);
-    }
+    };
+    eig_store<NE, MODE>(o, live, (int64_t)k1 + (int64_t)N * blockIdx.x, A, m, stage, deriv,
+                        [&](int b, int a) { return bx.lat[3 * b + a]; });
   }
 }
 
@@ -398,34 +475,53 @@ hipError_t launch_phase_table(int N, double2 *tab, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_bloch_eig(int mode, int n, int N, int64_t k0, int64_t nk, int nr, const int *R,
-                            const double *w, const double *Rcart, const double2 *M, const double2 *tab,
-                            const double *mode_mass, double cph, double omega_cut, double vel_unit,
-                            double *eval, double2 *evec, double *vel, unsigned long long *n_excluded,
-                            hipStream_t st) {
-  if (nk <= 0) return hipSuccess;
-  const EigOut o{mode, n, (int64_t)N * N, mode_mass, cph, omega_cut, vel_unit, eval, evec, vel, n_excluded};
-  int NP = n <= 1 ? 1 : n <= 2 ? 2 : n <= 4 ? 4 : 8;
-  int mpw = 64 / (NP * NP);
-  int64_t ngroups = (nk + mpw - 1) / mpw;
-  int grid = (int)(ngroups < 262144 ? ngroups : 262144);
-#define EPH_LAUNCH_BE(NPV) \
-  hipLaunchKernelGGL(bloch_eig_kernel<NPV>, dim3(grid), dim3(64), 0, st, o, N, k0, nk, nr, R, w, Rcart, M, tab)
-  switch (NP) {
-    case 1: EPH_LAUNCH_BE(1); break;
-    case 2: EPH_LAUNCH_BE(2); break;
-    case 4: EPH_LAUNCH_BE(4); break;
-    default: EPH_LAUNCH_BE(8); break;
+#define EPH_BLOCH_DISPATCH(GO) \
+  switch (mode) {              \
+    case kElectrons:           \
+      switch (n) {             \
+        GO(1, kElectrons)      \
+        GO(2, kElectrons)      \
+        GO(4, kElectrons)      \
+        GO(8, kElectrons)      \
+      }                        \
+      break;                   \
+    case kPhonons:             \
+      switch (n) {             \
+        GO(3, kPhonons)        \
+        GO(6, kPhonons)        \
+      }                        \
+      break;                   \
+    case kEnergies:            \
+      switch (n) {             \
+        GO(1, kEnergies)       \
+        GO(2, kEnergies)       \
+        GO(4, kEnergies)       \
+        GO(8, kEnergies)       \
+      }                        \
   }
-#undef EPH_LAUNCH_BE
-  return hipGetLastError();
+
+hipError_t launch_bloch_eig(int mode, int n, int N, int64_t nk, int nr, const int *R, const double *w,
+                            const double *Rcart, const double2 *M, const double2 *tab, const double *mode_mass,
+                            double cph, double omega_cut, double vel_unit, double *eval, double2 *evec, double *vel,
+                            unsigned long long *n_excluded, hipStream_t st) {
+  if (nk <= 0) return hipSuccess;
+  const EigOut o{(int64_t)N * N, mode_mass, cph, omega_cut, vel_unit, eval, evec, vel, n_excluded};
+  const int64_t ngroups = (nk * pow2_up(n) + 63) / 64;
+  const int grid = (int)(ngroups < 262144 ? ngroups : 262144);
+#define EPH_GO(NE, MODE)                                                                                             \
+  case NE:                                                                                                           \
+    hipLaunchKernelGGL((bloch_eig_kernel<NE, MODE>), dim3(grid), dim3(64), 0, st, o, N, nk, nr, R, w, Rcart, M, tab); \
+    return hipGetLastError();
+  EPH_BLOCH_DISPATCH(EPH_GO)
+#undef EPH_GO
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_bloch_lines(int mode, int n, int N, const int *lo, const int *nb, const double *lattice,
                               const double2 *Mb, const double2 *tab, const double *mode_mass, double cph,
                               double omega_cut, double vel_unit, double *eval, double2 *evec, double *vel,
                               unsigned long long *n_excluded, hipStream_t st) {
-  const EigOut o{mode, n, (int64_t)N * N, mode_mass, cph, omega_cut, vel_unit, eval, evec, vel, n_excluded};
+  const EigOut o{(int64_t)N * N, mode_mass, cph, omega_cut, vel_unit, eval, evec, vel, n_excluded};
   if (nb[0] > kBoxMaxR1) return hipErrorInvalidValue;
   BoxArgs bx;
   for (int a = 0; a < 3; a++) {
@@ -433,25 +529,21 @@ hipError_t launch_bloch_lines(int mode, int n, int N, const int *lo, const int *
     bx.nb[a] = nb[a];
   }
   for (int a = 0; a < 9; a++) bx.lat[a] = lattice[a];
-  const int NP = n <= 1 ? 1 : n <= 2 ? 2 : n <= 4 ? 4 : 8;
-  const int64_t nlines = (int64_t)N * N;
-  const int grid = (int)(nlines < 262144 ? nlines : 262144);
-#define EPH_LAUNCH_BL(NPV, R1)                                                                               \
-  if (mode == 0) hipLaunchKernelGGL((bloch_line_kernel<NPV, R1, 0>), dim3(grid), dim3(64), 0, st, o, N, bx, Mb, tab); \
-  else hipLaunchKernelGGL((bloch_line_kernel<NPV, R1, 1>), dim3(grid), dim3(64), 0, st, o, N, bx, Mb, tab);       \
-  return hipGetLastError();
-#define EPH_LAUNCH_NP(R1)        \
-  switch (NP) {                  \
-    case 1: EPH_LAUNCH_BL(1, R1) \
-    case 2: EPH_LAUNCH_BL(2, R1) \
-    case 4: EPH_LAUNCH_BL(4, R1) \
-    default: EPH_LAUNCH_BL(8, R1) \
+  const int waves = std::min(kLineWaves, (N * pow2_up(n) + 63) / 64);
+  const size_t sh = sizeof(double2) * (mode == kElectrons ? 3 : 1) * nb[0] * n * n +
+                    (mode == kElectrons ? waves * stage_bytes(n) : 0);
+#define EPH_GO(NE, MODE)                                                                                            \
+  case NE: {                                                                                                        \
+    auto kern = bloch_line_kernel<NE, MODE>;                                                                        \
+    const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh); \
+    if (e != hipSuccess) return e;                                                                                  \
+    hipLaunchKernelGGL(kern, dim3((unsigned)(N * N)), dim3(64 * waves), sh, st, o, N, bx, Mb, tab);                 \
+    return hipGetLastError();                                                                                       \
   }
-  if (nb[0] <= 7) EPH_LAUNCH_NP(7)
-  if (nb[0] <= 9) EPH_LAUNCH_NP(9)
-  EPH_LAUNCH_NP(kBoxMaxR1)
-#undef EPH_LAUNCH_NP
-#undef EPH_LAUNCH_BL
+  EPH_BLOCH_DISPATCH(EPH_GO)
+#undef EPH_GO
+  return hipErrorInvalidValue;
 }
+#undef EPH_BLOCH_DISPATCH
 
 }  // namespace eph

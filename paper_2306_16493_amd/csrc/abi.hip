@@ -26,13 +26,19 @@ Units units() {
 
 // Electron tables (eps, V, v on the N^3 grid): the separable Bloch sum
 // when the H(R) list has a dense box, else the direct sum over the list.
-hipError_t electron_tables(eph_ctx *c, int N, const Units &U, hipStream_t st) {
+// energies_only leaves out V and v.
+hipError_t electron_tables(eph_ctx *c, int N, const Units &U, bool energies_only, hipStream_t st) {
   const int64_t NQ = (int64_t)N * N * N;
+  const int mode = energies_only ? 2 : 0;
+  hipError_t e = c->eps.ensure(sizeof(double) * NQ * c->nw);
+  if (e == hipSuccess && !energies_only) e = c->evec.ensure(sizeof(double2) * NQ * c->nw * c->nw);
+  if (e == hipSuccess && !energies_only) e = c->vel.ensure(sizeof(double) * NQ * c->nw * 3);
+  if (e != hipSuccess) return e;
   if (c->hbox_n[0] > 0)
-    return launch_bloch_lines(0, c->nw, N, c->hbox_lo, c->hbox_n, c->lattice, c->hbox.as<double2>(),
+    return launch_bloch_lines(mode, c->nw, N, c->hbox_lo, c->hbox_n, c->lattice, c->hbox.as<double2>(),
                               c->tab.as<double2>(), nullptr, U.cph_ev, 0.0, U.vel_unit, c->eps.as<double>(),
                               c->evec.as<double2>(), c->vel.as<double>(), nullptr, st);
-  return launch_bloch_eig(0, c->nw, N, NQ, c->nrh, c->rh.as<int>(), c->rh_w.as<double>(), c->rh_cart.as<double>(),
+  return launch_bloch_eig(mode, c->nw, N, NQ, c->nrh, c->rh.as<int>(), c->rh_w.as<double>(), c->rh_cart.as<double>(),
                           c->ham.as<double2>(), c->tab.as<double2>(), nullptr, U.cph_ev, 0.0, U.vel_unit,
                           c->eps.as<double>(), c->evec.as<double2>(), c->vel.as<double>(), nullptr, st);
 }
@@ -458,9 +464,6 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
 
   // ---- grid tables: electrons and phonons on the full grid ----
   EPH_HIP(c, c->tab.ensure(sizeof(double2) * N));
-  EPH_HIP(c, c->eps.ensure(sizeof(double) * NQ * nw));
-  EPH_HIP(c, c->evec.ensure(sizeof(double2) * NQ * nw * nw));
-  EPH_HIP(c, c->vel.ensure(sizeof(double) * NQ * nw * 3));
   EPH_HIP(c, c->om.ensure(sizeof(double) * NQ * nm));
   EPH_HIP(c, c->uu.ensure(sizeof(double2) * NQ * nm * nm));
   EPH_HIP(c, c->counters.ensure(sizeof(unsigned long long) * 8));
@@ -469,8 +472,13 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
   //      6 vertex contractions
   EPH_HIP(c, launch_zero(ctr, sizeof(unsigned long long) * 8, st));
   EPH_HIP(c, launch_phase_table(N, c->tab.as<double2>(), st));
-  EPH_HIP(c, electron_tables(c, N, U, st));
-  EPH_HIP(c, phonon_tables(c, N, U, p->omega_cut_eV, ctr + 0, st));
+  // A call without room for a state counts them, for which the energies do
+  // (Si-like 130^3, 0.15 % of the states: 105 ms a call for 119); a list of the states needs no
+  // phonons.  Without a state in the window the excluded modes are still
+  // counted, below.
+  const bool count_only = capacity == 0, list_only = states_only && !gr;
+  EPH_HIP(c, electron_tables(c, N, U, count_only, st));
+  if (!count_only && !list_only) EPH_HIP(c, phonon_tables(c, N, U, p->omega_cut_eV, ctr + 0, st));
   const bool fp32 = p->precision != EPH_FP64;
   EPH_HIP(c, tm.mark(&e_tables));
 
@@ -500,7 +508,8 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
   }
   EPH_HIP(c, launch_write_states(nkl, d_klist, N, nw, c->eps.as<double>(), c->vel.as<double>(), blo, bhi, p->win_lo_eV,
                                  p->win_hi_eV, c->offs.as<int64_t>(), state_k, state_n, energy_eV, vel_ms, st));
-  if (states_only && !gr) {
+  if (count_only && !list_only) EPH_HIP(c, phonon_tables(c, N, U, p->omega_cut_eV, ctr + 0, st));
+  if (list_only) {
     EPH_HIP(c, hipStreamSynchronize(st));
     if (counts) *counts = cn;
     return EPH_OK;
@@ -1291,11 +1300,8 @@ int32_t eph_carrier_density(eph_ctx *c, int32_t grid, int32_t band_lo, int32_t b
   const int64_t NQ = (int64_t)N * N * N;
   // band energies on the full grid (the electron half of the grid tables)
   EPH_HIP(c, c->tab.ensure(sizeof(double2) * N));
-  EPH_HIP(c, c->eps.ensure(sizeof(double) * NQ * nw));
-  EPH_HIP(c, c->evec.ensure(sizeof(double2) * NQ * nw * nw));
-  EPH_HIP(c, c->vel.ensure(sizeof(double) * NQ * nw * 3));
   EPH_HIP(c, launch_phase_table(N, c->tab.as<double2>(), st));
-  EPH_HIP(c, electron_tables(c, N, U, st));
+  EPH_HIP(c, electron_tables(c, N, U, true, st));
   const int nblk = 256;
   EPH_HIP(c, c->sig_part.ensure(sizeof(double) * ((size_t)nblk * EPH_MAX_TEMPS + 2 * EPH_MAX_TEMPS)));
   double *part = c->sig_part.as<double>();

@@ -18,12 +18,15 @@
 //                      vector units;
 //   mlp_adam_kernel    per parameter: the tile gradients summed in tile
 //                      order, then the Adam update;
-//   mlp_forward_kernel inference for all members;
+//   mlp_forward_kernel inference for all members, on the same tiles with the
+//                      hidden weights in registers;
 //   helpers for features, normalisation, ensemble blending and merging.
 // Minibatch indices are the high half of a counter-based hash (splitmix64 of
 // seed, member, step and position) times n, so training is reproducible for
 // a given seed.
 #include <math.h>
+
+#include <algorithm>
 
 #include "internal.h"
 
@@ -32,8 +35,6 @@ namespace mlp {
 
 constexpr int NIN = 10;  // features: (sin, cos)(2 pi k_i/N) x 3, eps - mu, v x 3
 constexpr int H = 128;
-constexpr int TS = 32;       // samples per workgroup tile (inference)
-constexpr int THREADS = 256;
 constexpr int MAXOUT = EPH_MAX_TEMPS;
 
 __host__ __device__ inline int64_t n_params(int nout) {
@@ -61,36 +62,17 @@ __device__ __forceinline__ unsigned long long splitmix64(unsigned long long x) {
   x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
   return x ^ (x >> 31);
 }
-// logistic function with the hardware exponential and reciprocal (a few ulp;
+// logistic function with the hardware exponential, and the hardware reciprocal
+// with one Newton step, which rounds like the quotient but for rare cases (a few ulp;
 // the network is fit in FP32 to a target far coarser than that)
-__device__ __forceinline__ float sigm(float z) { return __fdividef(1.0f, 1.0f + __expf(-z)); }
+__device__ __forceinline__ float sigm(float z) {
+  const float d = 1.0f + __expf(fminf(-z, 87.0f)), r = __builtin_amdgcn_rcpf(d);
+  return fmaf(fmaf(-d, r, 1.0f), r, r);  // 1 / d, d from 1 to 6.1e37
+}
 __device__ __forceinline__ float silu(float z) { return z * sigm(z); }
 __device__ __forceinline__ float dsilu(float z) {
   const float s = sigm(z);
   return s * (1.0f + z * (1.0f - s));
-}
-
-// out[s][o] = b[o] + sum_i W[o][i] in[s][i] for the TS samples; thread t
-// owns output column o = t % H for samples (t / H) * TS/2 ... + TS/2 - 1.
-__device__ void dense_fwd(const float *__restrict__ W, const float *__restrict__ b, const float *in, int nin,
-                          int in_stride, float *out, int nout) {
-  constexpr int SG = THREADS / H;  // 2 sample groups
-  constexpr int SPT = TS / SG;     // 16 samples per thread
-  const int t = threadIdx.x;
-  const int o = t % H, g = t / H;
-  if (o < nout) {
-    float acc[SPT];
-    const float bo = b[o];
-#pragma unroll
-    for (int j = 0; j < SPT; j++) acc[j] = bo;
-    for (int i = 0; i < nin; i++) {
-      const float w = W[(size_t)o * nin + i];
-#pragma unroll
-      for (int j = 0; j < SPT; j++) acc[j] = fmaf(w, in[(g * SPT + j) * in_stride + i], acc[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < SPT; j++) out[(g * SPT + j) * H + o] = acc[j];
-  }
 }
 
 // Training tile: TT samples per workgroup of TN threads (four waves).
@@ -517,42 +499,133 @@ __global__ void mlp_loss_kernel(int members, int tiles, const float *__restrict_
 }
 
 // Inference: y_out[member][s][n] = denormalised network output.
-__global__ __launch_bounds__(THREADS) void mlp_forward_kernel(int nout, int64_t n, const float *__restrict__ x,
-                                                              const float *__restrict__ params,
-                                                              const float *__restrict__ norm,
-                                                              float *__restrict__ y_out) {
-  __shared__ float sX[TS][NIN + 1];
-  __shared__ float sA[TS][H];
-  __shared__ float sB[TS][H];
+//
+// What bounds it: the matrix cores, in FP32 (437296 samples x 5 members: 151
+// GFLOP, 1.0 ms at the rate of a large product; 1.45 ms here, the rest mostly
+// SiLU).  The hidden weights do not pass through LDS: each of the eight waves
+// keeps its 16 columns of both matrices in registers (64 of them) and walks
+// over the tiles of one member with them; only activations are exchanged,
+// through two LDS buffers in turn, one barrier per layer.  On the vector
+// units, with the weights read from the caches per tile, it took 4.97 ms.
+constexpr int FS = 64;  // samples per tile
+constexpr int FM = FS / 16;
+constexpr int FN = 4 * H;  // threads: a wave per 16 columns
+
+// hidden layer: acc = b + a W^T for the wave's 16 columns, W in registers
+__device__ __forceinline__ void reg_layer(const Lane &L, const float4 (&w)[H / 16], float bias, const float *sA,
+                                          f4v (&acc)[FM]) {
+#pragma unroll
+  for (int st = 0; st < FM; st++) acc[st] = f4v{bias, bias, bias, bias};
+#pragma unroll
+  for (int kb = 0; kb < H / 16; kb++) {
+    float4 av[FM];
+#pragma unroll
+    for (int st = 0; st < FM; st++) av[st] = ld4(&sA[(16 * st + L.r16) * HP + 16 * kb + 4 * L.g]);
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+#pragma unroll
+      for (int st = 0; st < FM; st++) acc[st] = mfma(comp(av[st], r), comp(w[kb], r), acc[st]);
+    __builtin_amdgcn_sched_barrier(0);  // one step of loads in flight fits the registers
+  }
+}
+
+__global__ __launch_bounds__(FN) __attribute__((amdgpu_waves_per_eu(4)))
+void mlp_forward_kernel(int nout, int64_t n, int64_t tiles, const float *__restrict__ x,
+                        const float *__restrict__ params, const float *__restrict__ norm, float *__restrict__ y_out) {
+  __shared__ __align__(16) float sA[2][FS * HP];
+  __shared__ __align__(16) float sW4[MAXOUT * H];
+  __shared__ float sX[FS][4 * ((NIN + 3) / 4) + 1];
   const int member = blockIdx.y, t = threadIdx.x;
-  const int64_t s0 = (int64_t)blockIdx.x * TS;
   const int64_t P = n_params(nout);
   const Offs of = offsets(nout);
   const float *prm = params + (size_t)member * P;
   const float *xm = norm, *xs = norm + NIN, *ym = norm + 2 * NIN, *ys = norm + 2 * NIN + MAXOUT;
-  for (int e = t; e < TS * NIN; e += THREADS) {
-    const int s = e / NIN, i = e % NIN;
-    sX[s][i] = (s0 + s < n) ? (x[(s0 + s) * NIN + i] - xm[i]) / xs[i] : 0.0f;
+  const Lane L;
+  constexpr int KX = (NIN + 3) / 4;  // 4-deep steps over the inputs
+  for (int e = t; e < nout * H; e += FN) sW4[e] = prm[of.w4 + e];
+  // the wave's columns 16 w + r16 of the weights; inner index 16 kb + 4 g + r
+  // for the hidden layers, 4 ks + g for the first
+  const int col = 16 * L.w + L.r16;
+  float4 w2[H / 16], w3[H / 16];
+  float w1[KX];
+#pragma unroll
+  for (int kb = 0; kb < H / 16; kb++) {
+    const float *p2 = prm + of.w2 + (size_t)col * H + 16 * kb + 4 * L.g;  // any 4-byte alignment
+    const float *p3 = prm + of.w3 + (size_t)col * H + 16 * kb + 4 * L.g;
+    w2[kb] = make_float4(p2[0], p2[1], p2[2], p2[3]);
+    w3[kb] = make_float4(p3[0], p3[1], p3[2], p3[3]);
   }
+#pragma unroll
+  for (int ks = 0; ks < KX; ks++) w1[ks] = 4 * ks + L.g < NIN ? prm[of.w1 + (size_t)col * NIN + 4 * ks + L.g] : 0.0f;
+  const float b1 = prm[of.b1 + col], b2 = prm[of.b2 + col], b3 = prm[of.b3 + col];
+  const int k4 = min(L.r16, nout - 1);  // output of the lane's column (columns past nout are not stored)
+  const float b4 = prm[of.b4 + k4], scale = ys[k4], shift = ym[k4];
+  // the thread's share of a tile's inputs, consecutive in memory
+  constexpr int XE = (FS * NIN + FN - 1) / FN;
+  float xv[XE];
+  auto load_x = [&](int64_t tile) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < XE; j++) {
+      const int64_t e = tile * (FS * NIN) + t + FN * j;
+      xv[j] = x[min(e, n * NIN - 1)];
+    }
+  };
+  auto put_x = [&](int64_t tile) __attribute__((always_inline)) {  // normalised
+#pragma unroll
+    for (int j = 0; j < XE; j++) {
+      const int e = t + FN * j, s = e / NIN, i = e % NIN;
+      if (e < FS * NIN) sX[s][i] = tile * FS + s < n ? (xv[j] - xm[i]) / xs[i] : 0.0f;
+    }
+  };
+  if (t < FS)
+    for (int i = NIN; i < 4 * KX; i++) sX[t][i] = 0.0f;
+  f4v acc[FM];
+  auto put = [&](float *out) __attribute__((always_inline)) {
+#pragma unroll
+    for (int st = 0; st < FM; st++)
+#pragma unroll
+      for (int q = 0; q < 4; q++) out[(16 * st + 4 * L.g + q) * HP + col] = silu(acc[st][q]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  load_x(blockIdx.x);
+  put_x(blockIdx.x);
   __syncthreads();
-  dense_fwd(prm + of.w1, prm + of.b1, &sX[0][0], NIN, NIN + 1, &sA[0][0], H);
-  __syncthreads();
-  for (int e = t; e < TS * H; e += THREADS) sA[e / H][e % H] = silu(sA[e / H][e % H]);
-  __syncthreads();
-  dense_fwd(prm + of.w2, prm + of.b2, &sA[0][0], H, H, &sB[0][0], H);
-  __syncthreads();
-  for (int e = t; e < TS * H; e += THREADS) sB[e / H][e % H] = silu(sB[e / H][e % H]);
-  __syncthreads();
-  dense_fwd(prm + of.w3, prm + of.b3, &sB[0][0], H, H, &sA[0][0], H);
-  __syncthreads();
-  for (int e = t; e < TS * H; e += THREADS) sA[e / H][e % H] = silu(sA[e / H][e % H]);
-  __syncthreads();
-  for (int e = t; e < TS * nout; e += THREADS) {
-    const int s = e / nout, k = e % nout;
-    if (s0 + s >= n) continue;
-    float yv = prm[of.b4 + k];
-    for (int i = 0; i < H; i++) yv = fmaf(prm[of.w4 + (size_t)k * H + i], sA[s][i], yv);
-    y_out[((size_t)member * n + s0 + s) * nout + k] = yv * ys[k] + ym[k];
+  int buf = 0;
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x, buf ^= 1) {
+    float *a = sA[buf], *b = sA[buf ^ 1];
+#pragma unroll
+    for (int st = 0; st < FM; st++) {
+      acc[st] = f4v{b1, b1, b1, b1};
+#pragma unroll
+      for (int ks = 0; ks < KX; ks++) acc[st] = mfma(sX[16 * st + L.r16][4 * ks + L.g], w1[ks], acc[st]);
+    }
+    put(a);
+    load_x(tile + gridDim.x);  // of the next tile, if there is one; arrives during a hidden layer
+    __syncthreads();
+    reg_layer(L, w2, b2, a, acc);
+    put(b);
+    __syncthreads();
+    put_x(tile + gridDim.x);  // all reads of this tile's were before the first barrier
+    reg_layer(L, w3, b3, b, acc);
+    put(a);  // all reads of a were before the last barrier
+    __syncthreads();
+    // output layer: waves 0 to 3 take 16 samples x 16 columns (nout of them
+    // real) each; the next tile's first layer writes b, whose reads are done
+    if (L.w >= FM) continue;
+    f4v yv = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int kb = 0; kb < H / 16; kb++) {
+      const float4 av = ld4(&a[(16 * L.w + L.r16) * HP + 16 * kb + 4 * L.g]);
+      const float4 wv = ld4(&sW4[k4 * H + 16 * kb + 4 * L.g]);
+#pragma unroll
+      for (int r = 0; r < 4; r++) yv = mfma(comp(av, r), comp(wv, r), yv);
+    }
+    if (L.r16 < nout)
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        const int64_t s = tile * FS + 16 * L.w + 4 * L.g + q;
+        if (s < n) y_out[((size_t)member * n + s) * nout + L.r16] = (yv[q] + b4) * scale + shift;
+      }
   }
 }
 
@@ -898,8 +971,10 @@ int32_t eph_mlp_predict(eph_mlp *m, int64_t n, const float *x, float *y, void *s
   DeviceGuard dg(m->ctx->device);
   if (!dg.ok) return EPH_E_DEVICE;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(mlp_forward_kernel, dim3((unsigned)((n + TS - 1) / TS), m->members), dim3(THREADS), 0, st,
-                     m->nout, n, x, m->params.as<float>(), m->norm.as<float>(), y);
+  // two workgroups per CU (what their LDS and registers allow) share out the tiles
+  const int64_t tiles = (n + FS - 1) / FS, walkers = std::min<int64_t>(tiles, std::max(1, 512 / m->members));
+  hipLaunchKernelGGL(mlp_forward_kernel, dim3((unsigned)walkers, m->members), dim3(FN), 0, st, m->nout, n, tiles, x,
+                     m->params.as<float>(), m->norm.as<float>(), y);
   MHIP(m, hipGetLastError());
   return EPH_OK;
 }

@@ -1047,10 +1047,10 @@ int32_t eph_stage_times(const eph_ctx *c, double *ms, int64_t *launches) {
 
 namespace {
 // Workspace of the conductivity reduction, in doubles: per-block partials
-// [kSigBlocks][EPH_MAX_TEMPS * 9], the reduced moments [3][EPH_MAX_TEMPS * 9]
-// and k_B T [EPH_MAX_TEMPS].
+// [3][kSigBlocks][EPH_MAX_TEMPS * 9] and the reduced moments
+// [3][EPH_MAX_TEMPS * 9].
 constexpr int kSigBlocks = 256;
-constexpr size_t kSigWorkDoubles = (size_t)kSigBlocks * EPH_MAX_TEMPS * 9 + 3 * EPH_MAX_TEMPS * 9 + EPH_MAX_TEMPS;
+constexpr size_t kSigWorkDoubles = 3 * (size_t)(kSigBlocks + 1) * EPH_MAX_TEMPS * 9;
 
 // Static device workspace of eph_conductivity_noalloc: one copy per GPU,
 // held until the process ends.  In host code `scratch` only names the
@@ -1089,15 +1089,12 @@ int32_t moments(eph_ctx *c, int64_t n_states, const double *energy_eV, const dou
   hipStream_t st = static_cast<hipStream_t>(stream);
   const Units U = units();
   double *part = work;
-  double *outd = part + (size_t)kSigBlocks * EPH_MAX_TEMPS * 9;
-  double *kts = outd + 3 * EPH_MAX_TEMPS * 9;
-  double hk[EPH_MAX_TEMPS] = {1.0, 1.0, 1.0, 1.0};
-  for (int t = 0; t < n_temps; t++) hk[t] = U.kb_evk * temps_K[t];
-  EPH_HIP(c, hipMemcpyAsync(kts, hk, sizeof(hk), hipMemcpyHostToDevice, st));
+  double *outd = part + 3 * (size_t)kSigBlocks * EPH_MAX_TEMPS * 9;
+  double kts[EPH_MAX_TEMPS];
+  for (int t = 0; t < n_temps; t++) kts[t] = U.kb_evk * temps_K[t];
   const double pref = 2.0 * kCharge / ((double)n_kpoints * c->volume * 1e-30);
-  for (int o = 0; o < n_orders; o++)
-    EPH_HIP(c, launch_sigma(n_states, energy_eV, vel_ms, inv_tau_s, mu_eV, n_temps, kts, pref, part, kSigBlocks,
-                            outd + o * EPH_MAX_TEMPS * 9, st, o, F));
+  EPH_HIP(c, launch_sigma(n_states, energy_eV, vel_ms, inv_tau_s, mu_eV, n_temps, kts, pref, part, kSigBlocks, outd, st,
+                          n_orders, F));
   EPH_HIP(c, hipMemcpyAsync(out, outd, sizeof(double) * n_orders * EPH_MAX_TEMPS * 9, hipMemcpyDeviceToHost, st));
   EPH_HIP(c, hipStreamSynchronize(st));
   return EPH_OK;
@@ -1303,13 +1300,11 @@ int32_t eph_carrier_density(eph_ctx *c, int32_t grid, int32_t band_lo, int32_t b
   EPH_HIP(c, launch_phase_table(N, c->tab.as<double2>(), st));
   EPH_HIP(c, electron_tables(c, N, U, true, st));
   const int nblk = 256;
-  EPH_HIP(c, c->sig_part.ensure(sizeof(double) * ((size_t)nblk * EPH_MAX_TEMPS + 2 * EPH_MAX_TEMPS)));
+  EPH_HIP(c, c->sig_part.ensure(sizeof(double) * (size_t)(nblk + 1) * EPH_MAX_TEMPS));
   double *part = c->sig_part.as<double>();
   double *outd = part + (size_t)nblk * EPH_MAX_TEMPS;
-  double *kts = outd + EPH_MAX_TEMPS;
-  double hk[EPH_MAX_TEMPS] = {1.0, 1.0, 1.0, 1.0};
-  for (int t = 0; t < n_temps; t++) hk[t] = U.kb_evk * temps_K[t];
-  EPH_HIP(c, hipMemcpyAsync(kts, hk, sizeof(hk), hipMemcpyHostToDevice, st));
+  double kts[EPH_MAX_TEMPS];
+  for (int t = 0; t < n_temps; t++) kts[t] = U.kb_evk * temps_K[t];
   const double pref = 2.0 / ((double)NQ * c->volume * 1e-30);
   EPH_HIP(c, launch_density(N, nw, c->eps.as<double>(), band_lo, band_hi, mu_eV, n_temps, kts, pref, part, nblk,
                             outd, st));

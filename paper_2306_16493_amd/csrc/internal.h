@@ -196,7 +196,6 @@ hipError_t launch_xform64(int64_t ns, const int32_t *sk, const int32_t *sn, int 
 hipError_t launch_xform32(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int nw, int nre,
                           const int *re, int ncol, const float2 *wt, const double2 *evec,
                           const double2 *tab, float2 *X, hipStream_t st);
-hipError_t launch_real_to_f32(int64_t n, const double *in, float *out, hipStream_t st);
 hipError_t launch_to_f32(int64_t n, const double2 *in, float2 *out, hipStream_t st);
 // bf16 hi/lo split of the g operand in real form (2 * bf16_w_elems bf16 values)
 size_t bf16_w_elems(int nre, int nw, int ncol);
@@ -321,11 +320,13 @@ hipError_t launch_occupations(int N, int nw, int nm, const double *eps, const do
 
 // sigma partial sums per block, then out[T*9 + ab] = pref * sum of partials
 // (partials: [nblk][EPH_MAX_TEMPS*9], out: [EPH_MAX_TEMPS*9], kts: device [nt]).
-// order n weights each state by (eps - mu)^n (n = 0: sigma)
-// F (optional, [nt][ns][3]) replaces v_b tau by the mean free path F_b.
+// moments 0 .. n_orders - 1 (1 or 3) weight each state by (eps - mu)^n (n = 0:
+// sigma), into out[n_orders][EPH_MAX_TEMPS * 9] (partials [n_orders][nblk] of
+// the same).  F (optional, [nt][ns][3], one moment) replaces v_b tau by the
+// mean free path F_b.
 hipError_t launch_sigma(int64_t ns, const double *e, const double *v, const double *inv_tau, double mu,
-                        int nt, const double *kts, double pref, double *partials, int nblk, double *out,
-                        hipStream_t st, int order = 0, const double *F = nullptr);
+                        int nt, const double *kts_host, double pref, double *partials, int nblk, double *out,
+                        hipStream_t st, int n_orders, const double *F = nullptr);
 // iterative BTE (k_bte.hip)
 hipError_t launch_state_index(int64_t nq, int nw, int64_t ns, const int32_t *sk, const int32_t *sn, int32_t *stidx,
                               hipStream_t st);

@@ -672,24 +672,26 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
       a.batch_lines = wave_batch_lines(N);
       a.plane_groups = wave_plane_groups(N);
     }
-    // Slabs of q3 planes per launch of the wave kernel: one where the states
-    // alone fill the card (the slab's q-side tables then stay in the L2s),
-    // else as many as it takes for kFillBlocks workgroups; the sums of the
-    // slabs of a launch are kept apart and added in order, so the results do
-    // not depend on the number
-    constexpr int64_t kFillBlocks = 16384;
+    // Slabs of q3 planes per launch of the wave kernel: as many as the memory
+    // for their sums allows, so that the launches' last workgroups, which
+    // leave the card half empty, are few (Al-like 100^3, FP64, 4 % of the
+    // states: 206 ms with 30 launches for 239 with 50, 194 with one; Si-like
+    // 130^3, FP32, 983 states: 44 ms with one launch, 62 with eight).  The sums
+    // are kept apart and added in order, so the results do not depend on the
+    // number.
+    constexpr int64_t kSlabSumBytes = (int64_t)128 << 20;
     int slabs = 1, nslab = 0;
     if (gwave > 0) {
-      a.slab_planes = wave_slab_planes(N, ns);
+      a.slab_planes = wave_slab_planes(N, ns, p->precision == EPH_FP64);
       nslab = (N + a.slab_planes - 1) / a.slab_planes;
     }
-    if (nslab > 1 && ns < kFillBlocks) {
+    if (nslab > 1 && kbatch_q == 0) {
       const int64_t slab_bytes = ns * (8 * p->n_temps + 32);
       const int64_t count_bytes = gr ? 8 * ns : 0;  // per slab and once more
-      slabs = (int)std::min<int64_t>(nslab, (kFillBlocks + ns - 1) / ns);
+      int64_t cap = kSlabSumBytes;
       if (p->mem_budget_bytes > 0)  // what the plan has for band ranges and slab sums
-        slabs = (int)std::min<int64_t>(slabs, (NQ * nw * 4 - 8 * (int64_t)nw * N * a.plane_groups - count_bytes) /
-                                                  (slab_bytes + count_bytes));
+        cap = std::min(cap, NQ * nw * 4 - 8 * (int64_t)nw * N * a.plane_groups);
+      slabs = (int)std::min<int64_t>(nslab, (cap - count_bytes) / (slab_bytes + count_bytes));
       slabs = std::max(slabs, 1);
       if (slabs > 1) {
         EPH_HIP(c, c->part.ensure(slab_bytes * slabs));

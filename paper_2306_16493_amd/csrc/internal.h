@@ -343,7 +343,7 @@ hipError_t launch_density(int N, int nw, const double *eps, int blo, int bhi, do
 // (rounded outwards), and the FP32 records (factors as launch_occupations).
 int wave_batch_lines(int N);
 int wave_plane_groups(int N);
-int wave_slab_planes(int N, int64_t ns);  // q3 planes per workgroup
+int wave_slab_planes(int N, int64_t ns, bool fp64);  // q3 planes per workgroup
 hipError_t launch_band_ranges(int N, int nw, const double *eps, float2 *out, hipStream_t st);
 size_t wave_rec_bytes(int nw, int nm, int nt, int64_t nq, size_t *q_offset);
 hipError_t launch_wave_records(int N, int nw, int nm, const double *eps, const double *om, const double2 *evec,

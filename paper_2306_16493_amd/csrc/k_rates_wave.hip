@@ -19,24 +19,26 @@ extern template hipError_t dispatch_nm<double, 6, kEmit>(const RatesArgs &, hipS
 
 namespace {
 
+// blockIdx.y: a temperature or one of the four counters
 __global__ void add_slabs_kernel(RatesArgs a) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= a.ns_launch) return;
   const int64_t s = a.s_lo + i;
-  const int np = a.slab_hi - a.slab_lo;
-  for (int t = 0; t < a.nt; t++) {
+  const int np = a.slab_hi - a.slab_lo, t = blockIdx.y, c = t - a.nt;
+  if (c < 0) {
     double *dst = a.inv_tau + (int64_t)t * a.ns_total + s;
     double v = a.slab_lo == 0 ? 0.0 : *dst;
+#pragma unroll 8
     for (int j = 0; j < np; j++) v += a.part_tau[((int64_t)j * a.nt + t) * a.ns_total + s];
     *dst = v;
-  }
-  for (int c = 0; c < 4; c++) {
+  } else {
     int64_t *dst = (c < 2 ? a.st_counts : a.kv_counts - 2) + 2 * s + c;
     int64_t v = a.slab_lo == 0 ? 0 : *dst;
+#pragma unroll 8
     for (int j = 0; j < np; j++) v += a.part_cnt[((int64_t)j * a.ns_total + s) * 4 + c];
     *dst = v;
+    if (c == 0 && a.g_slot) a.g_cursor[s] += a.g_slot[(int64_t)np * a.ns_total + s];
   }
-  if (a.g_slot) a.g_cursor[s] += a.g_slot[(int64_t)np * a.ns_total + s];
 }
 
 __global__ void slab_counts_kernel(RatesArgs a, int total) {
@@ -59,7 +61,7 @@ __global__ void slab_counts_kernel(RatesArgs a, int total) {
 
 hipError_t launch_add_slabs(const RatesArgs &a, hipStream_t st) {
   if (a.ns_launch <= 0) return hipSuccess;
-  hipLaunchKernelGGL(add_slabs_kernel, dim3((unsigned)((a.ns_launch + 255) / 256)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(add_slabs_kernel, dim3((unsigned)((a.ns_launch + 255) / 256), a.nt + 4), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -194,13 +194,15 @@ int wave_batch_lines(int N) {
   return (N + nb - 1) / nb;  // evened out over the batches
 }
 
-// Planes per workgroup: enough for about 20000 q, so that what a workgroup
-// does once (tables, reductions) stays small beside them, while the states
-// still make 8192 workgroups.  More q per workgroup cost more than they save,
-// the q-side tables of the planes in flight no longer fit the L2s (Al 71^3,
-// FP32: 449 ms at 20000 q, 459 at one plane, 490 at 80000).
-int wave_slab_planes(int N, int64_t ns) {
-  const int64_t n2 = (int64_t)N * N, p = std::min(((int64_t)20000 + n2 / 2) / n2, ns * N / 8192);
+// Planes per workgroup: enough for about 20000 q (10000 in FP64, whose tables
+// are twice as large), so that what a workgroup does once (tables, reductions)
+// stays small beside them, while the states still make 8192 workgroups.  More
+// q per workgroup cost more than they save, the q-side tables of the planes in
+// flight no longer fit the L2s (Al-like, FP32, 71^3: 387 ms at 20000 q, 407 at
+// 10000, 402 at 40000; FP64, 100^3, 4 % of the states: 185 ms at 10000, 194 at
+// 20000, 205 at 40000).
+int wave_slab_planes(int N, int64_t ns, bool fp64) {
+  const int64_t n2 = (int64_t)N * N, p = std::min(((fp64 ? 10000 : 20000) + n2 / 2) / n2, ns * N / 8192);
   return (int)std::max<int64_t>(1, std::min<int64_t>(p, N));
 }
 

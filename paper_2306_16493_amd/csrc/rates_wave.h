@@ -31,16 +31,16 @@
 // planes are fixed, so results are bit-reproducible.
 //
 // What bounds it.  Al-like model (4 bands, 3 modes, box 6^3), 71^3, 3
-// temperatures, FP32: 421 ms for 1.2e10 vertices, about 165 ms of it the
-// vertices (instruction issue: 700 or so FP32 operations each, at 70 TFLOP/s
-// in non-packed form), 130 the sieve, 25 Z, 100 the start of the planes.  One
-// wave per state and line, each with its own Z by vector operations, took
-// 648 ms; 128 threads per workgroup leave fewer waves waiting at a barrier
-// than 256 (443 ms).  The tables are stored by plane and component so that
-// the lanes' reads, neighbours in p or q, run along lines: an array of
-// records, one per gather, made the L1 the bound (160^3, FP32, 1
-// temperature: 173 ms against 101).  FP64, 100^3, 4 % of the states: 244 ms
-// (480 per line, 281 with records).
+// temperatures, FP32: 332 ms for 1.2e10 vertices, about 155 ms of it the
+// vertices (some 700 FP32 instructions to 64 of them, half the time waiting
+// for their gathers), 90 the sieve, 30 Z, 45 the reading of X.  One wave per
+// state and line, each with its own Z by vector operations, took 648 ms; 128
+// threads per workgroup leave fewer waves waiting at a barrier than 256.  The
+// tables are stored by plane and component so that the lanes' reads,
+// neighbours in p or q, run along lines: an array of records, one per gather,
+// made the L1 the bound (160^3, FP32, 1 temperature: 173 ms against 101).
+// FP64, 100^3, 4 % of the states: 183 ms (480 per line), 120 of it the
+// vertices, whose gathers, 370 bytes each, come from the L2s at 11 TB/s.
 #include <cstddef>
 #include <type_traits>
 
@@ -141,15 +141,27 @@ struct WaveLayout {
   static constexpr int ZB = ROWS + (int)(16 / sizeof(C2));
   // sieve passes (four entries each) whose table entries are loaded together
   static constexpr int SG = NM == 3 ? (sizeof(T) == 8 ? 3 : 4) : 2;
-  static constexpr int QC = 512;                     // queue entries per wave and round (a sieve pass adds 64 at most)
+  // Planes of Y formed from one reading of X, where the LDS for the waiting
+  // ones costs no workgroup per CU.  The rows of X in flight (20 KB each in
+  // FP32) do not fit the L2s, and reading one for every plane took 85 of 387
+  // ms (Al-like 71^3): 332 with two planes, 388 with three.  FP64: 2.33 ms
+  // with one, 3.12 with two at 24^3; with 48 channels 27.3 and 25.9 ms
+  // (Si-like 48^3); FP32 with 48 channels 11.5 and 15.8.
+  static constexpr int YP = (sizeof(T) == 4 ? NM == 3 : C >= 48) ? 2 : 1;
+  // queue entries per wave and round (a sieve pass adds 64 at most): smaller
+  // ones cut rounds short, larger ones cost workgroups (Al-like 71^3, FP32:
+  // 359 ms with 384, 332 with 512, 345 with 640)
+  static constexpr int QC = 512;
   __host__ __device__ static size_t tab_bytes(int N) { return sizeof(C2) * 2 * (size_t)((N + 1) & ~1); }
   static constexpr size_t z_bytes = sizeof(C2) * (size_t)NL * ZB;
   static constexpr size_t q_bytes = 2 * 2 * (size_t)WPB * QC;                      // two rounds of 16-bit entries
   static constexpr size_t rank_bytes = q_bytes;                                     // emit mode
   static constexpr int LC = 128;                    // (group, band) list entries per wave
   static constexpr size_t misc_bytes = 8 * (size_t)WPB * 8 + 2 * 4 * (size_t)WPB * 4 + 2 * (size_t)WPB * LC;
-  __host__ __device__ static size_t total(int N, int mode) {
-    return misc_bytes + (mode == kCount ? 0 : q_bytes + tab_bytes(N) + z_bytes) + (mode == kEmit ? rank_bytes : 0);
+  static constexpr size_t y_bytes = sizeof(T) * (size_t)(YP - 1) * TPW * KS * 64 * WPB;
+  __host__ __device__ static size_t total(int N, int mode, int slab_planes) {
+    return misc_bytes + (mode == kCount ? 0 : q_bytes + tab_bytes(N) + z_bytes + (slab_planes > 1 ? y_bytes : 0)) +
+           (mode == kEmit ? rank_bytes : 0);
   }
 };
 
@@ -182,7 +194,7 @@ void rates_wave_kernel(RatesArgs a) {
   constexpr int kPC = sizeof(PR) / 16, kQC = sizeof(QR) / 16;          // chunks of the FP32 records
   constexpr int kPE = offsetof(PR, e) / 4, kPF = offsetof(PR, f) / 4;  // floats before their members
   constexpr int kQW = offsetof(QR, w) / 4, kQN = offsetof(QR, n) / 4;
-  constexpr int C = LY::C, WPB = LY::WPB, TPW = LY::TPW, KS = LY::KS, QC = LY::QC;
+  constexpr int C = LY::C, WPB = LY::WPB, TPW = LY::TPW, KS = LY::KS, QC = LY::QC, YP = LY::YP;
   extern __shared__ __align__(16) unsigned char smem[];
   const int N = a.N;
   const int lane = threadIdx.x & 63;
@@ -205,6 +217,9 @@ void rates_wave_kernel(RatesArgs a) {
   C2 *sTab = reinterpret_cast<C2 *>(rest + LY::q_bytes);          // [2][N]: f = e^{2 pi i m/N}, then i f
   C2 *sZ = reinterpret_cast<C2 *>(rest + LY::q_bytes + LY::tab_bytes(N));  // [NL][ZB]: [p1][mu][i] + pad
   uint16_t *sRank = reinterpret_cast<uint16_t *>(rest + LY::q_bytes + LY::tab_bytes(N) + LY::z_bytes);  // as sQ
+  // [YP - 1][tile][step][thread] (slabs of more than one plane)
+  [[maybe_unused]] T *sY = reinterpret_cast<T *>(rest + LY::q_bytes + LY::tab_bytes(N) + LY::z_bytes +
+                                                 (MODE == kEmit ? LY::rank_bytes : 0));
 
   if constexpr (MODE != kCount) {
     for (int t = threadIdx.x; t < N; t += WPB * 64) {
@@ -409,21 +424,27 @@ void rates_wave_kernel(RatesArgs a) {
     // ---- Y_s(p1, p2; q3) as the A operand: lane (i, g) of tile t and step ks
     //      holds row 16 t + row_of(i) = (p1, channel), inner index 4 ks + g =
     //      (p2, re/im).  Rows past the last repeat it (their products are not
-    //      kept), so that a tile's loads go out together. ----
+    //      kept), so that a tile's loads go out together.  One reading of X
+    //      serves YP planes; the later ones wait in the lane's own LDS words. ----
     static_assert(NB % 2 == 0, "whole steps over (p2, re/im)");
     T ya[TPW][KS];
-    {
+    const int yj = YP == 1 || a.slab_planes == 1 ? 0 : (q3 - slab * a.slab_planes) % YP;
+    if (yj == 0) {
       int64_t x0 = (s - a.s_base) * (int64_t)(NB * NB * NB * C);
-      asm volatile("" : "+s"(x0));  // read again for every plane: kept over the loop the row would fill the registers
+      asm volatile("" : "+s"(x0));  // read again, not kept over the loop: the row would fill the registers
       const C2 *X = reinterpret_cast<const C2 *>(a.X) + x0;
-      C2 ph3[NB];  // Re(f x) = (f.x, -f.y) . x, Im(f x) = (f.y, f.x) . x
-      int i3 = 0;
+      C2 ph3[YP][NB];  // Re(f x) = (f.x, -f.y) . x, Im(f x) = (f.y, f.x) . x
 #pragma unroll
-      for (int p = 0; p < NB; p++) {
-        const C2 f = sTab[((lg & 1) ? N : 0) + i3];
-        ph3[p] = (lg & 1) ? mk<T>(-f.x, f.y) : mk<T>(f.x, -f.y);
-        i3 += q3;
-        i3 -= (i3 >= N) ? N : 0;
+      for (int j = 0; j < YP; j++) {
+        const int qj = min(q3 + j, N - 1);
+        int i3 = 0;
+#pragma unroll
+        for (int p = 0; p < NB; p++) {
+          const C2 f = sTab[((lg & 1) ? N : 0) + i3];
+          ph3[j][p] = (lg & 1) ? mk<T>(-f.x, f.y) : mk<T>(f.x, -f.y);
+          i3 += qj;
+          i3 -= (i3 >= N) ? N : 0;
+        }
       }
 #pragma unroll
       for (int i = 0; i < TPW; i++) {
@@ -435,19 +456,32 @@ void rates_wave_kernel(RatesArgs a) {
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) {
           const uint32_t off = off0 + ks * (uint32_t)(2 * NB * C * sizeof(C2));
-          T y = 0;
+          T y[YP];
+#pragma unroll
+          for (int j = 0; j < YP; j++) y[j] = 0;
 #pragma unroll
           for (int p = 0; p < NB; p++) {
             const C2 v = at_offset(X + p * C, off);
-            y = fma(ph3[p].x, v.x, y);
-            y = fma(ph3[p].y, v.y, y);
+#pragma unroll
+            for (int j = 0; j < YP; j++) {
+              y[j] = fma(ph3[j][p].x, v.x, y[j]);
+              y[j] = fma(ph3[j][p].y, v.y, y[j]);
+            }
           }
-          if constexpr (sizeof(T) == 8) asm volatile("" : "+v"(y));
-          ya[i][ks] = y;
+          if constexpr (sizeof(T) == 8) asm volatile("" : "+v"(y[0]));
+          ya[i][ks] = y[0];
+          if (YP > 1 && a.slab_planes > 1)
+#pragma unroll
+            for (int j = 1; j < YP; j++) sY[(((j - 1) * TPW + i) * KS + ks) * (64 * WPB) + threadIdx.x] = y[j];
         }
         // the loads in flight fit the registers: one tile's, in FP64 one step's
         if constexpr (sizeof(T) == 4) asm volatile("" : "+v"(ya[i][0]), "+v"(ya[i][KS - 1]));
       }
+    } else {
+#pragma unroll
+      for (int i = 0; i < TPW; i++)
+#pragma unroll
+        for (int ks = 0; ks < KS; ks++) ya[i][ks] = sY[(((yj - 1) * TPW + i) * KS + ks) * (64 * WPB) + threadIdx.x];
     }
     sieve(0);
     bool new_z = true;
@@ -744,7 +778,7 @@ void rates_wave_kernel(RatesArgs a) {
 template <class T, int NW, int NM, int NB, int NT, int MODE>
 hipError_t launch_wave(const RatesArgs &a, hipStream_t st) {
   using LY = WaveLayout<T, NW, NM, NB>;
-  const size_t sh = LY::total(a.N, MODE);
+  const size_t sh = LY::total(a.N, MODE, a.slab_planes);
   if (sh > 160 * 1024) return hipErrorInvalidValue;
   auto kern = rates_wave_kernel<T, NW, NM, NB, NT, MODE>;
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);

@@ -39,7 +39,7 @@
 // tables are stored by plane and component so that the lanes' reads,
 // neighbours in p or q, run along lines: an array of records, one per gather,
 // made the L1 the bound (160^3, FP32, 1 temperature: 173 ms against 101).
-// FP64, 100^3, 4 % of the states: 183 ms (480 per line), 120 of it the
+// FP64, 100^3, 4 % of the states: 167 ms (480 per line), 105 of it the
 // vertices, whose gathers, 370 bytes each, come from the L2s at 11 TB/s.
 #include <cstddef>
 #include <type_traits>
@@ -582,10 +582,21 @@ void rates_wave_kernel(RatesArgs a) {
           const float4 c = qc[f / 4];
           return f % 4 == 0 ? c.x : f % 4 == 1 ? c.y : f % 4 == 2 ? c.z : c.w;
         };
+        [[maybe_unused]] double wq[NM];
+        [[maybe_unused]] double2 uq[NM][NM];
         if constexpr (sizeof(T) == 8) {
           d = es - at_offset(eps_p + p0 * N, (m * (uint32_t)n2 + e) * 8u);
 #pragma unroll
           for (int j = 0; j < NW; j++) vrow[j] = at_offset(evec_b + j * n2, (m * (uint32_t)(NW * n2) + e) * 16u);
+          if constexpr (NM == 3) {  // the modes too, ahead of the sum (6 would not fit the registers)
+#pragma unroll
+            for (int nu = 0; nu < NM; nu++) {
+              wq[nu] = at_offset(om_q + nu * n2, qoff * 8u);
+#pragma unroll
+              for (int mu = 0; mu < NM; mu++) uq[nu][mu] = at_offset(uu_q + (nu * NM + mu) * n2, qoff * 16u);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
         } else {
 #pragma unroll
           for (int c = 0; c < kPC; c++) pc[c] = at_offset(rec_b + c * n2, (m * (uint32_t)(kPC * n2) + e) * 16u);
@@ -609,7 +620,9 @@ void rates_wave_kernel(RatesArgs a) {
             cmac_conj<T>(wr[mu], wi[mu], vrow[j].x, vrow[j].y, z.x, z.y);
           }
         }
-#pragma unroll 1
+        // two steps at a time: one copies the sums back, more spill (Al-like
+        // 100^3, FP64: 174, 167, 183 ms with 1, 2, 5; Si-like 48^3: 25, 20, 20)
+#pragma unroll 2
         for (int pp = NB - 2; pp >= 0; pp--) {
 #pragma unroll
           for (int mu = 0; mu < NM; mu++) {
@@ -636,7 +649,11 @@ void rates_wave_kernel(RatesArgs a) {
         for (int nu = 0; nu < NM; nu++) {
           double w;
           C2 u[NM];
-          if constexpr (sizeof(T) == 8) {
+          if constexpr (sizeof(T) == 8 && NM == 3) {
+            w = wq[nu];
+#pragma unroll
+            for (int mu = 0; mu < NM; mu++) u[mu] = uq[nu][mu];
+          } else if constexpr (sizeof(T) == 8) {
             w = at_offset(om_q + nu * n2, qoff * 8u);
 #pragma unroll
             for (int mu = 0; mu < NM; mu++) u[mu] = at_offset(uu_q + (nu * NM + mu) * n2, qoff * 16u);
@@ -654,8 +671,10 @@ void rates_wave_kernel(RatesArgs a) {
           const T g2 = fma(gr, gr, gi * gi);
           T dp, dm;
           if constexpr (sizeof(T) == 8) {
-            dp = okp ? exp_neg(-(xpd * inv_eta) * (xpd * inv_eta)) : 0.0;
-            dm = okm ? exp_neg(-(xmd * inv_eta) * (xmd * inv_eta)) : 0.0;
+            // exp_neg(-800) is zero: no branch, so that the modes' loads and
+            // chains run beside each other
+            dp = exp_neg(okp ? -(xpd * inv_eta) * (xpd * inv_eta) : -800.0);
+            dm = exp_neg(okm ? -(xmd * inv_eta) * (xmd * inv_eta) : -800.0);
           } else {
             // FP32 form: |g|^2, the Gaussians and the occupation weights in
             // FP32 (the arguments x are formed in FP64 from the FP64 energies)

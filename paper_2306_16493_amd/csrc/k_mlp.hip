@@ -75,9 +75,12 @@ __device__ __forceinline__ float dsilu(float z) {
   return s * (1.0f + z * (1.0f - s));
 }
 
-// Training tile: TT samples per workgroup of TN threads (four waves).
+// Training tile: TT samples per workgroup of TN threads (eight waves: two to
+// a SIMD, so that one computes while the other waits; 60 steps of 5 members,
+// batch 1024: 2.36 ms, with four waves 2.55).
 constexpr int TT = 32;
-constexpr int TN = 256;
+constexpr int TN = 512;
+constexpr int OT = H / 16 / (TN / 64);  // 16-column tiles of a hidden layer per wave
 // Row pitch (floats) of activations, gradients and staged weights in LDS: a
 // column read by the 16 rows of an MFMA operand falls in distinct banks.
 constexpr int HP = H + 4;
@@ -128,7 +131,7 @@ struct WStage {
 
 // Tile ownership of the hidden-layer products: wave w, lane l, r16 = l % 16,
 // g = l / 16.  Forward and input gradient: the wave holds samples
-// 16 st + 4 g + q (st < 2) x columns 16 (2 w + ot) + r16 (ot < 2).
+// 16 st + 4 g + q (st < 2) x columns 16 (OT w + ot) + r16 (ot < OT).
 struct Lane {
   int w, r16, g;
   __device__ Lane() : w(threadIdx.x >> 6), r16(threadIdx.x & 15), g((threadIdx.x >> 4) & 3) {}
@@ -136,62 +139,62 @@ struct Lane {
 
 // z[s][o] = b[o] + sum_i W[o][i] a[s][i]  (W staged in sW, a in sA)
 __device__ __forceinline__ void hidden_fwd(const Lane &L, const float *sW, const float *__restrict__ b,
-                                           const float *sA, f4v acc[2][2]) {
+                                           const float *sA, f4v acc[2][OT]) {
 #pragma unroll
-  for (int ot = 0; ot < 2; ot++) {
-    const float bo = b[16 * (2 * L.w + ot) + L.r16];
+  for (int ot = 0; ot < OT; ot++) {
+    const float bo = b[16 * (OT * L.w + ot) + L.r16];
 #pragma unroll
     for (int st = 0; st < 2; st++) acc[st][ot] = f4v{bo, bo, bo, bo};
   }
   for (int kb = 0; kb < H; kb += 16) {
-    float4 av[2], wv[2];
+    float4 av[2], wv[OT];
 #pragma unroll
     for (int st = 0; st < 2; st++) av[st] = ld4(&sA[(16 * st + L.r16) * HP + kb + 4 * L.g]);
 #pragma unroll
-    for (int ot = 0; ot < 2; ot++) wv[ot] = ld4(&sW[(16 * (2 * L.w + ot) + L.r16) * HP + kb + 4 * L.g]);
+    for (int ot = 0; ot < OT; ot++) wv[ot] = ld4(&sW[(16 * (OT * L.w + ot) + L.r16) * HP + kb + 4 * L.g]);
 #pragma unroll
     for (int r = 0; r < 4; r++)
 #pragma unroll
       for (int st = 0; st < 2; st++)
 #pragma unroll
-        for (int ot = 0; ot < 2; ot++) acc[st][ot] = mfma(comp(av[st], r), comp(wv[ot], r), acc[st][ot]);
+        for (int ot = 0; ot < OT; ot++) acc[st][ot] = mfma(comp(av[st], r), comp(wv[ot], r), acc[st][ot]);
   }
 }
 
 // g[s][i] = sum_o dz[s][o] W[o][i]  (W staged in sW, dz in sD)
-__device__ __forceinline__ void hidden_bwd_input(const Lane &L, const float *sW, const float *sD, f4v acc[2][2]) {
+__device__ __forceinline__ void hidden_bwd_input(const Lane &L, const float *sW, const float *sD, f4v acc[2][OT]) {
 #pragma unroll
   for (int st = 0; st < 2; st++)
 #pragma unroll
-    for (int ot = 0; ot < 2; ot++) acc[st][ot] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int ot = 0; ot < OT; ot++) acc[st][ot] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
   for (int kb = 0; kb < H; kb += 16) {
     float4 dv[2];
-    float wv[2][4];
+    float wv[OT][4];
 #pragma unroll
     for (int st = 0; st < 2; st++) dv[st] = ld4(&sD[(16 * st + L.r16) * HP + kb + 4 * L.g]);
 #pragma unroll
-    for (int ot = 0; ot < 2; ot++)
+    for (int ot = 0; ot < OT; ot++)
 #pragma unroll
-      for (int r = 0; r < 4; r++) wv[ot][r] = sW[(kb + 4 * L.g + r) * HP + 16 * (2 * L.w + ot) + L.r16];
+      for (int r = 0; r < 4; r++) wv[ot][r] = sW[(kb + 4 * L.g + r) * HP + 16 * (OT * L.w + ot) + L.r16];
 #pragma unroll
     for (int r = 0; r < 4; r++)
 #pragma unroll
       for (int st = 0; st < 2; st++)
 #pragma unroll
-        for (int ot = 0; ot < 2; ot++) acc[st][ot] = mfma(comp(dv[st], r), wv[ot][r], acc[st][ot]);
+        for (int ot = 0; ot < OT; ot++) acc[st][ot] = mfma(comp(dv[st], r), wv[ot][r], acc[st][ot]);
   }
 }
 
 // dW[o][i] = sum_s dz[s][o] a[s][i] over the tile's samples (the wave holds
-// rows 16 (2 w + ot) + 4 g + q x all columns), stored into the tile's slot;
+// rows 16 (OT w + ot) + 4 g + q x all columns), stored into the tile's slot;
 // db[o] = sum_s dz[s][o] (per lane over its samples, then across the four
 // lane groups).
 __device__ __forceinline__ void hidden_bwd_weights(const Lane &L, const float *sD, const float *sA,
                                                    float *__restrict__ gW, float *__restrict__ gb) {
-  f4v acc[2][8];
-  float db[2] = {0.0f, 0.0f};
+  f4v acc[OT][8];
+  float db[OT] = {};
 #pragma unroll
-  for (int ot = 0; ot < 2; ot++)
+  for (int ot = 0; ot < OT; ot++)
 #pragma unroll
     for (int it = 0; it < 8; it++) acc[ot][it] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -199,31 +202,31 @@ __device__ __forceinline__ void hidden_bwd_weights(const Lane &L, const float *s
 #pragma unroll
     for (int r = 0; r < 4; r++) {
       const int s = kb + 4 * L.g + r;
-      float dv[2], av[8];
+      float dv[OT], av[8];
 #pragma unroll
-      for (int ot = 0; ot < 2; ot++) {
-        dv[ot] = sD[s * HP + 16 * (2 * L.w + ot) + L.r16];
+      for (int ot = 0; ot < OT; ot++) {
+        dv[ot] = sD[s * HP + 16 * (OT * L.w + ot) + L.r16];
         db[ot] += dv[ot];
       }
 #pragma unroll
       for (int it = 0; it < 8; it++) av[it] = sA[s * HP + 16 * it + L.r16];
 #pragma unroll
-      for (int ot = 0; ot < 2; ot++)
+      for (int ot = 0; ot < OT; ot++)
 #pragma unroll
         for (int it = 0; it < 8; it++) acc[ot][it] = mfma(dv[ot], av[it], acc[ot][it]);
     }
   }
 #pragma unroll
-  for (int ot = 0; ot < 2; ot++)
+  for (int ot = 0; ot < OT; ot++)
 #pragma unroll
     for (int it = 0; it < 8; it++)
 #pragma unroll
-      for (int q = 0; q < 4; q++) gW[(size_t)(16 * (2 * L.w + ot) + 4 * L.g + q) * H + 16 * it + L.r16] = acc[ot][it][q];
+      for (int q = 0; q < 4; q++) gW[(size_t)(16 * (OT * L.w + ot) + 4 * L.g + q) * H + 16 * it + L.r16] = acc[ot][it][q];
 #pragma unroll
-  for (int ot = 0; ot < 2; ot++) {
+  for (int ot = 0; ot < OT; ot++) {
     db[ot] += __shfl_xor(db[ot], 16);
     db[ot] += __shfl_xor(db[ot], 32);
-    if (L.g == 0) gb[16 * (2 * L.w + ot) + L.r16] = db[ot];
+    if (L.g == 0) gb[16 * (OT * L.w + ot) + L.r16] = db[ot];
   }
 }
 
@@ -260,7 +263,8 @@ __global__ __launch_bounds__(TN) void mlp_fwdbwd_kernel(TrainArgs a) {
     sIdx[t] = idx;
   }
   // first layer (NIN inputs) on the vector units: thread (og, sg) owns
-  // columns og + 32 j and samples 4 sg + u; its weight rows are loaded now
+  // columns og + 32 j and samples SU sg + u; its weight rows are loaded now
+  constexpr int SU = TT / (TN / 32);
   const int og = t & 31, sg = t >> 5;
   float w1r[4][NIN + 1];
 #pragma unroll
@@ -285,36 +289,36 @@ __global__ __launch_bounds__(TN) void mlp_fwdbwd_kernel(TrainArgs a) {
   __syncthreads();
   // ---- forward ----
   {
-    float z[4][4];
+    float z[SU][4];
 #pragma unroll
     for (int j = 0; j < 4; j++) {
 #pragma unroll
-      for (int u = 0; u < 4; u++) z[u][j] = w1r[j][NIN];
+      for (int u = 0; u < SU; u++) z[u][j] = w1r[j][NIN];
 #pragma unroll
       for (int i = 0; i < NIN; i++)
 #pragma unroll
-        for (int u = 0; u < 4; u++) z[u][j] = fmaf(w1r[j][i], sX[4 * sg + u][i], z[u][j]);
+        for (int u = 0; u < SU; u++) z[u][j] = fmaf(w1r[j][i], sX[SU * sg + u][i], z[u][j]);
     }
 #pragma unroll
-    for (int u = 0; u < 4; u++)
+    for (int u = 0; u < SU; u++)
 #pragma unroll
       for (int j = 0; j < 4; j++) {
-        sZ[0][(4 * sg + u) * HP + og + 32 * j] = z[u][j];
-        sA[(4 * sg + u) * HP + og + 32 * j] = silu(z[u][j]);
+        sZ[0][(SU * sg + u) * HP + og + 32 * j] = z[u][j];
+        sA[(SU * sg + u) * HP + og + 32 * j] = silu(z[u][j]);
       }
   }
   ws.store(sW);
   __syncthreads();
-  f4v acc[2][2];
+  f4v acc[2][OT];
   // hidden activations written back from the product tiles
-  auto put = [&](float *z_out, const f4v (&v)[2][2]) {
+  auto put = [&](float *z_out, const f4v (&v)[2][OT]) {
 #pragma unroll
     for (int st = 0; st < 2; st++)
 #pragma unroll
-      for (int ot = 0; ot < 2; ot++)
+      for (int ot = 0; ot < OT; ot++)
 #pragma unroll
         for (int q = 0; q < 4; q++) {
-          const int e = (16 * st + 4 * L.g + q) * HP + 16 * (2 * L.w + ot) + L.r16;
+          const int e = (16 * st + 4 * L.g + q) * HP + 16 * (OT * L.w + ot) + L.r16;
           z_out[e] = v[st][ot][q];
           sA[e] = silu(v[st][ot][q]);
         }
@@ -359,14 +363,14 @@ __global__ __launch_bounds__(TN) void mlp_fwdbwd_kernel(TrainArgs a) {
   for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off);
   if ((t & 63) == 0) sLoss[t >> 6] = lsum;
   __syncthreads();
-  if (t == 0) a.loss_part[(size_t)member * a.tiles + tile] = (sLoss[0] + sLoss[1]) + (sLoss[2] + sLoss[3]);
+  if (t == 0) a.loss_part[(size_t)member * a.tiles + tile] = sLoss[0] + sLoss[1];  // the output layer's waves
   // ---- backward ----
   {  // output layer on 16 x 16 tiles over this wave's columns
-     // i = 16 (2 w + ot) + r16: dW4[n][i] = sum_s dy[s][n] h3[s][i] (rows
+     // i = 16 (OT w + ot) + r16: dW4[n][i] = sum_s dy[s][n] h3[s][i] (rows
      // n >= nout are zero and not stored); dh3 = dy W4 (inner index n, one
      // product per tile), dz3 = dh3 silu'(z3) into sD; then h2 into sA on the
      // same columns (this wave's reads of h3 there are done)
-    f4v g4[2] = {f4v{0.0f, 0.0f, 0.0f, 0.0f}, f4v{0.0f, 0.0f, 0.0f, 0.0f}};
+    f4v g4[OT] = {};
     float b4 = 0.0f;
 #pragma unroll
     for (int kb = 0; kb < TT; kb += 16)
@@ -376,14 +380,14 @@ __global__ __launch_bounds__(TN) void mlp_fwdbwd_kernel(TrainArgs a) {
         const float dv = L.r16 < nout ? sDY[s][L.r16 < nout ? L.r16 : 0] : 0.0f;
         b4 += dv;
 #pragma unroll
-        for (int ot = 0; ot < 2; ot++) g4[ot] = mfma(dv, sA[s * HP + 16 * (2 * L.w + ot) + L.r16], g4[ot]);
+        for (int ot = 0; ot < OT; ot++) g4[ot] = mfma(dv, sA[s * HP + 16 * (OT * L.w + ot) + L.r16], g4[ot]);
       }
     if (L.g == 0) {
 #pragma unroll
-      for (int ot = 0; ot < 2; ot++)
+      for (int ot = 0; ot < OT; ot++)
 #pragma unroll
         for (int q = 0; q < 4; q++)
-          if (q < nout) gp[of.w4 + (size_t)q * H + 16 * (2 * L.w + ot) + L.r16] = g4[ot][q];
+          if (q < nout) gp[of.w4 + (size_t)q * H + 16 * (OT * L.w + ot) + L.r16] = g4[ot][q];
     }
     b4 += __shfl_xor(b4, 16);
     b4 += __shfl_xor(b4, 32);
@@ -391,8 +395,8 @@ __global__ __launch_bounds__(TN) void mlp_fwdbwd_kernel(TrainArgs a) {
 #pragma unroll
     for (int st = 0; st < 2; st++)
 #pragma unroll
-      for (int ot = 0; ot < 2; ot++) {
-        const int col = 16 * (2 * L.w + ot) + L.r16;
+      for (int ot = 0; ot < OT; ot++) {
+        const int col = 16 * (OT * L.w + ot) + L.r16;
         const f4v d = mfma(L.g < nout ? sDY[16 * st + L.r16][L.g] : 0.0f, L.g < nout ? sW4[L.g * H + col] : 0.0f,
                            f4v{0.0f, 0.0f, 0.0f, 0.0f});
 #pragma unroll
@@ -414,10 +418,10 @@ __global__ __launch_bounds__(TN) void mlp_fwdbwd_kernel(TrainArgs a) {
 #pragma unroll
   for (int st = 0; st < 2; st++)
 #pragma unroll
-    for (int ot = 0; ot < 2; ot++)
+    for (int ot = 0; ot < OT; ot++)
 #pragma unroll
       for (int q = 0; q < 4; q++) {
-        const int e = (16 * st + 4 * L.g + q) * HP + 16 * (2 * L.w + ot) + L.r16;
+        const int e = (16 * st + 4 * L.g + q) * HP + 16 * (OT * L.w + ot) + L.r16;
         sD[e] = acc[st][ot][q] * dsilu(sZ[1][e]);
         sA[e] = silu(sZ[0][e]);
       }
@@ -430,17 +434,17 @@ __global__ __launch_bounds__(TN) void mlp_fwdbwd_kernel(TrainArgs a) {
 #pragma unroll
   for (int st = 0; st < 2; st++)
 #pragma unroll
-    for (int ot = 0; ot < 2; ot++)
+    for (int ot = 0; ot < OT; ot++)
 #pragma unroll
       for (int q = 0; q < 4; q++) {
-        const int e = (16 * st + 4 * L.g + q) * HP + 16 * (2 * L.w + ot) + L.r16;
+        const int e = (16 * st + 4 * L.g + q) * HP + 16 * (OT * L.w + ot) + L.r16;
         sD[e] = acc[st][ot][q] * dsilu(sZ[0][e]);
       }
   __syncthreads();
   {  // first layer: dW1[o][i] = sum_s dz1[s][o] x[s][i] on 16 x 16 tiles
      // (columns i >= NIN are zero and not stored), db1 as for the hidden layers
-    f4v w1[2] = {f4v{0.0f, 0.0f, 0.0f, 0.0f}, f4v{0.0f, 0.0f, 0.0f, 0.0f}};
-    float b1[2] = {0.0f, 0.0f};
+    f4v w1[OT] = {};
+    float b1[OT] = {};
 #pragma unroll
     for (int kb = 0; kb < TT; kb += 16)
 #pragma unroll
@@ -448,23 +452,23 @@ __global__ __launch_bounds__(TN) void mlp_fwdbwd_kernel(TrainArgs a) {
         const int s = kb + 4 * L.g + r;
         const float xv = L.r16 < NIN ? sX[s][L.r16 < NIN ? L.r16 : 0] : 0.0f;
 #pragma unroll
-        for (int ot = 0; ot < 2; ot++) {
-          const float dv = sD[s * HP + 16 * (2 * L.w + ot) + L.r16];
+        for (int ot = 0; ot < OT; ot++) {
+          const float dv = sD[s * HP + 16 * (OT * L.w + ot) + L.r16];
           w1[ot] = mfma(dv, xv, w1[ot]);
           b1[ot] += dv;
         }
       }
     if (L.r16 < NIN) {
 #pragma unroll
-      for (int ot = 0; ot < 2; ot++)
+      for (int ot = 0; ot < OT; ot++)
 #pragma unroll
-        for (int q = 0; q < 4; q++) gp[of.w1 + (size_t)(16 * (2 * L.w + ot) + 4 * L.g + q) * NIN + L.r16] = w1[ot][q];
+        for (int q = 0; q < 4; q++) gp[of.w1 + (size_t)(16 * (OT * L.w + ot) + 4 * L.g + q) * NIN + L.r16] = w1[ot][q];
     }
 #pragma unroll
-    for (int ot = 0; ot < 2; ot++) {
+    for (int ot = 0; ot < OT; ot++) {
       b1[ot] += __shfl_xor(b1[ot], 16);
       b1[ot] += __shfl_xor(b1[ot], 32);
-      if (L.g == 0) gp[of.b1 + 16 * (2 * L.w + ot) + L.r16] = b1[ot];
+      if (L.g == 0) gp[of.b1 + 16 * (OT * L.w + ot) + L.r16] = b1[ot];
     }
   }
 }

@@ -77,7 +77,7 @@ __device__ __forceinline__ float dsilu(float z) {
 
 // Training tile: TT samples per workgroup of TN threads (eight waves: two to
 // a SIMD, so that one computes while the other waits; 60 steps of 5 members,
-// batch 1024: 2.36 ms, with four waves 2.55).
+// batch 512: 2.36 ms, with four waves 2.55).
 constexpr int TT = 32;
 constexpr int TN = 512;
 constexpr int OT = H / 16 / (TN / 64);  // 16-column tiles of a hidden layer per wave
@@ -482,6 +482,7 @@ __global__ void mlp_adam_kernel(int members, int tiles, int64_t P, const float *
   if (i >= (int64_t)members * P) return;
   const int64_t e = i / P, p = i - (i / P) * P;
   float g = 0.0f;
+#pragma unroll 16
   for (int t = 0; t < tiles; t++) g += grad_part[((size_t)e * tiles + t) * P + p];
   if (grad_out) grad_out[i] = g;
   if (update) {

@@ -212,7 +212,7 @@ int32_t eph_conductivity(eph_ctx *ctx, int64_t n_states, const double *energy_eV
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): same arguments, same kernels and the same bit-identical
  * result, but the reduction's workspace is a static device array of
- * 9,328 doubles (74,624 bytes) per GPU, set up by eph_load_wannier and held
+ * 9,252 doubles (74,016 bytes) per GPU, set up by eph_load_wannier and held
  * until the process ends; the call itself allocates nothing.  The workspace
  * does not grow with n_states, so the only size limit is n_temps <=
  * EPH_MAX_TEMPS (EPH_E_INVALID beyond it).  Every call on one GPU shares

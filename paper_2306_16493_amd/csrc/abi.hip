@@ -1048,16 +1048,16 @@ int32_t eph_stage_times(const eph_ctx *c, double *ms, int64_t *launches) {
 }  // extern "C"
 
 namespace {
-// Workspace of the conductivity reduction, in doubles: per-block partials
-// [3][kSigBlocks][EPH_MAX_TEMPS * 9] and the reduced moments
-// [3][EPH_MAX_TEMPS * 9].
+// Workspace of the conductivity reduction, in doubles: per moment the
+// per-block partials [kSigBlocks][EPH_MAX_TEMPS * 9] and the reduced moment
+// [EPH_MAX_TEMPS * 9].
 constexpr int kSigBlocks = 256;
-constexpr size_t kSigWorkDoubles = 3 * (size_t)(kSigBlocks + 1) * EPH_MAX_TEMPS * 9;
+constexpr size_t sig_work_doubles(int n_orders) { return (size_t)n_orders * (kSigBlocks + 1) * EPH_MAX_TEMPS * 9; }
 
 // Static device workspace of eph_conductivity_noalloc: one copy per GPU,
 // held until the process ends.  In host code `scratch` only names the
 // symbol; its device address comes from hipGetSymbolAddress (per device).
-static __device__ __align__(256) double scratch[kSigWorkDoubles];
+static __device__ __align__(256) double scratch[sig_work_doubles(1)];
 
 std::mutex g_scratch_mu;
 double *g_scratch_ptr[64] = {nullptr};
@@ -1083,7 +1083,7 @@ namespace {
 
 // Moments 0..n_orders-1 of the SERTA sum on the device inputs, into host
 // out[order][EPH_MAX_TEMPS * 9] (S/m times eV^order).  work is a device
-// buffer of kSigWorkDoubles; every part of it is written before it is read.
+// buffer of sig_work_doubles(n_orders); every part of it is written before it is read.
 int32_t moments(eph_ctx *c, int64_t n_states, const double *energy_eV, const double *vel_ms,
                 const double *inv_tau_s, double mu_eV, int32_t n_temps, const double *temps_K, int64_t n_kpoints,
                 void *stream, int n_orders, double (*out)[EPH_MAX_TEMPS * 9], double *work,
@@ -1091,7 +1091,7 @@ int32_t moments(eph_ctx *c, int64_t n_states, const double *energy_eV, const dou
   hipStream_t st = static_cast<hipStream_t>(stream);
   const Units U = units();
   double *part = work;
-  double *outd = part + 3 * (size_t)kSigBlocks * EPH_MAX_TEMPS * 9;
+  double *outd = part + (size_t)n_orders * kSigBlocks * EPH_MAX_TEMPS * 9;
   double kts[EPH_MAX_TEMPS];
   for (int t = 0; t < n_temps; t++) kts[t] = U.kb_evk * temps_K[t];
   const double pref = 2.0 * kCharge / ((double)n_kpoints * c->volume * 1e-30);
@@ -1126,7 +1126,7 @@ int32_t moments_ctx(eph_ctx *c, int64_t n_states, const double *energy_eV, const
   if (r != EPH_OK) return r;
   DeviceGuard dg(c->device);
   if (!dg.ok) return fail(c, EPH_E_DEVICE, "hipSetDevice failed");
-  EPH_HIP(c, c->sig_part.ensure(sizeof(double) * kSigWorkDoubles));
+  EPH_HIP(c, c->sig_part.ensure(sizeof(double) * sig_work_doubles(n_orders)));
   return moments(c, n_states, energy_eV, vel_ms, inv_tau_s, mu_eV, n_temps, temps_K, n_kpoints, stream, n_orders,
                  out, c->sig_part.as<double>());
 }
@@ -1219,7 +1219,7 @@ int32_t eph_bte_iterate(eph_ctx *c, const eph_gamma *g, const double *energy_eV,
   DeviceGuard dg(c->device);
   if (!dg.ok) return fail(c, EPH_E_DEVICE, "hipSetDevice failed");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  EPH_HIP(c, c->sig_part.ensure(sizeof(double) * kSigWorkDoubles));
+  EPH_HIP(c, c->sig_part.ensure(sizeof(double) * sig_work_doubles(1)));
   const size_t fsz = (size_t)nt * ns * 3;
   EPH_HIP(c, c->bte_f.ensure(sizeof(double) * 3 * std::max<size_t>(fsz, 1)));
   double *F0 = c->bte_f.as<double>(), *Fa = F0 + fsz, *Fb = Fa + fsz;

@@ -6,8 +6,9 @@
 // col = (Rp, mu, i); the state-side operand B (a phase times one
 // eigenvector component) is generated on the fly into LDS.
 //
-// What bounds it: the matrix cores.  The FP64 and FP32 products run there at
-// the vector units' rate, but read a sixteenth of the LDS per operation.  A
+// What bounds it: the matrix cores.  FP64 products run there at the vector
+// units' rate, FP32 ones at twice that of single (non-packed) instructions,
+// and both read a sixteenth of the LDS per operation.  A
 // workgroup makes a 64 x 64 tile of X, each of its four waves 2 x 2 blocks of
 // 16 x 16 complex elements, four real products per complex one.  A thread's
 // elements of B share their state and (with 4 or 8 bands) their R vector, so

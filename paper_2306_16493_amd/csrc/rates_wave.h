@@ -87,13 +87,14 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// exp(x) for x <= 0: x = n ln 2 + r, Taylor series of e^r to r^13 (|r| <=
-// 0.347: remainder below 5e-18), scaled by 2^n.  No special values to tell
-// apart, so 19 instructions.
+// exp(x) for x <= 0 by Cody and Waite's reduction x = n ln 2 + r (ln 2 as a
+// 32-bit head and a tail) and the Taylor series of e^r to r^13 (|r| <= 0.347:
+// remainder below 5e-18), scaled by 2^n.  No special values to tell apart, so
+// 19 instructions.
 __device__ __forceinline__ double exp_neg(double x) {
   x = fmax(x, -800.0);
   const double n = rint(x * 1.4426950408889634074);
-  double r = fma(n, -6.93147180369123816490e-01, x);  // ln 2 in two parts
+  double r = fma(n, -6.93147180369123816490e-01, x);  // head of ln 2, then its tail
   r = fma(n, -1.90821492927058770002e-10, r);
   double p = 1.0 / 6227020800.0;
   p = fma(p, r, 1.0 / 479001600.0);
@@ -139,8 +140,10 @@ struct WaveLayout {
   // one line's Z, padded by 16 bytes so that neighbouring lines start in
   // different LDS banks
   static constexpr int ZB = ROWS + (int)(16 / sizeof(C2));
-  // sieve passes (four entries each) whose table entries are loaded together
-  static constexpr int SG = NM == 3 ? (sizeof(T) == 8 ? 3 : 4) : 2;
+  // sieve passes (four entries each) whose table entries are loaded together:
+  // as many as the registers hold (Al-like 71^3, FP32, half of the states: 157
+  // ms with 3, 160 with 2 or 4)
+  static constexpr int SG = NM == 3 ? 3 : 2;
   // Planes of Y formed from one reading of X, where the LDS for the waiting
   // ones costs no workgroup per CU.  The rows of X in flight (20 KB each in
   // FP32) do not fit the L2s, and reading one for every plane took 85 of 387
@@ -537,7 +540,7 @@ void rates_wave_kernel(RatesArgs a) {
       //      vertices more take fewer chunks; its band ranges load meanwhile ----
       const int turn = (wave - rot) & (WPB - 1);  // this wave's turn in the round
       if (!more && b + 1 < nbatch) {
-        constexpr int kPassChunks = NM == 3 ? 64 : 256;  // groups of sieve that cost a pass
+        constexpr int kPassChunks = NM == 3 ? 32 : 256;  // groups of sieve that cost a pass
         const int nc = (min(nlb, N - (b + 1) * nlb) * N + 15) >> 4;
         const int heavy = ((total + 63) >> 6) % WPB, light = WPB - heavy;
         const int x = heavy ? max(0, nc - light * kPassChunks) / WPB : 0, rest_c = nc - heavy * x;

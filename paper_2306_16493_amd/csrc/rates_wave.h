@@ -31,9 +31,9 @@
 // planes are fixed, so results are bit-reproducible.
 //
 // What bounds it.  Al-like model (4 bands, 3 modes, box 6^3), 71^3, 3
-// temperatures, FP32: 332 ms for 1.2e10 vertices, about 155 ms of it the
-// vertices (some 700 FP32 instructions to 64 of them, half the time waiting
-// for their gathers), 90 the sieve, 30 Z, 45 the reading of X.  One wave per
+// temperatures, FP32: 322 ms for 1.2e10 vertices, about 170 ms of it the
+// vertices (534 vector instructions to a pass of 64), 85 the sieve, 27 Z, 18
+// the reading of X; vector instructions issue in nine cycles of ten.  One wave per
 // state and line, each with its own Z by vector operations, took 648 ms; 128
 // threads per workgroup leave fewer waves waiting at a barrier than 256.  The
 // tables are stored by plane and component so that the lanes' reads,

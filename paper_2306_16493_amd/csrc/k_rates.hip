@@ -102,7 +102,8 @@ __global__ __launch_bounds__(256) void rates_kernel(RatesArgs a) {
   int *sCnt = sLo + STM;
   int *sK1 = sCnt + STM;
   int *sTerms = sK1 + STM;  // kept terms of the current q-line
-  unsigned long long *sNq = reinterpret_cast<unsigned long long *>(sTerms + STM + (STM & 1));
+  static_assert(4 * STM * sizeof(int) % sizeof(unsigned long long) == 0, "the 64-bit counters are added to by LDS atomics");
+  unsigned long long *sNq = reinterpret_cast<unsigned long long *>(sTerms + STM);
   unsigned long long *sNt = sNq + SMAX;
   unsigned long long *sNkq = sNt + SMAX;  // [0] (k,q) pairs, [1] vertex contractions
   double *sEps = reinterpret_cast<double *>(sNkq + 2);  // sNkq holds 2 counters

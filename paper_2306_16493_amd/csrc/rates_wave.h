@@ -640,12 +640,13 @@ void rates_wave_kernel(RatesArgs a) {
             wi[mu] = ti;
           }
         }
-        // modes: with a = |g|^2 (d+ + d-), b = |g|^2 (d+ - d-), c = |g|^2 d-
-        // (d+- the Gaussians), sum_nu |g|^2 [(N + f) d+ + (1 + N - f) d-] =
-        // sum_nu N a + f sum_nu b + sum_nu c.  Every mode is evaluated and
-        // masked (about 5 of the 6 (nu, +-) terms of a vertex are kept, so
-        // branching would not save work).
-        T sb = 0, sc = 0, ct[NT];
+        // modes: with a = |g|^2 d+, b = |g|^2 d- (d+- the Gaussians),
+        // sum_nu |g|^2 [(N + f) d+ + (1 + N - f) d-] =
+        // sum_nu N (a + b) + f sum_nu a + (1 - f) sum_nu b, all terms >= 0: near
+        // f = 1 blocked emission must not cancel into what absorption leaves.
+        // Every mode is evaluated and masked (about 5 of the 6 (nu, +-) terms of
+        // a vertex are kept, so branching would not save work).
+        T sa = 0, sb = 0, ct[NT];
 #pragma unroll
         for (int t = 0; t < NT; t++) ct[t] = 0;
 #pragma unroll MU
@@ -686,8 +687,8 @@ void rates_wave_kernel(RatesArgs a) {
             dm = okm ? __builtin_amdgcn_exp2f(-xm * xm) : 0.f;
           }
           const T ga = g2 * (dp + dm);
-          sb = fma(g2, dp - dm, sb);
-          sc = fma(g2, dm, sc);
+          sa = fma(g2, dp, sa);
+          sb = fma(g2, dm, sb);
 #pragma unroll
           for (int t = 0; t < NT; t++) {
             T nq;
@@ -713,7 +714,7 @@ void rates_wave_kernel(RatesArgs a) {
             const double2 f2 = at_offset(reinterpret_cast<const double2 *>(occ_b) + (t / 2) * n2, (m * (uint32_t)(2 * n2) + e) * 16u);
             f = t % 2 ? f2.y : f2.x;
           }
-          ct[t] += fma(f, sb, sc);
+          ct[t] += fma(f, sa, (T(1) - f) * sb);
         }
         if (live) {
 #pragma unroll

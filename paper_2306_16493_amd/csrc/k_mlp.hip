@@ -63,11 +63,14 @@ __device__ __forceinline__ unsigned long long splitmix64(unsigned long long x) {
   return x ^ (x >> 31);
 }
 // logistic function with the hardware exponential, and the hardware reciprocal
-// with one Newton step, which rounds like the quotient but for rare cases (a few ulp;
-// the network is fit in FP32 to a target far coarser than that)
+// with one Newton step: within (|z| + 8) 2^-23 of its value, the |z| from the
+// exponent's rounding (the network is fit in FP32 to a target far coarser than
+// that).  Where e^-z overflows the reciprocal is 0 and the step's correction
+// NaN, which the maximum drops: the value is 0 there, however large -z, so that
+// z sigm(z) stays 0.
 __device__ __forceinline__ float sigm(float z) {
-  const float d = 1.0f + __expf(fminf(-z, 87.0f)), r = __builtin_amdgcn_rcpf(d);
-  return fmaf(fmaf(-d, r, 1.0f), r, r);  // 1 / d, d from 1 to 6.1e37
+  const float d = 1.0f + __expf(-z), r = __builtin_amdgcn_rcpf(d);
+  return fmaf(fmaxf(fmaf(-d, r, 1.0f), -1.0f), r, r);  // 1 / d
 }
 __device__ __forceinline__ float silu(float z) { return z * sigm(z); }
 __device__ __forceinline__ float dsilu(float z) {

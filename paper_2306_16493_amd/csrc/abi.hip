@@ -26,8 +26,8 @@ Units units() {
 
 // Electron tables (eps, V, v on the N^3 grid): the separable Bloch sum
 // when the H(R) list has a dense box, else the direct sum over the list.
-// energies_only leaves out V and v.
-hipError_t electron_tables(eph_ctx *c, int N, const Units &U, bool energies_only, hipStream_t st) {
+// n2 points per plane of the tables; energies_only leaves out V and v.
+hipError_t electron_tables(eph_ctx *c, int N, int64_t n2, const Units &U, bool energies_only, hipStream_t st) {
   const int64_t NQ = (int64_t)N * N * N;
   const int mode = energies_only ? 2 : 0;
   hipError_t e = c->eps.ensure(sizeof(double) * NQ * c->nw);
@@ -35,23 +35,23 @@ hipError_t electron_tables(eph_ctx *c, int N, const Units &U, bool energies_only
   if (e == hipSuccess && !energies_only) e = c->vel.ensure(sizeof(double) * NQ * c->nw * 3);
   if (e != hipSuccess) return e;
   if (c->hbox_n[0] > 0)
-    return launch_bloch_lines(mode, c->nw, N, c->hbox_lo, c->hbox_n, c->lattice, c->hbox.as<double2>(),
+    return launch_bloch_lines(mode, c->nw, N, n2, c->hbox_lo, c->hbox_n, c->lattice, c->hbox.as<double2>(),
                               c->tab.as<double2>(), nullptr, U.cph_ev, 0.0, U.vel_unit, c->eps.as<double>(),
                               c->evec.as<double2>(), c->vel.as<double>(), nullptr, st);
-  return launch_bloch_eig(mode, c->nw, N, NQ, c->nrh, c->rh.as<int>(), c->rh_w.as<double>(), c->rh_cart.as<double>(),
+  return launch_bloch_eig(mode, c->nw, N, n2, NQ, c->nrh, c->rh.as<int>(), c->rh_w.as<double>(), c->rh_cart.as<double>(),
                           c->ham.as<double2>(), c->tab.as<double2>(), nullptr, U.cph_ev, 0.0, U.vel_unit,
                           c->eps.as<double>(), c->evec.as<double2>(), c->vel.as<double>(), nullptr, st);
 }
 
 // Phonon tables (hbar w, u on the N^3 grid), the same two forms.
-hipError_t phonon_tables(eph_ctx *c, int N, const Units &U, double omega_cut, unsigned long long *n_excluded,
+hipError_t phonon_tables(eph_ctx *c, int N, int64_t n2, const Units &U, double omega_cut, unsigned long long *n_excluded,
                          hipStream_t st) {
   const int64_t NQ = (int64_t)N * N * N;
   if (c->dbox_n[0] > 0)
-    return launch_bloch_lines(1, c->nm, N, c->dbox_lo, c->dbox_n, c->lattice, c->dbox.as<double2>(),
+    return launch_bloch_lines(1, c->nm, N, n2, c->dbox_lo, c->dbox_n, c->lattice, c->dbox.as<double2>(),
                               c->tab.as<double2>(), c->mode_mass_d.as<double>(), U.cph_ev, omega_cut, U.vel_unit,
                               c->om.as<double>(), c->uu.as<double2>(), nullptr, n_excluded, st);
-  return launch_bloch_eig(1, c->nm, N, NQ, c->nrd, c->rd.as<int>(), c->rd_w.as<double>(), nullptr,
+  return launch_bloch_eig(1, c->nm, N, n2, NQ, c->nrd, c->rd.as<int>(), c->rd_w.as<double>(), nullptr,
                           c->dyn.as<double2>(), c->tab.as<double2>(), c->mode_mass_d.as<double>(), U.cph_ev,
                           omega_cut, U.vel_unit, c->om.as<double>(), c->uu.as<double2>(), nullptr, n_excluded, st);
 }
@@ -477,8 +477,9 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
   // phonons.  Without a state in the window the excluded modes are still
   // counted, below.
   const bool count_only = capacity == 0, list_only = states_only && !gr;
-  EPH_HIP(c, electron_tables(c, N, U, count_only, st));
-  if (!count_only && !list_only) EPH_HIP(c, phonon_tables(c, N, U, p->omega_cut_eV, ctr + 0, st));
+  const int64_t n2 = gwave > 0 && kbatch_q == 0 ? (int64_t)N * N : 1;  // points per plane of the tables
+  EPH_HIP(c, electron_tables(c, N, n2, U, count_only, st));
+  if (!count_only && !list_only) EPH_HIP(c, phonon_tables(c, N, n2, U, p->omega_cut_eV, ctr + 0, st));
   const bool fp32 = p->precision != EPH_FP64;
   EPH_HIP(c, tm.mark(&e_tables));
 
@@ -493,7 +494,7 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
   EPH_HIP(c, c->offs.ensure(sizeof(int64_t) * (nkl + 1)));
   EPH_HIP(c, c->scan_tmp.ensure(sizeof(int64_t) * scan_tmp_elems(nkl + 1)));
   EPH_HIP(c, launch_zero(c->cnt.as<int64_t>() + nkl, sizeof(int64_t), st));
-  EPH_HIP(c, launch_count_states(nkl, d_klist, N, nw, c->eps.as<double>(), blo, bhi, p->win_lo_eV, p->win_hi_eV,
+  EPH_HIP(c, launch_count_states(nkl, d_klist, n2, nw, c->eps.as<double>(), blo, bhi, p->win_lo_eV, p->win_hi_eV,
                                  c->cnt.as<int64_t>(), st));
   EPH_HIP(c, launch_scan(nkl + 1, c->cnt.as<int64_t>(), c->offs.as<int64_t>(), c->scan_tmp.as<int64_t>(), st));
   int64_t ns = 0;
@@ -506,9 +507,9 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
     if (counts) *counts = cn;
     return fail(c, EPH_E_TRUNCATED, "capacity below the number of states");
   }
-  EPH_HIP(c, launch_write_states(nkl, d_klist, N, nw, c->eps.as<double>(), c->vel.as<double>(), blo, bhi, p->win_lo_eV,
+  EPH_HIP(c, launch_write_states(nkl, d_klist, n2, nw, c->eps.as<double>(), c->vel.as<double>(), blo, bhi, p->win_lo_eV,
                                  p->win_hi_eV, c->offs.as<int64_t>(), state_k, state_n, energy_eV, vel_ms, st));
-  if (count_only && !list_only) EPH_HIP(c, phonon_tables(c, N, U, p->omega_cut_eV, ctr + 0, st));
+  if (count_only && !list_only) EPH_HIP(c, phonon_tables(c, N, n2, U, p->omega_cut_eV, ctr + 0, st));
   if (list_only) {
     EPH_HIP(c, hipStreamSynchronize(st));
     if (counts) *counts = cn;
@@ -849,15 +850,15 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
       int eb0, eb1, eb2;
       EPH_HIP(c, tm.mark(&eb0));
       if (p->precision == EPH_BF16X3)
-        EPH_HIP(c, launch_xform_bf16x3(sb - sa, state_k + sa, state_n + sa, N, nw, c->nre, c->re.as<int>(), ncol,
+        EPH_HIP(c, launch_xform_bf16x3(sb - sa, state_k + sa, state_n + sa, N, n2, nw, c->nre, c->re.as<int>(), ncol,
                                        c->wtbf.p, c->abf.p, c->evec.as<double2>(), c->tab.as<double2>(),
                                        c->xbuf.as<float2>(), st));
       else if (fp32)
-        EPH_HIP(c, launch_xform32(sb - sa, state_k + sa, state_n + sa, N, nw, c->nre, c->re.as<int>(), ncol,
+        EPH_HIP(c, launch_xform32(sb - sa, state_k + sa, state_n + sa, N, n2, nw, c->nre, c->re.as<int>(), ncol,
                                   c->wt32.as<float2>(), c->evec.as<double2>(), c->tab.as<double2>(),
                                   c->xbuf.as<float2>(), st));
       else
-        EPH_HIP(c, launch_xform64(sb - sa, state_k + sa, state_n + sa, N, nw, c->nre, c->re.as<int>(), ncol,
+        EPH_HIP(c, launch_xform64(sb - sa, state_k + sa, state_n + sa, N, n2, nw, c->nre, c->re.as<int>(), ncol,
                                   c->wt64.as<double2>(), c->evec.as<double2>(), c->tab.as<double2>(),
                                   c->xbuf.as<double2>(), st));
       a.ng = g1 - g0;
@@ -1300,7 +1301,7 @@ int32_t eph_carrier_density(eph_ctx *c, int32_t grid, int32_t band_lo, int32_t b
   // band energies on the full grid (the electron half of the grid tables)
   EPH_HIP(c, c->tab.ensure(sizeof(double2) * N));
   EPH_HIP(c, launch_phase_table(N, c->tab.as<double2>(), st));
-  EPH_HIP(c, electron_tables(c, N, U, true, st));
+  EPH_HIP(c, electron_tables(c, N, (int64_t)N * N, U, true, st));
   const int nblk = 256;
   EPH_HIP(c, c->sig_part.ensure(sizeof(double) * (size_t)(nblk + 1) * EPH_MAX_TEMPS));
   double *part = c->sig_part.as<double>();

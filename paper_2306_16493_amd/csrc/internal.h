@@ -57,6 +57,11 @@ struct DevBuf {
 // modes, mode-matrix elements) are kept by i3 plane, each component of a
 // plane contiguous over its N^2 points, so that neighbouring points are read
 // together: element (k, c) of nc components is at plane_at(k, c, nc, N^2).
+// That is for the wave kernel, whose lanes are neighbours in p and q; the
+// workgroup form, whose lanes lie scattered along a line, and the k-batch order
+// gather whole points and have them contiguous, k nc + c: one point to a plane
+// (Al-like 40^3, Rp box 3^3, FP32: 138.7 ms, 145.3 by plane; k-batch order,
+// Si-like 8^3: 394 and 405 ms).
 __host__ __device__ inline int64_t plane_at(int64_t k, int c, int nc, int64_t n2) {
   return ((k / n2) * nc + c) * n2 + k % n2;
 }
@@ -149,12 +154,13 @@ struct eph_gamma {
 namespace eph {
 
 // ---- launchers (each returns the launch error) ----
-// Bloch sum + Hermitian eigensolve on grid points [0, nk).
+// Bloch sum + Hermitian eigensolve on grid points [0, nk); n2 points per plane
+// of the tables (plane_at).
 //  mode 0 (electrons): eval (k, n), evec (k, m n + i) = V_im, vel[k][n][3] (m/s)
 //  mode 1 (phonons):   eval (k, nu) = hbar w (eV), evec (k, nu n + mu) = u_{mu nu}
 //                      (A), zero for hbar w < omega_cut; counts excluded modes
 //  mode 2:             mode 0's eval alone
-hipError_t launch_bloch_eig(int mode, int n, int N, int64_t nk, int nr, const int *R,
+hipError_t launch_bloch_eig(int mode, int n, int N, int64_t n2, int64_t nk, int nr, const int *R,
                             const double *w, const double *Rcart, const double2 *M, const double2 *tab,
                             const double *mode_mass, double cph, double omega_cut, double vel_unit,
                             double *eval, double2 *evec, double *vel, unsigned long long *n_excluded,
@@ -165,17 +171,17 @@ hipError_t launch_phase_table(int N, double2 *tab, hipStream_t st);
 // matrices on the box [lo, lo + nb) of R vectors (zero where the list has
 // no vector), nb[0] <= kBoxMaxR1; lattice as rows a1, a2, a3 (Angstrom).
 constexpr int kBoxMaxR1 = 12;
-hipError_t launch_bloch_lines(int mode, int n, int N, const int *lo, const int *nb, const double *lattice,
+hipError_t launch_bloch_lines(int mode, int n, int N, int64_t n2, const int *lo, const int *nb, const double *lattice,
                               const double2 *Mb, const double2 *tab, const double *mode_mass, double cph,
                               double omega_cut, double vel_unit, double *eval, double2 *evec, double *vel,
                               unsigned long long *n_excluded, hipStream_t st);
 
 // State selection.  cnt/offs sized nklist+1.
-hipError_t launch_count_states(int64_t nklist, const int64_t *klist, int N, int nw, const double *eps, int blo,
+hipError_t launch_count_states(int64_t nklist, const int64_t *klist, int64_t n2, int nw, const double *eps, int blo,
                                int bhi, double wlo, double whi, int64_t *cnt, hipStream_t st);
 hipError_t launch_scan(int64_t n, const int64_t *in, int64_t *out_excl, int64_t *tmp, hipStream_t st);
 size_t scan_tmp_elems(int64_t n);
-hipError_t launch_write_states(int64_t nklist, const int64_t *klist, int N, int nw, const double *eps,
+hipError_t launch_write_states(int64_t nklist, const int64_t *klist, int64_t n2, int nw, const double *eps,
                                const double *vel, int blo, int bhi, double wlo, double whi,
                                const int64_t *offs, int32_t *sk, int32_t *sn, double *se, double *sv,
                                hipStream_t st);
@@ -190,10 +196,10 @@ hipError_t launch_line_sort(int N, int nw, const double *eps, double *line_e, ui
 
 // Re transform fused with the j->n rotation:
 //   X[s][rp][mu][i] = sum_{Re,j} Wt[(Re,j)][(rp,mu,i)] e^{i k_s.Re} V_{j n_s}(k_s)
-hipError_t launch_xform64(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int nw, int nre,
+hipError_t launch_xform64(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int64_t n2, int nw, int nre,
                           const int *re, int ncol, const double2 *wt, const double2 *evec,
                           const double2 *tab, double2 *X, hipStream_t st);
-hipError_t launch_xform32(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int nw, int nre,
+hipError_t launch_xform32(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int64_t n2, int nw, int nre,
                           const int *re, int ncol, const float2 *wt, const double2 *evec,
                           const double2 *tab, float2 *X, hipStream_t st);
 hipError_t launch_to_f32(int64_t n, const double2 *in, float2 *out, hipStream_t st);
@@ -203,7 +209,7 @@ size_t bf16_w_elems(int nre, int nw, int ncol);
 size_t bf16_a_elems(int nre, int nw);
 hipError_t launch_split_bf16(int nre, int nw, int ncol, const double2 *wt, void *out, hipStream_t st);
 // abf: workspace of 2 * ns * bf16_a_elems bf16 values (the state operand, hi and lo)
-hipError_t launch_xform_bf16x3(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int nw, int nre,
+hipError_t launch_xform_bf16x3(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int64_t n2, int nw, int nre,
                                const int *re, int ncol, const void *wbf, void *abf, const double2 *evec,
                                const double2 *tab, float2 *X, hipStream_t st);
 
@@ -237,7 +243,7 @@ struct RatesArgs {
   const int64_t *gstart;           // [ng+1] absolute state indices
   int64_t s_base;                  // state index of X row 0
   const int32_t *sk, *sn;
-  // grid tables by plane_at: energies (k, m), (q, nu) (inf below omega_cut for
+  // grid tables by plane_at (wave kernel; by point otherwise): energies (k, m), (q, nu) (inf below omega_cut for
   // the wave kernel), eigenvectors (k, m nw + i),
   // mode matrices (q, nu nm + mu)
   const double *eps, *om;

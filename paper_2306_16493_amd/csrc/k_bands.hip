@@ -500,12 +500,12 @@ hipError_t launch_phase_table(int N, double2 *tab, hipStream_t st) {
       }                        \
   }
 
-hipError_t launch_bloch_eig(int mode, int n, int N, int64_t nk, int nr, const int *R, const double *w,
-                            const double *Rcart, const double2 *M, const double2 *tab, const double *mode_mass,
+hipError_t launch_bloch_eig(int mode, int n, int N, int64_t n2, int64_t nk, int nr, const int *R,
+                            const double *w, const double *Rcart, const double2 *M, const double2 *tab, const double *mode_mass,
                             double cph, double omega_cut, double vel_unit, double *eval, double2 *evec, double *vel,
                             unsigned long long *n_excluded, hipStream_t st) {
   if (nk <= 0) return hipSuccess;
-  const EigOut o{(int64_t)N * N, mode_mass, cph, omega_cut, vel_unit, eval, evec, vel, n_excluded};
+  const EigOut o{n2, mode_mass, cph, omega_cut, vel_unit, eval, evec, vel, n_excluded};
   const int64_t ngroups = (nk * pow2_up(n) + 63) / 64;
   const int grid = (int)(ngroups < 262144 ? ngroups : 262144);
 #define EPH_GO(NE, MODE)                                                                                             \
@@ -517,11 +517,11 @@ hipError_t launch_bloch_eig(int mode, int n, int N, int64_t nk, int nr, const in
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_bloch_lines(int mode, int n, int N, const int *lo, const int *nb, const double *lattice,
+hipError_t launch_bloch_lines(int mode, int n, int N, int64_t n2, const int *lo, const int *nb, const double *lattice,
                               const double2 *Mb, const double2 *tab, const double *mode_mass, double cph,
                               double omega_cut, double vel_unit, double *eval, double2 *evec, double *vel,
                               unsigned long long *n_excluded, hipStream_t st) {
-  const EigOut o{(int64_t)N * N, mode_mass, cph, omega_cut, vel_unit, eval, evec, vel, n_excluded};
+  const EigOut o{n2, mode_mass, cph, omega_cut, vel_unit, eval, evec, vel, n_excluded};
   if (nb[0] > kBoxMaxR1) return hipErrorInvalidValue;
   BoxArgs bx;
   for (int a = 0; a < 3; a++) {

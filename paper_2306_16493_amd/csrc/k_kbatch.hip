@@ -41,7 +41,7 @@ __global__ void kb_step1_kernel(int64_t q0, int nb, int N, RpBox box, int nre, i
         ph += ph < 0 ? N : 0;
         const double2 f = tab[ph];
         for (int mu = 0; mu < nm; mu++) {
-          const double2 u = uu[plane_at(q, nu * nm + mu, nm * nm, (int64_t)N * N)];
+          const double2 u = uu[(q * nm + nu) * nm + mu];
           const double2 g = wt[((size_t)r * nw + j) * ncol + ((size_t)p * nm + mu) * nw + i];
           const double fr = f.x * u.x - f.y * u.y, fi = f.x * u.y + f.y * u.x;  // e^{iq.Rp} u_{mu nu}
           sr = fma(fr, g.x, sr);
@@ -62,11 +62,10 @@ __global__ __launch_bounds__(64) void kb_step2_kernel(KBatchArgs a) {
   const int64_t s = blockIdx.x;
   if (s >= a.ns) return;
   const int N = a.N;
-  const int64_t n2 = (int64_t)N * N;
   const int64_t k = a.sk[s];
   const int n = a.sn[s];
   const int k1 = (int)(k % N), k2 = (int)((k / N) % N), k3 = (int)(k / ((int64_t)N * N));
-  const double es = a.eps[plane_at(k, n, NW, n2)];
+  const double es = a.eps[k * NW + n];
   const double cut = a.sw * a.eta, inv_eta = 1.0 / a.eta, dnorm = 1.0 / (1.7724538509055160273 * a.eta);
   double acc[EPH_MAX_TEMPS] = {0.0, 0.0, 0.0, 0.0};
   int64_t nq_valid = 0, nterms = 0;
@@ -78,7 +77,7 @@ __global__ __launch_bounds__(64) void kb_step2_kernel(KBatchArgs a) {
     unsigned okp = 0u, okm = 0u;
     if (lane < NW * NM) {
       const int m = lane / NM, nu = lane % NM;
-      const double w = a.om[plane_at(q, nu, NM, n2)], ep = a.eps[plane_at(pidx, m, NW, n2)];
+      const double w = a.om[q * NM + nu], ep = a.eps[pidx * NW + m];
       const bool live = w >= a.wcut;
       okp = (live && fabs(es + w - ep) <= cut) ? 1u : 0u;
       okm = (live && fabs(es - w - ep) <= cut) ? 1u : 0u;
@@ -110,26 +109,26 @@ __global__ __launch_bounds__(64) void kb_step2_kernel(KBatchArgs a) {
       for (int i = 0; i < NW; i++) {
         double ur = 0.0, ui = 0.0;  // sum_j G(nu, i, j) V_jn(k)
         for (int j = 0; j < NW; j++) {
-          const double2 g = sG[(nu * NW + i) * NW + j], v = a.evec[plane_at(k, n * NW + j, NW * NW, n2)];
+          const double2 g = sG[(nu * NW + i) * NW + j], v = a.evec[(k * NW + n) * NW + j];
           ur = fma(g.x, v.x, ur);
           ur = fma(-g.y, v.y, ur);
           ui = fma(g.x, v.y, ui);
           ui = fma(g.y, v.x, ui);
         }
-        const double2 vp = a.evec[plane_at(pidx, m * NW + i, NW * NW, n2)];  // conj(V_im(k+q))
+        const double2 vp = a.evec[(pidx * NW + m) * NW + i];  // conj(V_im(k+q))
         tr = fma(vp.x, ur, tr);
         tr = fma(vp.y, ui, tr);
         ti = fma(vp.x, ui, ti);
         ti = fma(-vp.y, ur, ti);
       }
       const double g2 = tr * tr + ti * ti;
-      const double w = a.om[plane_at(q, nu, NM, n2)], ep = a.eps[plane_at(pidx, m, NW, n2)];
+      const double w = a.om[q * NM + nu], ep = a.eps[pidx * NW + m];
       const double xp = es + w - ep, xm = es - w - ep;
       const double dp = okp ? exp(-(xp * inv_eta) * (xp * inv_eta)) * dnorm : 0.0;
       const double dm = okm ? exp(-(xm * inv_eta) * (xm * inv_eta)) * dnorm : 0.0;
       for (int t = 0; t < EPH_MAX_TEMPS; t++) {
-        const double nq = a.occ_n[plane_at(q, nu, NM, n2) * EPH_MAX_TEMPS + t];
-        const double fo = a.occ_f[plane_at(pidx, m, NW, n2) * EPH_MAX_TEMPS + t];
+        const double nq = a.occ_n[(q * NM + nu) * EPH_MAX_TEMPS + t];
+        const double fo = a.occ_f[(pidx * NW + m) * EPH_MAX_TEMPS + t];
         acc[t] = fma(g2, fma(nq + fo, dp, (1.0 + nq - fo) * dm), acc[t]);
       }
     }

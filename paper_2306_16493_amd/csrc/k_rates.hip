@@ -80,7 +80,6 @@ __global__ __launch_bounds__(256) void rates_kernel(RatesArgs a) {
   constexpr int C = NW * NM;
   extern __shared__ __align__(16) unsigned char smem[];
   const int N = a.N;
-  const int64_t NN = (int64_t)N * N;
   const int n1 = a.box.n[0], n2 = a.box.n[1], n3 = a.box.n[2];
   const int lo1 = a.box.lo[0], lo2 = a.box.lo[1], lo3 = a.box.lo[2];
   const int nbox = n1 * n2 * n3;
@@ -136,7 +135,7 @@ __global__ __launch_bounds__(256) void rates_kernel(RatesArgs a) {
     if (tid < ST) {
       int64_t k = a.sk[s0 + tid];
       sK1[tid] = (int)(k % N);
-      sEps[tid] = a.eps[plane_at(k, a.sn[s0 + tid], NW, NN)];
+      sEps[tid] = a.eps[k * NW + a.sn[s0 + tid]];
     }
     if (tid < SMAX) {
       sNq[tid] = 0;
@@ -189,6 +188,10 @@ __global__ __launch_bounds__(256) void rates_kernel(RatesArgs a) {
         sZ[(s * n1 + p1) * C + c] = mk<T>(zr, zi);
       }
       const int64_t line = (int64_t)((k2 + q2) % N) + (int64_t)N * ((k3 + q3) % N);
+      // rows of the tables of this q-line and p-line
+      const int64_t qline = (int64_t)q2 + (int64_t)N * q3;
+      const double *om_q = a.om + qline * N * NM;
+      const int64_t v0 = line * N * (NW * NW), u0 = qline * N * (NM * NM);
       for (int t = tid; t < LN; t += 256) {
         sLE[t] = a.line_e[line * LN + t];
         sLK[t] = a.line_key[line * LN + t];
@@ -216,14 +219,12 @@ __global__ __launch_bounds__(256) void rates_kernel(RatesArgs a) {
         const int key = sLK[jj];
         const int p1 = key / NW, m = key % NW;
         const int q1 = pmod(p1 - sK1[s], N);
-        const int64_t qidx = q1 + (int64_t)N * (q2 + (int64_t)N * q3);
-        const int64_t pidx = p1 + (int64_t)N * line;
         const double es = sEps[s], ep = sLE[jj];
         double om[NM];
         unsigned vp = 0, vm = 0;
 #pragma unroll
         for (int nu = 0; nu < NM; nu++) {
-          om[nu] = a.om[plane_at(qidx, nu, NM, NN)];
+          om[nu] = om_q[q1 * NM + nu];
           bool ok = om[nu] >= a.wcut;
           vp |= (ok && fabs(es + om[nu] - ep) <= cut) ? (1u << nu) : 0u;
           vm |= (ok && fabs(es - om[nu] - ep) <= cut) ? (1u << nu) : 0u;
@@ -238,9 +239,9 @@ __global__ __launch_bounds__(256) void rates_kernel(RatesArgs a) {
 #pragma unroll
         for (int i = 0; i < NW; i++) {
           if constexpr (sizeof(T) == 8) {
-            vrow[i] = a.evec[plane_at(pidx, m * NW + i, NW * NW, NN)];
+            vrow[i] = a.evec[v0 + (p1 * NW + m) * NW + i];
           } else {
-            vrow[i] = a.evec32[plane_at(pidx, m * NW + i, NW * NW, NN)];
+            vrow[i] = a.evec32[v0 + (p1 * NW + m) * NW + i];
           }
         }
         T wr[NM], wi[NM];
@@ -276,9 +277,9 @@ __global__ __launch_bounds__(256) void rates_kernel(RatesArgs a) {
           for (int mu = 0; mu < NM; mu++) {
             C2 u;
             if constexpr (sizeof(T) == 8) {
-              u = a.uu[plane_at(qidx, nu * NM + mu, NM * NM, NN)];
+              u = a.uu[u0 + (q1 * NM + nu) * NM + mu];
             } else {
-              u = a.uu32[plane_at(qidx, nu * NM + mu, NM * NM, NN)];
+              u = a.uu32[u0 + (q1 * NM + nu) * NM + mu];
             }
             gr += wr[mu] * u.x - wi[mu] * u.y;
             gi += wr[mu] * u.y + wi[mu] * u.x;

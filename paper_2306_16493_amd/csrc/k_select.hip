@@ -107,7 +107,7 @@ __global__ __launch_bounds__(256) void line_sort_kernel(int N, int nw, const dou
   for (int t = threadIdx.x; t < P; t += blockDim.x) {
     if (t < cnt) {
       int i1 = t / nw, m = t % nw;
-      se[t] = eps[plane_at(line * N + i1, m, nw, (int64_t)N * N)];
+      se[t] = eps[(line * N + i1) * nw + m];
       sk[t] = (uint16_t)t;
     } else {
       se[t] = __builtin_huge_val();
@@ -166,20 +166,20 @@ hipError_t launch_scan(int64_t n, const int64_t *in, int64_t *out_excl, int64_t 
   return hipGetLastError();
 }
 
-hipError_t launch_count_states(int64_t nklist, const int64_t *klist, int N, int nw, const double *eps, int blo, int bhi,
-                               double wlo, double whi, int64_t *cnt, hipStream_t st) {
+hipError_t launch_count_states(int64_t nklist, const int64_t *klist, int64_t n2, int nw, const double *eps, int blo,
+                               int bhi, double wlo, double whi, int64_t *cnt, hipStream_t st) {
   if (nklist <= 0) return hipSuccess;
-  hipLaunchKernelGGL(count_states_kernel, dim3((nklist + 255) / 256), dim3(256), 0, st, nklist, klist,
-                     (int64_t)N * N, nw, eps, blo, bhi, wlo, whi, cnt);
+  hipLaunchKernelGGL(count_states_kernel, dim3((nklist + 255) / 256), dim3(256), 0, st, nklist, klist, n2, nw,
+                     eps, blo, bhi, wlo, whi, cnt);
   return hipGetLastError();
 }
 
-hipError_t launch_write_states(int64_t nklist, const int64_t *klist, int N, int nw, const double *eps, const double *vel,
-                               int blo, int bhi, double wlo, double whi, const int64_t *offs, int32_t *sk,
-                               int32_t *sn, double *se, double *sv, hipStream_t st) {
+hipError_t launch_write_states(int64_t nklist, const int64_t *klist, int64_t n2, int nw, const double *eps,
+                               const double *vel, int blo, int bhi, double wlo, double whi, const int64_t *offs,
+                               int32_t *sk, int32_t *sn, double *se, double *sv, hipStream_t st) {
   if (nklist <= 0) return hipSuccess;
-  hipLaunchKernelGGL(write_states_kernel, dim3((nklist + 255) / 256), dim3(256), 0, st, nklist, klist,
-                     (int64_t)N * N, nw, eps, vel, blo, bhi, wlo, whi, offs, sk, sn, se, sv);
+  hipLaunchKernelGGL(write_states_kernel, dim3((nklist + 255) / 256), dim3(256), 0, st, nklist, klist, n2, nw,
+                     eps, vel, blo, bhi, wlo, whi, offs, sk, sn, se, sv);
   return hipGetLastError();
 }
 

@@ -54,7 +54,7 @@ struct Mat<double> {
 // T = accumulation/operand type (double for the FP64 form, float for FP32).
 template <class T, int NW>
 __global__ __launch_bounds__(256) void xform_kernel(int64_t ns, const int32_t *__restrict__ sk,
-                                                    const int32_t *__restrict__ sn, int N, int nre,
+                                                    const int32_t *__restrict__ sn, int N, int64_t n2, int nre,
                                                     const int *__restrict__ re, int ncol, int64_t nrow_blocks,
                                                     int64_t nblocks, const typename V2<T>::t *__restrict__ wt,
                                                     const double2 *__restrict__ evec,
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(256) void xform_kernel(int64_t ns, const int32_t *_
     k2 = (k / N) % N;
     k3 = k / (N * N);
 #pragma unroll
-    for (int q = 0; q < kSlots; q++) v[q] = evec[plane_at(k, n * NW + (kq + q) % NW, NW * NW, (int64_t)N * N)];
+    for (int q = 0; q < kSlots; q++) v[q] = evec[plane_at(k, n * NW + (kq + q) % NW, NW * NW, n2)];
   }
   const float inv_n = 1.0f / (float)N;
 
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(256) void xform_kernel(int64_t ns, const int32_t *_
 }
 
 template <class T>
-hipError_t launch(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int nw, int nre, const int *re, int ncol,
+hipError_t launch(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int64_t n2, int nw, int nre, const int *re, int ncol,
                   const typename V2<T>::t *wt, const double2 *evec, const double2 *tab, typename V2<T>::t *X,
                   hipStream_t st) {
   if (ns <= 0) return hipSuccess;
@@ -182,8 +182,8 @@ hipError_t launch(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int n
   const size_t sh = sizeof(double2) * N;
 #define EPH_XF(NW)                                                                                                  \
   case NW:                                                                                                          \
-    hipLaunchKernelGGL((xform_kernel<T, NW>), grid, dim3(256), sh, st, ns, sk, sn, N, nre, re, ncol, nrow, nblocks, \
-                       wt, evec, tab, X);                                                                           \
+    hipLaunchKernelGGL((xform_kernel<T, NW>), grid, dim3(256), sh, st, ns, sk, sn, N, n2, nre, re, ncol, nrow,     \
+                       nblocks, wt, evec, tab, X);                                                                  \
     return hipGetLastError();
   switch (nw) {
     EPH_XF(1)
@@ -197,16 +197,16 @@ hipError_t launch(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int n
 
 }  // namespace
 
-hipError_t launch_xform64(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int nw, int nre, const int *re,
+hipError_t launch_xform64(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int64_t n2, int nw, int nre, const int *re,
                           int ncol, const double2 *wt, const double2 *evec, const double2 *tab, double2 *X,
                           hipStream_t st) {
-  return launch<double>(ns, sk, sn, N, nw, nre, re, ncol, wt, evec, tab, X, st);
+  return launch<double>(ns, sk, sn, N, n2, nw, nre, re, ncol, wt, evec, tab, X, st);
 }
 
-hipError_t launch_xform32(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int nw, int nre, const int *re,
+hipError_t launch_xform32(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int64_t n2, int nw, int nre, const int *re,
                           int ncol, const float2 *wt, const double2 *evec, const double2 *tab, float2 *X,
                           hipStream_t st) {
-  return launch<float>(ns, sk, sn, N, nw, nre, re, ncol, wt, evec, tab, X, st);
+  return launch<float>(ns, sk, sn, N, n2, nw, nre, re, ncol, wt, evec, tab, X, st);
 }
 
 }  // namespace eph

@@ -41,7 +41,7 @@ __host__ __device__ inline int padk(int k2) { return (k2 + TK - 1) / TK * TK; }
 
 // A hi/lo [ns][KP] of the states: one thread per (state, kk).
 __global__ void state_operand_kernel(int64_t ns, const int32_t *__restrict__ sk, const int32_t *__restrict__ sn,
-                                     int N, int nw, int K, int KP, const int *__restrict__ re,
+                                     int N, int64_t n2, int nw, int K, int KP, const int *__restrict__ re,
                                      const double2 *__restrict__ evec, const double2 *__restrict__ tab,
                                      __bf16 *__restrict__ ahi, __bf16 *__restrict__ alo) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -61,7 +61,7 @@ __global__ void state_operand_kernel(int64_t ns, const int32_t *__restrict__ sk,
   // phase index (k.Re mod N) in 32-bit integers: |k_i re_i| < 2^31
   int ph = (k1 * re[3 * ir] % N + k2 * re[3 * ir + 1] % N + k3 * re[3 * ir + 2] % N) % N;
   ph += ph < 0 ? N : 0;
-  const double2 p = tab[ph], e = evec[plane_at(k, n * nw + j, nw * nw, (int64_t)N * N)];
+  const double2 p = tab[ph], e = evec[plane_at(k, n * nw + j, nw * nw, n2)];
   __bf16 h, l;
   split_bf16((float)(p.x * e.x - p.y * e.y), h, l);
   rh[kk] = h;
@@ -217,7 +217,7 @@ hipError_t launch_split_bf16(int nre, int nw, int ncol, const double2 *wt, void 
   return hipGetLastError();
 }
 
-hipError_t launch_xform_bf16x3(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int nw, int nre,
+hipError_t launch_xform_bf16x3(int64_t ns, const int32_t *sk, const int32_t *sn, int N, int64_t n2, int nw, int nre,
                                const int *re, int ncol, const void *wbf, void *abf, const double2 *evec,
                                const double2 *tab, float2 *X, hipStream_t st) {
   if (ns <= 0) return hipSuccess;
@@ -226,8 +226,8 @@ hipError_t launch_xform_bf16x3(int64_t ns, const int32_t *sk, const int32_t *sn,
   const __bf16 *whi = static_cast<const __bf16 *>(wbf), *wlo = whi + nw_el;
   __bf16 *ahi = static_cast<__bf16 *>(abf), *alo = ahi + (size_t)ns * KP;
   const int64_t na = ns * KP;
-  hipLaunchKernelGGL(state_operand_kernel, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, st, ns, sk, sn, N, nw,
-                     K, KP, re, evec, tab, ahi, alo);
+  hipLaunchKernelGGL(state_operand_kernel, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, st, ns, sk, sn, N, n2,
+                     nw, K, KP, re, evec, tab, ahi, alo);
   const int tiles_m = (int)((ns + TM - 1) / TM), tiles_n = (ncol2 + TN - 1) / TN;
   const int64_t ntile = (int64_t)tiles_m * tiles_n;
   const int64_t grid = (ntile + 7) / 8 * 8;

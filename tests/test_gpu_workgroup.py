@@ -2,7 +2,7 @@
 cubes of edge 4 and 6, at each (orbitals, modes) shape: models cut to a 3^3 or
 3 x 4 x 4 box, or to one orbital, against the oracle.
 
-Tolerances as for the other grids: 1e-10 per state in FP64, 1e-4 in FP32,
+Tolerances as for the other grids: 1e-10 per state in FP64, 1e-4 in FP32 and BF16x3,
 counts equal.
 """
 import dataclasses
@@ -38,7 +38,7 @@ def cut(s, box, nw=None):
 @pytest.mark.parametrize("name,nw,box,N,prec", [
     ("mini_w1", 1, (3, 3, 3), 6, "fp64"), ("mini_w1", 1, (3, 4, 4), 5, "fp32"), ("mini_w2a2", 1, (3, 3, 3), 5, "fp64"),
     ("chain_w2", 2, (3, 4, 4), 5, "fp64"), ("toy_sc", 4, (3, 3, 3), 5, "fp64"), ("mini_w8", 8, (3, 3, 3), 5, "fp64"),
-    ("mini_w8", 8, (3, 4, 4), 5, "fp32"), ("mini_w2a2", 2, (3, 3, 3), 5, "fp64"),
+    ("mini_w8", 8, (3, 4, 4), 5, "fp32"), ("toy_sc", 4, (3, 4, 4), 5, "bf16x3"), ("mini_w2a2", 2, (3, 3, 3), 5, "fp64"),
     ("mini_w4a2", 4, (3, 4, 4), 5, "fp64"), ("si_fcc", 8, (3, 3, 3), 4, "fp64"), ("si_fcc", 8, (3, 3, 3), 4, "fp32")])
 def test_every_shape(torch_cuda, name, nw, box, N, prec):
     from paper_2306_16493_amd import Context

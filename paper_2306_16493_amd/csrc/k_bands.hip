@@ -295,6 +295,15 @@ __device__ __forceinline__ void eig_store(const EigOut &o, bool live, int64_t kl
   }
 }
 
+// Direct sum over the R list, a wave per 64 / NP points.  With 3 columns and
+// more to a matrix its lanes share the phases (weights in them): they are formed
+// together for a run of R vectors, each by one lane, and wait in LDS, while the
+// next matrix column loads; with 1 or 2 each lane forms its own, four at a time.
+// What bounds it on a small grid is the chain of a pass over the list (four
+// passes: H and its derivatives), on a large one the phases and the Jacobi.
+// Tables, 87 R vectors each: 4 bands and 3 modes, 16^3: 0.125 ms (0.219 with a
+// phase per lane and pass, its remainder of 64-bit integers), 100^3: 4.0 (5.2);
+// 8 and 6, 80^3: 9.0 (12.8); 1 and 3, 100^3: 1.5 (1.9), 2.0 with shared phases.
 template <int NE, int MODE>
 __global__ __launch_bounds__(64) void bloch_eig_kernel(EigOut o, int N, int64_t nk, int nr,
                                                        const int *__restrict__ R, const double *__restrict__ w,
@@ -302,50 +311,85 @@ __global__ __launch_bounds__(64) void bloch_eig_kernel(EigOut o, int N, int64_t 
                                                        const double2 *__restrict__ M,
                                                        const double2 *__restrict__ tab) {
   constexpr int NP = pow2_up(NE), MPW = 64 / NP;
+  constexpr bool kShare = NE > 2;
+  constexpr int RC = 512 / MPW;  // R vectors to a run
   __shared__ double2 stage[MODE == kElectrons ? stage_bytes(NE) / sizeof(double2) : 1];
+  __shared__ double2 sPh[kShare ? RC * MPW : 1];  // [R][point]
   const int lane = threadIdx.x;
   const Cols m{lane % NP, 4 * (lane / NP * NP)};
   const int jc = min(m.j, NE - 1);
+  const float inv_n = 1.0f / (float)N;
 
   const int64_t ngroups = (nk + MPW - 1) / MPW;
   for (int64_t gidx = blockIdx.x; gidx < ngroups; gidx += gridDim.x) {
     const int64_t kl = gidx * MPW + lane / NP;
     const bool live = kl < nk;
-    const int64_t kg = live ? kl : 0;
-    const int64_t k1 = kg % N, k2 = (kg / N) % N, k3 = kg / ((int64_t)N * N);
-    // ---- Bloch sum, direct over the R list ----
-    auto phase = [&](int r) {
-      int64_t s = (k1 * R[3 * r] + k2 * R[3 * r + 1] + k3 * R[3 * r + 2]) % N;
-      if (s < 0) s += N;
-      double2 ph = tab[s];
+    const int64_t kp = min(gidx * MPW + (kShare ? lane % MPW : lane / NP), nk - 1);  // whose phases the lane forms
+    const int k1 = (int)(kp % N), k2 = (int)((kp / N) % N), k3 = (int)(kp / ((int64_t)N * N));
+    auto phase = [&](int r) __attribute__((always_inline)) {
+      // k . R mod N: below 3 N^2 < 2^20, so the float quotient is off by one at most
+      const int a = k1 * imod(R[3 * r], N) + k2 * imod(R[3 * r + 1], N) + k3 * imod(R[3 * r + 2], N);
+      int s = a - (int)((float)a * inv_n) * N;
+      s += (s < 0) ? N : 0;
+      s -= (s >= N) ? N : 0;
+      const double2 ph = tab[s];
       const double wr = w[r];
-      ph.x *= wr;
-      ph.y *= wr;
-      return ph;
+      return make_double2(ph.x * wr, ph.y * wr);
     };
+    // use(r, phase, the lane's column of the matrix) for every R vector in order
+    auto over_list = [&](auto use) __attribute__((always_inline)) {
+      double2 col[NE];
+      auto load = [&](int r, double2 (&c)[NE]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NE; i++) c[i] = M[(size_t)min(r, nr - 1) * NE * NE + i * NE + jc];
+      };
+      if constexpr (!kShare) {
+#pragma unroll 4
+        for (int r = 0; r < nr; r++) {
+          load(r, col);
+          use(r, phase(r), col);
+        }
+      } else {
+        double2 next[NE];
+        load(0, next);
+        for (int r0 = 0; r0 < nr; r0 += RC) {
+          const int n = min(RC, nr - r0);
+          __syncthreads();  // the last run's phases are read
+          for (int r = lane / MPW; r < n; r += NP) sPh[r * MPW + lane % MPW] = phase(r0 + r);
+          __syncthreads();
+          for (int r = 0; r < n; r++) {
+#pragma unroll
+            for (int i = 0; i < NE; i++) col[i] = next[i];
+            load(r0 + r + 1, next);
+            use(r0 + r, sPh[r * MPW + lane / NP], col);
+          }
+        }
+      }
+    };
+    // ---- Bloch sum ----
     double2 A[NE];
 #pragma unroll
     for (int i = 0; i < NE; i++) A[i] = make_double2(0.0, 0.0);
-    if (m.j < NE)
-      for (int r = 0; r < nr; r++) {
-        const double2 ph = phase(r);
+    over_list([&](int, double2 ph, const double2 (&col)[NE]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < NE; i++) A[i] = cadd(A[i], cmul(ph, M[(size_t)r * NE * NE + i * NE + jc]));
-      }
+      for (int i = 0; i < NE; i++) A[i] = cadd(A[i], cmul(ph, col[i]));
+    });
+    if (m.j >= NE)
+#pragma unroll
+      for (int i = 0; i < NE; i++) A[i] = make_double2(0.0, 0.0);
     // i R_a times the terms of the sum
-    auto deriv = [&](int a, double2(&d)[NE]) {
+    auto deriv = [&](int a, double2 (&d)[NE]) {
 #pragma unroll
       for (int i = 0; i < NE; i++) d[i] = make_double2(0.0, 0.0);
-      for (int r = 0; r < nr; r++) {
-        const double2 ph = phase(r);
+      over_list([&](int r, double2 ph, const double2 (&col)[NE]) __attribute__((always_inline)) {
         const double ra = Rcart[3 * r + a];
 #pragma unroll
         for (int i = 0; i < NE; i++) {
-          const double2 t = cmul(ph, M[(size_t)r * NE * NE + i * NE + jc]);
+          const double2 t = cmul(ph, col[i]);
           d[i].x -= ra * t.y;
           d[i].y += ra * t.x;
         }
-      }
+      });
     };
     eig_store<NE, MODE>(o, live, kl, A, m, stage, deriv, [](int b, int a) { return b == a ? 1.0 : 0.0; });
   }

@@ -877,8 +877,8 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
         for (int j = 0; j < nslab; j += slabs) {
           a.slab_lo = j;
           a.slab_hi = std::min(j + slabs, nslab);
-          if (gr && slabs > 1) {  // where each slab's rows start
-            EPH_HIP(c, launch_rates_wave(EPH_FP64, a, st, kCount));
+          if (gr && slabs > 1) {  // where each slab's rows start; one launch's counts are still there
+            if (slabs < nslab) EPH_HIP(c, launch_rates_wave(EPH_FP64, a, st, kCount));
             EPH_HIP(c, launch_slab_counts(a, 0, st));
           }
           EPH_HIP(c, launch_rates_wave(p->precision, a, st, gr ? kEmit : kRates));

@@ -144,23 +144,32 @@ struct Workspace {
   size_t per_state = 0;
 };
 
-Workspace plan_workspace(const eph_ctx *c, int N, int precision, int64_t nkl, int64_t ns, bool wave,
-                         bool gamma = false) {
+// Band ranges of the wave kernel, and with them the sums of the slabs of a
+// launch, which take the rest.
+size_t wave_sums_bytes(const eph_ctx *c, int N) {
+  const size_t ranges = 8 * (size_t)c->nw * N * wave_plane_groups(N);
+  return std::max(ranges, (size_t)N * N * N * c->nw * 4);
+}
+
+// occ_row: values per element of the FP64 occupation tables.
+Workspace plan_workspace(const eph_ctx *c, int N, int precision, int nt, int occ_row, int64_t nkl, int64_t ns,
+                         bool wave, bool gamma = false) {
   const size_t NQ = (size_t)N * N * N, nw = c->nw, nm = c->nm;
   const bool red = precision != EPH_FP64;
   Workspace w;
   size_t t = 16 * (size_t)N + 64;                                   // phase table, counters
   t += NQ * nw * 8 + NQ * nw * nw * 16 + NQ * nw * 24;              // eps, eigenvectors, velocities
   t += NQ * nm * 8 + NQ * nm * nm * 16;                             // phonon energies, displacements
-  if (red) t += NQ * nw * nw * 8 + NQ * nm * nm * 8;                // FP32 rotation tables
-  if (red && wave) t += NQ * (nw + nm) * EPH_MAX_TEMPS * 4;         // FP32 occupation tables
   const size_t ncol = (size_t)c->box.count() * nm * nw, K = (size_t)c->nre * nw;
   if (precision == EPH_FP32) t += ncol * K * 8;                     // FP32 copy of g
   if (precision == EPH_BF16X3) t += 4 * bf16_w_elems(c->nre, c->nw, (int)ncol);  // bf16 hi/lo of g
   if (wave) {
-    t += NQ * (nw + nm) * EPH_MAX_TEMPS * 8;                        // occupation tables
-    t += NQ * nw * 4;                                               // band ranges, sums of the slabs of a launch
+    size_t q_offset;
+    t += red ? wave_rec_bytes(c->nw, c->nm, nt, (int64_t)NQ, &q_offset)  // FP32 records
+             : NQ * (nw + nm) * (size_t)occ_row * 8;                     // occupation tables
+    t += wave_sums_bytes(c, N);
   } else {
+    if (red) t += NQ * nw * nw * 8 + NQ * nm * nm * 8;              // FP32 rotation tables
     t += NQ * nw * 10;                                              // energy-sorted lines
   }
   const size_t nl = (size_t)nkl + 1;
@@ -445,8 +454,11 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
     return fail(c, EPH_E_UNSUPPORTED,
                 "transition rates need FP64 and the wave rate kernel (cubic Rp box of edge 4 or 6)");
   const int64_t nkl = p->k_subset ? (int64_t)klist.size() : (int64_t)N * N * N;
+  // temperatures per element of the occupation tables (the k-batch kernels read
+  // full rows)
+  const int occ_row = kbatch_q > 0 ? EPH_MAX_TEMPS : occ_stride(p->n_temps);
   {  // the grid tables and lists alone must fit the budget (states not known yet)
-    const Workspace w0 = plan_workspace(c, N, p->precision, nkl, 0, gwave > 0);
+    const Workspace w0 = plan_workspace(c, N, p->precision, p->n_temps, occ_row, nkl, 0, gwave > 0);
     if (p->mem_budget_bytes > 0 && w0.fixed > (size_t)p->mem_budget_bytes)
       return fail(c, EPH_E_NOMEM, "mem_budget_bytes below the grid tables and lists (" + std::to_string(w0.fixed) +
                                       " bytes)");
@@ -521,7 +533,7 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
     // the wave-autonomous kernel where it applies, else the workgroup form
     const int gmax = gwave > 0 ? gwave : rates_group_max(nw, nm);
     // state batches: the per-batch buffers (X) within the budget
-    const Workspace ws = plan_workspace(c, N, p->precision, nkl, ns, gwave > 0, gr != nullptr);
+    const Workspace ws = plan_workspace(c, N, p->precision, p->n_temps, occ_row, nkl, ns, gwave > 0, gr != nullptr);
     int64_t max_states;
     if (p->mem_budget_bytes > 0) {
       const size_t need = ws.fixed + ws.per_state * (size_t)gmax;
@@ -580,9 +592,6 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
         EPH_HIP(c, launch_split_bf16(c->nre, nw, c->box.count() * nm * nw, c->wt64.as<double2>(), c->wtbf.p, st));
       }
     }
-    // temperatures per row of the occupation tables (the k-batch kernels read
-    // full rows)
-    const int occ_row = kbatch_q > 0 ? EPH_MAX_TEMPS : occ_stride(p->n_temps);
     // ---- tables of the rate kernel: the workgroup form's energy-sorted lines
     //      and FP32 rotation tables; the wave form's band ranges, and its
     //      occupations or FP32 records ----
@@ -691,7 +700,7 @@ static int32_t rates_impl(eph_ctx *c, const eph_rates_params *p, int64_t capacit
       const int64_t count_bytes = gr ? 8 * ns : 0;  // per slab and once more
       int64_t cap = kSlabSumBytes;
       if (p->mem_budget_bytes > 0)  // what the plan has for band ranges and slab sums
-        cap = std::min(cap, NQ * nw * 4 - 8 * (int64_t)nw * N * a.plane_groups);
+        cap = std::min(cap, (int64_t)wave_sums_bytes(c, N) - 8 * (int64_t)nw * N * a.plane_groups);
       slabs = (int)std::min<int64_t>(nslab, (cap - count_bytes) / (slab_bytes + count_bytes));
       slabs = std::max(slabs, 1);
       if (slabs > 1) {

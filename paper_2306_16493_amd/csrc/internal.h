@@ -66,6 +66,10 @@ __host__ __device__ inline int64_t plane_at(int64_t k, int c, int nc, int64_t n2
   return ((k / n2) * nc + c) * n2 + k % n2;
 }
 
+// A launch has less than 2^32 threads along x (HIP refuses some larger sizes and
+// wraps others): launchers whose work may pass that go in pieces of this many.
+constexpr int64_t kLaunchThreads = (int64_t)1 << 31;
+
 struct RpBox {
   int lo[3];
   int n[3];

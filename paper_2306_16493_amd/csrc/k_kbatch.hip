@@ -154,15 +154,22 @@ __global__ __launch_bounds__(64) void kb_step2_kernel(KBatchArgs a) {
 
 hipError_t launch_kbatch_step1(int64_t q0, int nb, int N, RpBox box, int nre, int nm, int nw, int ncol,
                                const double2 *wt, const double2 *uu, const double2 *tab, double2 *Gq, hipStream_t st) {
-  const int64_t n = (int64_t)nb * nre * nm * nw * nw;
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(kb_step1_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, q0, nb, N, box, nre, nm,
-                     nw, ncol, wt, uu, tab, Gq);
-  return hipGetLastError();
+  const int64_t per_q = (int64_t)nre * nm * nw * nw;
+  if (nb * per_q <= 0) return hipSuccess;
+  const int64_t piece = per_q < kLaunchThreads ? kLaunchThreads / per_q : 1;
+  hipError_t e = hipSuccess;
+  for (int64_t b = 0; b < nb && e == hipSuccess; b += piece) {
+    const int64_t m = nb - b < piece ? nb - b : piece;
+    hipLaunchKernelGGL(kb_step1_kernel, dim3((unsigned)((m * per_q + 255) / 256)), dim3(256), 0, st, q0 + b, (int)m, N,
+                       box, nre, nm, nw, ncol, wt, uu, tab, Gq + b * per_q);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 hipError_t launch_kbatch_step2(const KBatchArgs &a, hipStream_t st) {
   if (a.ns <= 0) return hipSuccess;
+  if (a.ns > kLaunchThreads / 64) return hipErrorInvalidConfiguration;
 #define EPH_KB(NW_, NM_) \
   if (a.nw == NW_ && a.nm == NM_) { \
     hipLaunchKernelGGL((kb_step2_kernel<NW_, NM_>), dim3((unsigned)a.ns), dim3(64), 0, st, a); \

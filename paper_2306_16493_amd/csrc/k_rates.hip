@@ -378,9 +378,15 @@ hipError_t launch_one(const RatesArgs &a, hipStream_t st) {
   auto kern = rates_kernel<T, NW, NM, SMAX>;
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L.total);
   if (e != hipSuccess) return e;
-  int64_t nblk = ((a.ng + 7) / 8) * 8;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(256), L.total, st, a);
-  return hipGetLastError();
+  constexpr int64_t kPiece = kLaunchThreads / 256;  // groups
+  for (int64_t g = 0; g < a.ng && e == hipSuccess; g += kPiece) {
+    RatesArgs b = a;
+    b.gstart = a.gstart + g;
+    b.ng = a.ng - g < kPiece ? a.ng - g : kPiece;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((b.ng + 7) / 8 * 8)), dim3(256), L.total, st, b);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 template <class T>

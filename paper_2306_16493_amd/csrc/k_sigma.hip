@@ -158,8 +158,8 @@ __global__ __launch_bounds__(kSigThreads) void density_kernel(int64_t nk, int64_
 }
 
 __global__ void to_f32_kernel(int64_t n, const double2 *__restrict__ in, float2 *__restrict__ out) {
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) out[i] = make_float2((float)in[i].x, (float)in[i].y);
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    out[i] = make_float2((float)in[i].x, (float)in[i].y);
 }
 
 }  // namespace
@@ -199,7 +199,8 @@ hipError_t launch_density(int N, int nw, const double *eps, int blo, int bhi, do
 
 hipError_t launch_to_f32(int64_t n, const double2 *in, float2 *out, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(to_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, in, out);
+  const int64_t nb = std::min<int64_t>((n + 255) / 256, 8192);
+  hipLaunchKernelGGL(to_f32_kernel, dim3((unsigned)nb), dim3(256), 0, st, n, in, out);
   return hipGetLastError();
 }
 

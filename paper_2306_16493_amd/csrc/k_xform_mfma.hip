@@ -44,7 +44,7 @@ __global__ void state_operand_kernel(int64_t ns, const int32_t *__restrict__ sk,
                                      int N, int64_t n2, int nw, int K, int KP, const int *__restrict__ re,
                                      const double2 *__restrict__ evec, const double2 *__restrict__ tab,
                                      __bf16 *__restrict__ ahi, __bf16 *__restrict__ alo) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t i = (blockIdx.y * (int64_t)gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
   const int64_t s = i / KP;
   const int kk = (int)(i - s * KP);
   if (s >= ns || kk >= KP) return;
@@ -225,9 +225,9 @@ hipError_t launch_xform_bf16x3(int64_t ns, const int32_t *sk, const int32_t *sn,
   const size_t nw_el = bf16_w_elems(nre, nw, ncol);
   const __bf16 *whi = static_cast<const __bf16 *>(wbf), *wlo = whi + nw_el;
   __bf16 *ahi = static_cast<__bf16 *>(abf), *alo = ahi + (size_t)ns * KP;
-  const int64_t na = ns * KP;
-  hipLaunchKernelGGL(state_operand_kernel, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, st, ns, sk, sn, N, n2,
-                     nw, K, KP, re, evec, tab, ahi, alo);
+  const int64_t nb = (ns * KP + 255) / 256, nx = nb < kLaunchThreads / 256 ? nb : kLaunchThreads / 256;
+  hipLaunchKernelGGL(state_operand_kernel, dim3((unsigned)nx, (unsigned)((nb + nx - 1) / nx)), dim3(256), 0, st, ns, sk, sn,
+                     N, n2, nw, K, KP, re, evec, tab, ahi, alo);
   const int tiles_m = (int)((ns + TM - 1) / TM), tiles_n = (ncol2 + TN - 1) / TN;
   const int64_t ntile = (int64_t)tiles_m * tiles_n;
   const int64_t grid = (ntile + 7) / 8 * 8;

@@ -806,9 +806,16 @@ hipError_t launch_wave(const RatesArgs &a, hipStream_t st) {
   auto kern = rates_wave_kernel<T, NW, NM, NB, NT, MODE>;
   hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
   if (e != hipSuccess) return e;
-  const int64_t grid = ((a.ns_launch + 7) / 8) * 8;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid, (unsigned)(a.slab_hi - a.slab_lo)), dim3(LY::WPB * 64), sh, st, a);
-  return hipGetLastError();
+  constexpr int64_t kPiece = kLaunchThreads / (LY::WPB * 64);  // states
+  for (int64_t i = 0; i < a.ns_launch && e == hipSuccess; i += kPiece) {
+    RatesArgs b = a;
+    b.s_lo = a.s_lo + i;
+    b.ns_launch = a.ns_launch - i < kPiece ? a.ns_launch - i : kPiece;
+    const int64_t grid = ((b.ns_launch + 7) / 8) * 8;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid, (unsigned)(a.slab_hi - a.slab_lo)), dim3(LY::WPB * 64), sh, st, b);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 template <class T, int NW, int NM, int NB, int MODE>

@@ -32,14 +32,14 @@
 //
 // What bounds it.  Al-like model (4 bands, 3 modes, box 6^3), 71^3, 3
 // temperatures, FP32: 322 ms for 1.2e10 vertices, about 170 ms of it the
-// vertices (534 vector instructions to a pass of 64), 85 the sieve, 27 Z, 18
+// vertices (539 vector instructions to a pass of 64), 85 the sieve, 27 Z, 18
 // the reading of X; vector instructions issue in nine cycles of ten.  One wave per
 // state and line, each with its own Z by vector operations, took 648 ms; 128
 // threads per workgroup leave fewer waves waiting at a barrier than 256.  The
 // tables are stored by plane and component so that the lanes' reads,
 // neighbours in p or q, run along lines: an array of records, one per gather,
 // made the L1 the bound (160^3, FP32, 1 temperature: 173 ms against 101).
-// FP64, 100^3, 4 % of the states: 167 ms (480 per line), 105 of it the
+// FP64, 100^3, 4 % of the states: 167 ms, 105 of it the
 // vertices, whose gathers, 370 bytes each, come from the L2s at 11 TB/s.
 #include <cstddef>
 #include <type_traits>
@@ -87,32 +87,6 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// exp(x) for x <= 0 by Cody and Waite's reduction x = n ln 2 + r (ln 2 as a
-// 32-bit head and a tail) and the Taylor series of e^r to r^13 (|r| <= 0.347:
-// remainder below 5e-18), scaled by 2^n.  No special values to tell apart, so
-// 19 instructions.
-__device__ __forceinline__ double exp_neg(double x) {
-  x = fmax(x, -800.0);
-  const double n = rint(x * 1.4426950408889634074);
-  double r = fma(n, -6.93147180369123816490e-01, x);  // head of ln 2, then its tail
-  r = fma(n, -1.90821492927058770002e-10, r);
-  double p = 1.0 / 6227020800.0;
-  p = fma(p, r, 1.0 / 479001600.0);
-  p = fma(p, r, 1.0 / 39916800.0);
-  p = fma(p, r, 1.0 / 3628800.0);
-  p = fma(p, r, 1.0 / 362880.0);
-  p = fma(p, r, 1.0 / 40320.0);
-  p = fma(p, r, 1.0 / 5040.0);
-  p = fma(p, r, 1.0 / 720.0);
-  p = fma(p, r, 1.0 / 120.0);
-  p = fma(p, r, 1.0 / 24.0);
-  p = fma(p, r, 1.0 / 6.0);
-  p = fma(p, r, 0.5);
-  p = fma(p, r, 1.0);
-  p = fma(p, r, 1.0);
-  return ldexp(p, (int)n);
-}
-
 // (a mod N) for 0 <= a < 2^14, N <= 512, inv_n the float nearest 1/N: the
 // quotient of a + 1/2 is at least 1/(2 N) from a whole number, the float
 // product within 2^-9 / N of it, so the truncation is exact
@@ -132,7 +106,12 @@ struct WaveLayout {
   static constexpr int ROWS = NB * C;               // (p1, channel) rows of Y and Z
   static constexpr int MT = (ROWS + 15) / 16;       // 16-row tiles
   static constexpr int KS = (2 * NB + 3) / 4;       // 4-deep steps over (p2, re/im)
-  static constexpr int WPB = (C >= 48 && sizeof(T) == 8) ? 8 : C >= 48 ? 4 : 2;  // waves per workgroup
+  // Waves per workgroup.  48 channels: each wave's share of Y has to fit its
+  // registers beside a vertex (Si-like 130^3, FP64: 95.8 ms with 8, 158 with 4;
+  // FP32: 42.5 with 4, 74.5 with 2, 64.8 with 8).  24 channels: 4 are from 4 %
+  // faster to 10 % slower than 2 (8 bands with 3 modes and 4 with 6, box 4^3,
+  // 30^3 and 60^3, both precisions).
+  static constexpr int WPB = (C >= 48 && sizeof(T) == 8) ? 8 : C >= 48 ? 4 : 2;
   static constexpr int TPW = (MT + WPB - 1) / WPB;  // tiles per wave
   // most lines per batch: the matrix product's columns (32 lines with 4 waves
   // to a workgroup took 443 ms for 421 at Al-like 71^3, FP32)
@@ -168,9 +147,12 @@ struct WaveLayout {
   }
 };
 
-// Waves per SIMD the register allocation targets: as many as leave (almost)
-// no spills.  FP64 with 3 modes: 244 ms with 3, 269 with 2 (Al-like, 100^3);
-// FP32 with 6: 63 ms with 3, 94 with 4, 77 with 2 (Si-like, 130^3).
+// Waves per SIMD the register allocation targets, as timed: FP64 with 3 modes
+// 244 ms with 3, 269 with 2 (Al-like, 100^3); FP32 with 6 modes 63 ms with 3, 94
+// with 4, 77 with 2 (Si-like, 130^3).  Some instances spill at that: FP32 with 6
+// modes 20 to 248 bytes a lane (8 bands, box 6^3, one temperature: 116), with 8
+// bands and 3 modes up to 92 in FP32 and 88 in FP64, with 4 and 3 at several
+// temperatures 16 in FP32.
 template <class T, int NW, int NM>
 __host__ __device__ constexpr int waves_per_eu() {
   return sizeof(T) == 4 ? (NM == 6 ? 3 : 4) : (NW * NM >= 48 ? 2 : 3);
@@ -540,7 +522,10 @@ void rates_wave_kernel(RatesArgs a) {
       //      vertices more take fewer chunks; its band ranges load meanwhile ----
       const int turn = (wave - rot) & (WPB - 1);  // this wave's turn in the round
       if (!more && b + 1 < nbatch) {
-        constexpr int kPassChunks = NM == 3 ? 32 : 256;  // groups of sieve that cost a pass
+        // groups of sieve that cost a pass; with 6 modes it hardly matters (Si-like
+        // 48^3, FP64: 20.16 ms with 256, 20.21 with 32, 20.15 with 1024; 130^3,
+        // FP32: 42.5, 41.3, 42.5)
+        constexpr int kPassChunks = NM == 3 ? 32 : 256;
         const int nc = (min(nlb, N - (b + 1) * nlb) * N + 15) >> 4;
         const int heavy = ((total + 63) >> 6) % WPB, light = WPB - heavy;
         const int x = heavy ? max(0, nc - light * kPassChunks) / WPB : 0, rest_c = nc - heavy * x;

@@ -32,7 +32,7 @@
 //
 // What bounds it.  Al-like model (4 bands, 3 modes, box 6^3), 71^3, 3
 // temperatures, FP32: 322 ms for 1.2e10 vertices, about 170 ms of it the
-// vertices (539 vector instructions to a pass of 64), 85 the sieve, 27 Z, 18
+// vertices (535 vector instructions to a pass of 64), 85 the sieve, 27 Z, 18
 // the reading of X; vector instructions issue in nine cycles of ten.  One wave per
 // state and line, each with its own Z by vector operations, took 648 ms; 128
 // threads per workgroup leave fewer waves waiting at a barrier than 256.  The
@@ -699,7 +699,7 @@ void rates_wave_kernel(RatesArgs a) {
             const double2 f2 = at_offset(reinterpret_cast<const double2 *>(occ_b) + (t / 2) * n2, (m * (uint32_t)(2 * n2) + e) * 16u);
             f = t % 2 ? f2.y : f2.x;
           }
-          ct[t] += fma(f, sa, (T(1) - f) * sb);
+          ct[t] = fma(f, sa, ct[t]) + fma(-f, sb, sb);  // (1 - f) sb rounded once
         }
         if (live) {
 #pragma unroll

@@ -31,7 +31,7 @@
 // planes are fixed, so results are bit-reproducible.
 //
 // What bounds it.  Al-like model (4 bands, 3 modes, box 6^3), 71^3, 3
-// temperatures, FP32: 322 ms for 1.2e10 vertices, about 170 ms of it the
+// temperatures, FP32: 328 ms for 1.2e10 vertices, about 172 ms of it the
 // vertices (535 vector instructions to a pass of 64), 85 the sieve, 27 Z, 18
 // the reading of X; vector instructions issue in nine cycles of ten.  One wave per
 // state and line, each with its own Z by vector operations, took 648 ms; 128
@@ -39,7 +39,7 @@
 // tables are stored by plane and component so that the lanes' reads,
 // neighbours in p or q, run along lines: an array of records, one per gather,
 // made the L1 the bound (160^3, FP32, 1 temperature: 173 ms against 101).
-// FP64, 100^3, 4 % of the states: 167 ms, 105 of it the
+// FP64, 100^3, 4 % of the states: 164 ms, 102 of it the
 // vertices, whose gathers, 370 bytes each, come from the L2s at 11 TB/s.
 #include <cstddef>
 #include <type_traits>
